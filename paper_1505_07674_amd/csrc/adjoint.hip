@@ -40,61 +40,51 @@ __device__ __forceinline__ void resolve(const WorkArgs& w, int& point, int& tile
 // ---------------------------------------------------------------------------
 // g = A^T rho, interior pixels: g[u][v] = sum_{a,b} rho0[u+a][v+b] F[a][b].
 // ---------------------------------------------------------------------------
-// TWc = 0 with P >= 0: a wide tile (runtime width, LDS stride WIDE_STRIDE), as
-// in the forward stencil.
-template <int P, int TWc, int ROWS>
-__global__ __launch_bounds__(P >= 0 && TWc == 0 ? WIDE_MAX_THREADS : 512) void adj_psf_kernel(
-    WorkArgs w, const float* __restrict__ R, float* __restrict__ G) {
-  constexpr bool WIDE = P >= 0 && TWc == 0;
-  extern __shared__ float S[];
+// The forward stencil's tiles and threads, with zeros outside the image and the
+// unflipped taps.
+template <int KP>
+__global__ __launch_bounds__(PSF_MAX_THREADS, KP <= 24 ? 4 : 2) void adj_psf_kernel(WorkArgs w,
+                                                                                    const float* __restrict__ R,
+                                                                                    float* __restrict__ G) {
+  constexpr int Q = PSF_Q, C = PSF_C;
+  extern __shared__ __align__(16) float S[];
   int point, tile;
   resolve(w, point, tile);
-  const SysDesc sd = w.sys_table ? w.sys_table[w.point_sys ? w.point_sys[point] : 0] : w.single;
-  const int64_t loff = w.point_loff ? w.point_loff[point] : 0;
-  const int p = P >= 0 ? P : sd.ph / 2;
-  const int q = P >= 0 ? P : sd.pw / 2;
-  const int TW = (P >= 0 && !WIDE) ? TWc : sd.TW, TH = sd.TH;
-  const int SW = TW + 2 * q, SH = TH + 2 * p;     // staged columns and rows
-  const int LS = WIDE ? WIDE_STRIDE : SW;         // LDS row stride
-  const int ty = tile / sd.tiles_x, tx = tile - ty * sd.tiles_x;
+  point = uniform(point);
+  tile = uniform(tile);
+  const SysDesc& sd = w.sys_table ? w.sys_table[w.point_sys ? w.point_sys[point] : 0] : w.single;
+  const int64_t loff = uniform(w.point_loff ? w.point_loff[point] : (int64_t)0);
+  const int H = uniform(sd.H), W = uniform(sd.W), TW = uniform(sd.TW), TH = uniform(sd.TH);
+  const int ph = uniform(sd.ph), pw = uniform(sd.pw), tiles_x = uniform(sd.tiles_x);
+  gbyte_in* taps = uniform_in(sd.psfn + 2 * ph * pw);
+  gbyte_in* Rp = uniform_in(R + loff);
+  gbyte_out* Gp = uniform_out(G + loff);
+  const int ty = tile / tiles_x, tx = tile - ty * tiles_x;
   const int x0 = tx * TW, y0 = ty * TH;
-  const float* __restrict__ Rp = R + loff;
   const int tid = threadIdx.x;
-  const int jx = tid % TW, jy = tid / TW;
-  const int rows_per_pass = blockDim.x / TW;
-  for (int row = jy; row < SH; row += rows_per_pass) {
-    const int gi = y0 + row - p;
-    for (int col = jx; col < SW; col += TW) {
-      const int gj = x0 + col - q;
-      S[row * LS + col] = (gi >= 0 && gi < sd.H && gj >= 0 && gj < sd.W) ? Rp[(size_t)gi * sd.W + gj] : 0.0f;
-    }
-  }
+  const int cs = psf_col_stride(TH, KP);
+  float* __restrict__ T = S + (TW + pw - 1) * cs;
+  const bool mine = stage_tile<false>(S, Rp, H, W, TW + pw - 1, psf_tile_rows(TH, KP) / 4, cs, y0 - ph / 2, x0 - pw / 2);
+  stage_taps(T, taps, ph, pw, tap_stride(KP), 3);
+  const bool finite = __syncthreads_and(mine);
+  const int nc = TW / C;   // threads per row of threads
+  const int jr = tid / nc;
+  const bool own = jr < TH / (4 * Q);
+  const int row = own ? jr * 4 * Q : 0, col = own ? (tid - jr * nc) * C : 0;
+  f32x4_t acc[C][Q];
+  stencil<KP, Q, C>(S + col * cs + row, T, ph, pw, cs, finite, acc);
   __syncthreads();
-  const int i0 = jy * ROWS;
-  float acc[ROWS];
+  if (own) outputs_to_lds<Q, C>(S, cs, row, col, acc);
+  __syncthreads();
+  for (int it = tid; it < TW * (TH / 4); it += blockDim.x) {
+    const int g = it / TW, c = it - g * TW;
+    const int gj = x0 + c, gi0 = y0 + 4 * g;
+    if (gj <= 0 || gj >= W - 1) continue;   // border pixels: the folded tables
+    const f32x4_t v = *(const f32x4_t*)(S + c * cs + 4 * g);
+    const unsigned W4 = 4u * (unsigned)W, o = (unsigned)gi0 * W4 + 4u * (unsigned)gj;
 #pragma unroll
-  for (int r = 0; r < ROWS; ++r) acc[r] = 0.0f;
-  if (P >= 0) {
-    constexpr int K = 2 * (P > 0 ? P : 0) + 1;
-    constexpr int SWc = WIDE ? WIDE_STRIDE : (TWc > 0 ? TWc : 1) + K - 1;
-    // taps F[k][l] of stencil column l, contiguous in k
-    stencil_columns<K, SWc, ROWS>(S + i0 * SWc + jx, uniform_const(sd.psfn + 2 * K * K), acc);
-  } else {
-    const float* __restrict__ F = sd.psfn;
-    const int KH = 2 * p + 1, KW = 2 * q + 1;
-    for (int l = 0; l < KW; ++l)
-      for (int k = 0; k < KH; ++k) {
-        const float f = F[k * KW + l];
-#pragma unroll
-        for (int r = 0; r < ROWS; ++r) acc[r] = fmaf(f, S[(i0 + r + k) * SW + jx + l], acc[r]);
-      }
-  }
-  const int gj = x0 + jx;
-#pragma unroll
-  for (int r = 0; r < ROWS; ++r) {
-    const int gi = y0 + i0 + r;
-    const bool border = gi == 0 || gi == sd.H - 1 || gj == 0 || gj == sd.W - 1;
-    if (gi < sd.H && gj < sd.W && i0 + r < TH && !border) G[loff + (size_t)gi * sd.W + gj] = acc[r];
+    for (int r = 0; r < 4; ++r)
+      if (gi0 + r > 0 && gi0 + r < H - 1) store_at(Gp, o + (unsigned)r * W4, v[r]);
   }
 }
 
@@ -659,41 +649,22 @@ __global__ __launch_bounds__(FGRAD_THREADS) void finalize_grad_kernel(
   for (int k = 0; k < NPAR; ++k) grad[(size_t)p * NPAR + k] = (float)g[k];
 }
 
-template <int P, int TWc, int R>
-hipError_t launch_adj_t(const WorkArgs& w, const float* R_, float* G, int n_blocks, int threads, size_t lds,
-                        hipStream_t st) {
-  return for_item_parts(w, n_blocks, [&](const WorkArgs& part, int n) {
-    hipLaunchKernelGGL((adj_psf_kernel<P, TWc, R>), dim3(n), dim3(threads), lds, st, part, R_, G);
-    return hipGetLastError();
-  });
-}
-
-template <int P, int R>
-hipError_t launch_adj_w(int TW, const WorkArgs& w, const float* R_, float* G, int n_blocks, int threads, size_t lds,
-                        hipStream_t st) {
-  if (TW == 64) return launch_adj_t<P, 64, R>(w, R_, G, n_blocks, threads, lds, st);
-  return launch_adj_t<P, 32, R>(w, R_, G, n_blocks, threads, lds, st);
-}
-
 }  // namespace
 
-hipError_t launch_adjoint_psf(const WorkArgs& w, const float* R, float* G, int n_blocks, int square_psf, int TW,
-                              int TH, int ph, int pw, int n_points, int H, int W, hipStream_t st) {
+hipError_t launch_adjoint_psf(const WorkArgs& w, const float* R, float* G, int n_blocks, int TW, int TH, int ph,
+                              int pw, int n_points, int H, int W, hipStream_t st) {
   if (n_blocks <= 0) return hipSuccess;
-  const int Rr = psf_rows(square_psf, TW, TH);
-  const int threads = TW * (TH / Rr);
-  const size_t lds = psf_lds_bytes(square_psf, TW, TH, ph, pw);
-  hipError_t e;
-  if (psf_wide(square_psf, TW)) {
-    e = launch_adj_t<10, 0, 8>(w, R, G, n_blocks, threads, lds, st);
-  } else if (psf_specialised(square_psf, TW)) {
-    if (square_psf == 21) e = Rr == 8 ? launch_adj_w<10, 8>(TW, w, R, G, n_blocks, threads, lds, st)
-                                      : launch_adj_w<10, 4>(TW, w, R, G, n_blocks, threads, lds, st);
-    else if (square_psf == 7) e = launch_adj_w<3, 4>(TW, w, R, G, n_blocks, threads, lds, st);
-    else e = launch_adj_w<0, 4>(TW, w, R, G, n_blocks, threads, lds, st);
-  } else {
-    e = launch_adj_t<-1, 0, 4>(w, R, G, n_blocks, threads, lds, st);
-  }
+  const int threads = psf_threads(TW, TH);
+  const size_t lds = psf_lds_bytes(TW, TH, ph, pw);
+  if (threads > PSF_MAX_THREADS || lds > PSF_MAX_LDS || TH % (4 * PSF_Q) != 0 || TW % PSF_C != 0)
+    return hipErrorInvalidValue;
+  const hipError_t e = with_psf_steps(ph, [&](auto steps) {
+    constexpr int KP = decltype(steps)::value;
+    return for_item_parts(w, n_blocks, [&](const WorkArgs& part, int n) {
+      hipLaunchKernelGGL((adj_psf_kernel<KP>), dim3(n), dim3(threads), lds, st, part, R, G);
+      return hipGetLastError();
+    });
+  });
   if (e != hipSuccess) return e;
   const int nseg = border_segments(H, W);
   // the window, and with 21-wide tables also the four tables of a segment

@@ -300,8 +300,7 @@ int lensed_render(lensed_ctx* c, const lensed_system* sys, const float* theta, f
   LENSED_HIP(c, launch_prologue(theta, 1, pc, p64, nullptr, sd, nullptr, 1, cl.count, st));
   LENSED_HIP(c, launch_render(w, pc, p64, L, sd.n_rtiles, cl, st));
   if (apply_psf)
-    LENSED_HIP(c, launch_psf(w, L, image, nullptr, 0, sd.n_ptiles, square_psf_code(sd.ph, sd.pw), sd.TW, sd.TH,
-                             sd.ph, sd.pw, st));
+    LENSED_HIP(c, launch_psf_single(w, L, image, nullptr, 0, st));
   return LENSED_OK;
 }
 
@@ -346,8 +345,7 @@ int lensed_render_composite(lensed_ctx* c, const lensed_system* sys, const float
   LENSED_HIP(c, launch_sum_images(L, (int64_t)npix, K, sky_px, apply_psf ? L : image, st));
   w.point0 = 0;
   if (apply_psf)
-    LENSED_HIP(c, launch_psf(w, L, image, nullptr, 0, sd.n_ptiles, square_psf_code(sd.ph, sd.pw), sd.TW, sd.TH,
-                             sd.ph, sd.pw, st));
+    LENSED_HIP(c, launch_psf_single(w, L, image, nullptr, 0, st));
   return LENSED_OK;
 }
 
@@ -424,8 +422,7 @@ int lensed_loglike(lensed_ctx* c, const lensed_system* sys, const float* theta, 
   w.single = sd;
   LENSED_HIP(c, launch_prologue(theta, 1, pc, p64, nullptr, sd, nullptr, 1, cl.count, st));
   LENSED_HIP(c, launch_render(w, pc, p64, L, sd.n_rtiles, cl, st));
-  LENSED_HIP(c, launch_psf(w, L, nullptr, part, 1, sd.n_ptiles, square_psf_code(sd.ph, sd.pw), sd.TW, sd.TH, sd.ph,
-                           sd.pw, st));
+  LENSED_HIP(c, launch_psf_single(w, L, nullptr, part, 1, st));
   LENSED_HIP(c, launch_finalize(part, nullptr, nullptr, 1, sd.n_ptiles, logl, st));
   return LENSED_OK;
 }
@@ -460,7 +457,7 @@ int run_batch(lensed_ctx* c, const lensed_system* systems, int n_systems, const 
       // warm-up) and keep
       // the fastest for every later plan over the same set of system shapes.
       const std::vector<TileShape> cand = c->tiles.ranked(systems, n_systems, 6);
-      TileShape best = cand.empty() ? TileShape{32, 32} : cand[0];
+      TileShape best = cand.empty() ? TileShape{16, 16} : cand[0];
       float best_ms = 1e30f;
       for (const TileShape& t : cand) {
         BatchPlan trial;
@@ -696,8 +693,7 @@ int lensed_render_model(lensed_ctx* c, const lensed_system* sys, const lensed_mo
   LENSED_HIP(c, launch_model_prologue(theta, 1, spec_params(spec), spec, mc, st));
   LENSED_HIP(c, launch_model_render(w, spec, mc, L, sd.n_rtiles, st));
   if (apply_psf)
-    LENSED_HIP(c, launch_psf(w, L, image, nullptr, 0, sd.n_ptiles, square_psf_code(sd.ph, sd.pw), sd.TW, sd.TH,
-                             sd.ph, sd.pw, st));
+    LENSED_HIP(c, launch_psf_single(w, L, image, nullptr, 0, st));
   return LENSED_OK;
 }
 

@@ -132,13 +132,18 @@ hipError_t launch_rule_error(const WorkArgs& w, const PointConst* pcs, float* E,
 // mode 1: PSF convolution fused with the weighted chi^2; one compensated
 //         (hi, lo) float pair per tile is written to partials.
 // mode 2: as mode 1, and the weighted residual w (d - L*) is written to out.
-// Every system of one launch uses the same TW x TH output tile (the block is
-// TW x TH/R threads, R = psf_rows()). square_psf = 21, 7 or 1 with TW = 32 or 64
-// selects a specialised stencil when every PSF of the launch has that square
-// size; anything else runs the generic one.
-hipError_t launch_psf(const WorkArgs& w, const float* L, float* out, float2* partials, int mode, int n_blocks,
-                      int square_psf, int TW, int TH, int max_ph, int max_pw, hipStream_t stream);
-
+// Every system of one launch uses the same TW x TH output tile (stencil.h);
+// max_ph, max_pw: the largest PSF of the launch. group: rows of a Kahan chain of the chi^2 (8 or
+// 4, dividing TH): what is rounded of a product before it is summed depends on
+// it, so it follows psf_group, not the tile.
+hipError_t launch_psf(const WorkArgs& w, const float* L, float* out, float2* partials, int mode, int n_blocks, int TW,
+                      int TH, int max_ph, int max_pw, int group, hipStream_t stream);
+// One image (w.single, with a tile of TileCache::latency_best) on an idle chip.
+hipError_t launch_psf_single(const WorkArgs& w, const float* L, float* out, float2* partials, int mode,
+                             hipStream_t stream);
+// Rows of a Kahan chain in a launch of many images whose PSFs have the given
+// square size (0: not all of one square size); one image at a time always has 4.
+inline int psf_group(int square_psf) { return square_psf == 21 ? 8 : 4; }
 
 // log L = -1/2 * sum over the point's tiles of (hi + lo), in float64.
 hipError_t launch_finalize(const float2* partials, const int* point_pbase, const int* point_ntiles, int n_points,
@@ -146,8 +151,8 @@ hipError_t launch_finalize(const float2* partials, const int* point_pbase, const
 
 // g = A^T rho for every point of a single-system launch (same tiles as the PSF
 // kernel, border pixels by the folded tables); R and G use the image offsets.
-hipError_t launch_adjoint_psf(const WorkArgs& w, const float* R, float* G, int n_blocks, int square_psf, int TW,
-                              int TH, int ph, int pw, int n_points, int H, int W, hipStream_t st);
+hipError_t launch_adjoint_psf(const WorkArgs& w, const float* R, float* G, int n_blocks, int TW, int TH, int ph,
+                              int pw, int n_points, int H, int W, hipStream_t st);
 
 // d log L / d sky of every composite model m (its points m K .. m K + K - 1,
 // its rho in R at the offset of its first image): the sky adds sky d^2 to

@@ -18,6 +18,9 @@ namespace lensed {
 struct TileShape {
   int TW, TH;
 };
+// The tiles of psf_single_kernel (one image at a time).
+constexpr int64_t SINGLE_MAX_PIXELS = 1 << 18;
+inline bool is_single_tile(TileShape t) { return (t.TW == 32 && t.TH == 16) || (t.TW == 16 && t.TH == 8); }
 
 // Chooses the TW x TH output tile of the PSF/chi^2 kernel for a launch. The
 // model counts lane slots of the stencil (ragged tiles and partly idle waves
@@ -26,8 +29,8 @@ struct TileShape {
 // fastest per set of system shapes, which then overrides the model.
 class TileCache {
  public:
-  // The tile for one image (the single-point entry points): the specialised
-  // 32- or 64-wide tiles, ranked by latency, not by throughput.
+  // The tile for one image (the single-point entry points): ranked by latency,
+  // not by throughput.
   static TileShape latency_best(const lensed_system& s);
   TileShape choose(const lensed_system& s);
   TileShape choose_common(const lensed_system* s, int n);
@@ -43,15 +46,13 @@ class TileCache {
   }
   bool has_render_measured(const lensed_system* s, int n) const { return render_measured_.count(render_key(s, n)) != 0; }
   void set_render_measured(const lensed_system* s, int n, RenderSchedule r) { render_measured_[render_key(s, n)] = r; }
-  static double model_cost(int H, int W, int ph, int pw, TileShape t, int sq);
-  static std::vector<TileShape> candidates(int sq, const lensed_system* s = nullptr, int n = 0);
+  static double model_cost(int H, int W, int ph, int pw, TileShape t, int max_ph);
   // The cost model's best tile for one system (no cache, no allocation).
   static TileShape model_best(const lensed_system& s);
 
  private:
   static std::string key(const lensed_system* s, int n);
   static std::string render_key(const lensed_system* s, int n);
-  static int launch_square(const lensed_system* s, int n);
   std::map<std::tuple<int, int, int, int>, TileShape> cache_;
   std::map<std::string, TileShape> measured_;
   std::map<std::string, RenderSchedule> render_measured_;

@@ -10,48 +10,37 @@
 namespace lensed {
 
 namespace {
-// Calls f(t) for every candidate PSF output tile of a launch over systems s
-// (sq: the launch's square-PSF code); a shape may come more than once.
+// Calls f(t) for every candidate PSF output tile of a launch over systems s; a
+// shape may come more than once. Widths: a few plain ones and the images' widths
+// cut into one to four parts, heights likewise, so that the tiles cover an image
+// without ragged columns or rows.
 template <class F>
-void each_candidate(int sq, const lensed_system* s, int n, F f) {
-  const int tws[] = {16, 32, 40, 48, 64};
-  const int ths[] = {16, 20, 24, 32, 40, 48, 64};
+void each_candidate(const lensed_system* s, int n, F f) {
+  int mph = 1, mpw = 1;
+  for (int i = 0; i < n; ++i) mph = std::max(mph, s[i].psf_h), mpw = std::max(mpw, s[i].psf_w);
+  auto up = [](int x, int m) { return (x + m - 1) / m * m; };
+  std::vector<int> tws = {16, 32, 48, 64}, ths = {16, 24, 32, 40, 48, 64};
+  for (int i = 0; i < n; ++i)
+    for (int parts = 1; parts <= 4; ++parts) {
+      tws.push_back(up((s[i].width + parts - 1) / parts, PSF_C));
+      ths.push_back(up((s[i].height + parts - 1) / parts, 4 * PSF_Q));
+    }
+  for (auto* v : {&tws, &ths}) {
+    std::sort(v->begin(), v->end());
+    v->erase(std::unique(v->begin(), v->end()), v->end());
+  }
   for (int tw : tws)
-    for (int th : ths) {
-      const int threads = tw * th / psf_rows(sq, tw, th);
-      if (threads >= 64 && threads <= 512) f(TileShape{tw, th});
-    }
-  // Wide tiles of the 21 x 21 stencil: a whole image row, or a half or a third
-  // of it, so that the tiles cover the image without ragged columns; heights
-  // whose LDS block stays within 64 KiB.
-  for (int i = 0; s && i < n; ++i)
-    for (int parts = 1; parts <= 3; ++parts) {
-      const int tw = (s[i].width + parts - 1) / parts;
-      if (!psf_wide(sq, tw)) continue;
-      for (int th : {16, 24, 32, 40}) {
-        const int threads = tw * th / psf_rows(sq, tw, th);
-        if (threads < 64 || threads > WIDE_MAX_THREADS || psf_lds_bytes(sq, tw, th, 21, 21) > 65536) continue;
+    for (int th : ths)
+      if (psf_threads(tw, th) <= PSF_MAX_THREADS && psf_lds_bytes(tw, th, mph, mpw) <= PSF_MAX_LDS)
         f(TileShape{tw, th});
-      }
-    }
 }
 }  // namespace
 
-std::vector<TileShape> TileCache::candidates(int sq, const lensed_system* s, int n) {
-  std::vector<TileShape> out;
-  each_candidate(sq, s, n, [&](TileShape t) {
-    if (std::none_of(out.begin(), out.end(), [&](const TileShape& o) { return o.TW == t.TW && o.TH == t.TH; }))
-      out.push_back(t);
-  });
-  return out;
-}
-
 TileShape TileCache::model_best(const lensed_system& s) {
-  TileShape best{32, 32};
+  TileShape best{16, 16};
   double bc = 1e300;
-  const int sq = square_psf_code(s.psf_h, s.psf_w);
-  each_candidate(sq, &s, 1, [&](TileShape t) {
-    const double cst = model_cost(s.height, s.width, s.psf_h, s.psf_w, t, sq);
+  each_candidate(&s, 1, [&](TileShape t) {
+    const double cst = model_cost(s.height, s.width, s.psf_h, s.psf_w, t, s.psf_h);
     if (cst < bc) {
       bc = cst;
       best = t;
@@ -60,48 +49,27 @@ TileShape TileCache::model_best(const lensed_system& s) {
   return best;
 }
 
-// Lane slots of one launch: per tile, the block's lanes (whole waves) times the
-// per-thread work of R outputs (R ph pw FMAs and pw (R + ph - 1) LDS reads),
-// plus the LDS staging of the tile and its halo and a fixed block cost. The
-// generic stencil (runtime sizes, taps by vector loads) costs twice as much
-// per tap as the specialised ones. sq is the square-PSF code of the launch
-// (-1 when its systems differ), which decides the kernel and R.
-double TileCache::model_cost(int H, int W, int ph, int pw, TileShape t, int sq) {
-  const int R = psf_rows(sq, t.TW, t.TH);
+// Lane slots of one launch, in wave-instruction times of v_fma: per tile, the
+// block's lanes (whole waves) times the matrix instructions of a thread (two
+// slots each) and its LDS reads, plus the staging of the tile and its halo, the
+// pass over the outputs and a fixed block cost. max_ph: the largest PSF of the
+// launch, which sets the matrix steps.
+double TileCache::model_cost(int H, int W, int ph, int pw, TileShape t, int max_ph) {
+  (void)ph;
   const double ntiles = (double)((W + t.TW - 1) / t.TW) * (double)((H + t.TH - 1) / t.TH);
-  const int threads = t.TW * t.TH / R;
-  const double lanes = 64.0 * ((threads + 63) / 64);
-  const double tap = psf_specialised(sq, t.TW) ? 1.0 : 2.0;
-  const double per_lane = tap * (double)R * ph * pw + 0.5 * (double)pw * (R + ph - 1);
-  const double staging = 6.0 * (double)(t.TW + pw - 1) * (double)(t.TH + ph - 1);
-  return ntiles * (lanes * per_lane + staging + 2000.0);
+  const double lanes = (double)psf_threads(t.TW, t.TH);
+  const int KP = psf_steps(max_ph);
+  const double per_lane = (double)pw * (2.0 * PSF_Q * PSF_C * KP + 0.5 * (KP + 4 * PSF_Q));
+  const double staging = 6.0 * (double)(t.TW + pw - 1) * (double)psf_tile_rows(t.TH, KP);
+  return ntiles * (lanes * (per_lane + 200.0) + staging + 20.0 * t.TW * t.TH + 4000.0);
 }
 
-// One image runs on a few blocks, so what counts is how long a block takes:
-// its waves share the CU's four SIMDs, and each thread applies R ph pw taps.
-// Cost: (waves per SIMD, from the block's own waves or from the whole launch
-// spread over 1024 SIMDs, whichever is larger) x the taps per thread, plus
-// the block's LDS staging per thread.
+// One image: the small tiles of psf_single_kernel, as long as the image leaves the
+// chip mostly idle with them; a larger image takes the tile of the batches.
 TileShape TileCache::latency_best(const lensed_system& s) {
-  const int sq = square_psf_code(s.psf_h, s.psf_w);
-  TileShape best{32, 32};
-  double bc = 1e300;
-  each_candidate(sq, &s, 1, [&](TileShape t) {
-    if (t.TW != 32 && t.TW != 64) return;
-    const int R = psf_rows(sq, t.TW, t.TH);
-    const int threads = t.TW * t.TH / R;
-    const double waves = (double)((threads + 63) / 64);
-    const double ntiles = (double)((s.width + t.TW - 1) / t.TW) * (double)((s.height + t.TH - 1) / t.TH);
-    const double per_simd = std::max(std::ceil(waves / 4.0), std::ceil(ntiles * waves / 1024.0));
-    const double tap = psf_specialised(sq, t.TW) ? 1.0 : 2.0;
-    const double cst = per_simd * tap * R * s.psf_h * s.psf_w +
-                       6.0 * (double)(t.TW + s.psf_w - 1) * (double)(t.TH + s.psf_h - 1) / threads;
-    if (cst < bc) {
-      bc = cst;
-      best = t;
-    }
-  });
-  return best;
+  const int64_t npix = (int64_t)s.height * s.width;
+  if (npix > SINGLE_MAX_PIXELS) return model_best(s);
+  return npix > 128 * 128 ? TileShape{32, 16} : TileShape{16, 8};
 }
 
 std::string TileCache::key(const lensed_system* s, int n) {
@@ -128,21 +96,15 @@ std::string TileCache::render_key(const lensed_system* s, int n) {
   return k;
 }
 
-int TileCache::launch_square(const lensed_system* s, int n) {
-  int sq = square_psf_code(s[0].psf_h, s[0].psf_w);
-  for (int i = 1; i < n; ++i)
-    if (square_psf_code(s[i].psf_h, s[i].psf_w) != sq) sq = -1;
-  return sq;
-}
-
 std::vector<TileShape> TileCache::ranked(const lensed_system* s, int n, int k) const {
-  const int sq = launch_square(s, n);
+  int mph = 1;
+  for (int i = 0; i < n; ++i) mph = std::max(mph, s[i].psf_h);
   std::vector<std::pair<double, TileShape>> all;
-  for (const TileShape& t : candidates(sq, s, n)) {
+  each_candidate(s, n, [&](TileShape t) {
     double cst = 0.0;
-    for (int i = 0; i < n; ++i) cst += model_cost(s[i].height, s[i].width, s[i].psf_h, s[i].psf_w, t, sq);
+    for (int i = 0; i < n; ++i) cst += model_cost(s[i].height, s[i].width, s[i].psf_h, s[i].psf_w, t, mph);
     all.push_back({cst, t});
-  }
+  });
   std::stable_sort(all.begin(), all.end(), [](const auto& a, const auto& b) { return a.first < b.first; });
   std::vector<TileShape> out;
   for (int i = 0; i < (int)all.size() && i < k; ++i) out.push_back(all[i].second);
@@ -165,7 +127,7 @@ TileShape TileCache::choose_common(const lensed_system* s, int n) {
   auto m = measured_.find(key(s, n));
   if (m != measured_.end()) return m->second;
   const std::vector<TileShape> r = ranked(s, n, 1);
-  return r.empty() ? TileShape{32, 32} : r[0];
+  return r.empty() ? TileShape{16, 16} : r[0];
 }
 
 namespace {
@@ -557,7 +519,8 @@ hipError_t BatchPlan::enqueue(hipStream_t st, hipEvent_t* ev) const {
   wp.items = d_pitems_;
   wp.n_items = n_pitems_;
   const int mode = grad_ ? 2 : 1;
-  if ((e = launch_psf(wp, d_L_, d_R_, d_part_, mode, n_pitems_, square_psf_, TW_, TH_, max_ph_, max_pw_, st)) !=
+  if ((e = launch_psf(wp, d_L_, d_R_, d_part_, mode, n_pitems_, TW_, TH_, max_ph_, max_pw_,
+                      psf_group(square_psf_), st)) !=
       hipSuccess)
     return e;
   if (ev && (e = hipEventRecord(ev[4], st)) != hipSuccess) return e;
@@ -575,8 +538,8 @@ hipError_t BatchPlan::enqueue(hipStream_t st, hipEvent_t* ev) const {
       return e;
     // g = A^T rho overwrites the unconvolved images, which are no longer needed
     const lensed_system& s0 = systems_[0];
-    if ((e = launch_adjoint_psf(wa, d_R_, d_L_, n_pitems_, square_psf_, TW_, TH_, max_ph_, max_pw_, n_points_,
-                                s0.height, s0.width, st)) != hipSuccess)
+    if ((e = launch_adjoint_psf(wa, d_R_, d_L_, n_pitems_, TW_, TH_, max_ph_, max_pw_, n_points_, s0.height,
+                                s0.width, st)) != hipSuccess)
       return e;
     if (ev && (e = hipEventRecord(ev[6], st)) != hipSuccess) return e;
     if (has_model_) {
