@@ -97,36 +97,29 @@ int ensure_mlp(lensed_ctx* c, int rows) {
     c->mlp_mem = nullptr;
     c->mlp = MlpScratch();
   }
-  const size_t R = (size_t)std::max(rows, 256);
+  const size_t R = (size_t)mlp_padded_rows(std::max(rows, 256));
   size_t off = 0;
   auto take = [&](size_t bytes) { const size_t o = off; off = align_up(off + bytes, 256); return o; };
   const size_t o_wb = take(sizeof(uint16_t) * MLP_WB_SIZE);
-  const size_t o_x0 = take(sizeof(uint16_t) * R * MLP_KPAD);
-  size_t o_z[3], o_h[3];
-  for (int l = 0; l < 3; ++l) {
-    o_z[l] = take(sizeof(float) * R * MLP_H);
-    o_h[l] = take(sizeof(uint16_t) * R * MLP_H);
-  }
+  const size_t RT = (size_t)mlp_transposed_stride((int)R);
+  const size_t o_x0 = take(sizeof(uint16_t) * RT * MLP_KPAD);
+  size_t o_h[2], o_dz[3];
+  for (size_t& o : o_h) o = take(sizeof(uint16_t) * RT * MLP_H);
+  for (size_t& o : o_dz) o = take(sizeof(uint16_t) * RT * MLP_H);
   const size_t o_d = take(sizeof(float) * R), o_sq = take(sizeof(float) * R);
-  const size_t o_dz = take(sizeof(float) * R * MLP_H), o_dz2 = take(sizeof(float) * R * MLP_H);
-  const size_t o_dzb = take(sizeof(uint16_t) * R * MLP_H), o_dzb2 = take(sizeof(uint16_t) * R * MLP_H);
-  const size_t o_g = take(sizeof(float) * MLP_NPARAM);
+  const size_t o_cols = take(sizeof(float) * (R / 16) * MLP_COLS);
+  const size_t o_dw = take(sizeof(float) * MLP_MAX_SPLITS * (size_t)MLP_NPARAM);
   LENSED_HIP(c, hipMalloc((void**)&c->mlp_mem, off));
   char* b = c->mlp_mem;
   c->mlp.cap = (int)R;
   c->mlp.wb = (uint16_t*)(b + o_wb);
-  c->mlp.X0 = (uint16_t*)(b + o_x0);
-  for (int l = 0; l < 3; ++l) {
-    c->mlp.Z[l] = (float*)(b + o_z[l]);
-    c->mlp.H[l] = (uint16_t*)(b + o_h[l]);
-  }
+  c->mlp.X0T = (uint16_t*)(b + o_x0);
+  for (int l = 0; l < 2; ++l) c->mlp.HT[l] = (uint16_t*)(b + o_h[l]);
+  for (int l = 0; l < 3; ++l) c->mlp.dZT[l] = (uint16_t*)(b + o_dz[l]);
   c->mlp.d = (float*)(b + o_d);
   c->mlp.sq = (float*)(b + o_sq);
-  c->mlp.dZ = (float*)(b + o_dz);
-  c->mlp.dZ2 = (float*)(b + o_dz2);
-  c->mlp.dZb = (uint16_t*)(b + o_dzb);
-  c->mlp.dZb2 = (uint16_t*)(b + o_dzb2);
-  c->mlp.grad = (float*)(b + o_g);
+  c->mlp.cols = (float*)(b + o_cols);
+  c->mlp.dw = (float*)(b + o_dw);
   return LENSED_OK;
 }
 
@@ -930,7 +923,8 @@ int lensed_mlp_adam(lensed_ctx* c, float* params, const float* grad, float* m, f
       !(eps > 0.0))
     return set_err(c, LENSED_INVALID_ARGUMENT, "step >= 1, finite lr, betas in [0,1) and eps > 0 are required");
   LENSED_HIP(c, hipSetDevice(c->device));
-  LENSED_HIP(c, mlp_adam(params, grad, m, v, MLP_NPARAM, step, lr, beta1, beta2, eps, (hipStream_t)stream));
+  LENSED_HIP(c, mlp_adam(params, grad, m, v, MLP_NPARAM, adam_factors(step, lr, beta1, beta2, eps),
+                         (hipStream_t)stream));
   return LENSED_OK;
 }
 
@@ -945,9 +939,8 @@ int lensed_mlp_train_step(lensed_ctx* c, float* params, float* m, float* v, int 
   if (step < 1 || !std::isfinite(lr)) return set_err(c, LENSED_INVALID_ARGUMENT, "step >= 1 and finite lr required");
   LENSED_HIP(c, hipSetDevice(c->device));
   if ((rc = ensure_mlp(c, batch))) return rc;
-  hipStream_t st = (hipStream_t)stream;
-  LENSED_HIP(c, mlp_grad(params, norm, x, y, batch, c->mlp.grad, loss, c->mlp, st));
-  LENSED_HIP(c, mlp_adam(params, c->mlp.grad, m, v, MLP_NPARAM, step, lr, 0.9, 0.999, 1e-8, st));
+  LENSED_HIP(c, mlp_train(params, m, v, adam_factors(step, lr, 0.9, 0.999, 1e-8), norm, x, y, batch, loss, c->mlp,
+                          (hipStream_t)stream));
   return LENSED_OK;
 }
 

@@ -1,14 +1,28 @@
 // mlp.hip -- the surrogate network of log L: 17 -> 256 -> 256 -> 256 -> 1, SiLU.
 //
 // Matrix products run on the matrix cores with bfloat16 operands and float32
-// accumulation (v_mfma_f32_16x16x32_bf16): a 64x64 block tile, four waves of
-// 2x2 MFMA tiles, operands staged in LDS with k contiguous so that each lane's
-// eight k values are one 16-byte LDS read. Epilogues fuse the bias and SiLU
-// (forward), the SiLU derivative (backward dZ) or plain stores (weight
-// gradients). The 256 -> 1 head, column sums, loss and Adam run on the VALU.
-// Operands are rounded to bfloat16 (nearest even) at fixed points: normalised
-// input, weights, activations H and back-propagated dZ; everything else is
-// float32.
+// accumulation (v_mfma_f32_16x16x32_bf16). Operands are rounded to bfloat16
+// (nearest even) at fixed points: normalised input, weights, activations H and
+// back-propagated dZ; everything else is float32.
+//
+// The work is small (0.8 MFLOP a row and direction) and was bound by launches,
+// by reads and writes of every layer's Z and H, and, in the weight gradients, by
+// 16 blocks that each walked all rows with strided two-byte loads. So:
+//   mlp_rows_kernel   a block takes 16, 32 or 64 rows through all layers, and in
+//                     training back again. Activations and dZ pass between the
+//                     layers in LDS, Z stays in registers, the weights come from
+//                     L2 in the lanes' operand layout, one layer ahead. For the
+//                     weight gradients it also writes H and dZ transposed (rows
+//                     contiguous) and its own column sums (bias gradients, dW4).
+//   mlp_dw_kernel     dW_l = dZ_l^T H_{l-1}: a wave takes a 64 x 64 (64 x 32 for
+//                     W1) piece over a part of the rows, both operands straight
+//                     from the transposed copies.
+//   mlp_sum_kernel    adds the parts in a fixed order and writes the gradient, or
+//                     applies Adam to it.
+// One Adam step at 4096 rows: 1959 us with one kernel per layer and reduction, 49 us
+// so (rows 27, weight gradients 13, sums 6, weight conversion 5 us, of which a
+// launch is about 4 each); predictions for 16384 rows 154 -> 29 us. What is left
+// is latency: 12.6 million SiLUs are 6 us of vector work, the products 4 us.
 //
 // Flat parameter layout (float32): W1 [256][17], b1 [256], W2 [256][256], b2,
 // W3 [256][256], b3, W4 [1][256], b4 [1]. Normalisation block: x_shift [17],
@@ -16,6 +30,7 @@
 #include <stdint.h>
 
 #include <cmath>
+#include <type_traits>
 
 #include "internal.h"
 #include "kernels.h"
@@ -26,240 +41,475 @@ namespace {
 
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef uint16_t u16x8 __attribute__((ext_vector_type(8)));
+typedef uint16_t u16x4 __attribute__((ext_vector_type(4)));
 typedef float f32x4 __attribute__((ext_vector_type(4)));
 
-__device__ __forceinline__ uint16_t f2bf(float f) {
-  uint32_t u = __builtin_bit_cast(uint32_t, f);
-  if ((u & 0x7fffffffu) > 0x7f800000u) return 0x7fc0;   // NaN
-  u += 0x7fffu + ((u >> 16) & 1u);
-  return (uint16_t)(u >> 16);
-}
+// Nearest even (v_cvt_pk_bf16_f32).
+__device__ __forceinline__ uint16_t f2bf(float f) { return __builtin_bit_cast(uint16_t, (__bf16)f); }
 __device__ __forceinline__ float bf2f(uint16_t h) { return __builtin_bit_cast(float, (uint32_t)h << 16); }
 
-__device__ __forceinline__ float silu(float z) { return z / (1.0f + __expf(-z)); }
+// n / d for d in [1, 1e30]: the steps of a correctly rounded division that need no
+// scaling there (the compiler's general division takes half again as many
+// instructions, and these divisions are most of the vector work here).
+__device__ __forceinline__ float div_unscaled(float n, float d) {
+  float r = __builtin_amdgcn_rcpf(d);
+  r = fmaf(fmaf(-d, r, 1.0f), r, r);
+  float q = n * r;
+  q = fmaf(fmaf(-d, q, n), r, q);
+  return fmaf(fmaf(-d, q, n), r, q);
+}
+// 1 + exp(-z), kept finite (past z = -69 it only makes a quotient below 1e-28).
+__device__ __forceinline__ float one_plus_exp(float z) { return 1.0f + fminf(__expf(-z), 1e30f); }
+__device__ __forceinline__ float silu(float z) { return div_unscaled(z, one_plus_exp(z)); }
 __device__ __forceinline__ float dsilu(float z) {
-  const float s = 1.0f / (1.0f + __expf(-z));
+  const float s = div_unscaled(1.0f, one_plus_exp(z));
   return s * (1.0f + z * (1.0f - s));
 }
 
-constexpr int BM = 64, BN = 64, BK = 32, LDSK = BK + 8;
+__device__ __forceinline__ bf16x8 frag(const uint16_t* p) { return __builtin_bit_cast(bf16x8, *(const u16x8*)p); }
+__device__ __forceinline__ f32x4 mfma(bf16x8 a, bf16x8 b, f32x4 c) {
+  return __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, b, c, 0, 0, 0);
+}
 
-struct GemmArgs {
-  const uint16_t* A;
-  long sam, sak;        // A(m, k) = A[m * sam + k * sak]
-  const uint16_t* B;
-  long sbk, sbn;        // B(k, n) = B[k * sbk + n * sbn]
-  int M, N, K;
-  int epi;              // 0: Z = acc + bias, H = bf16(silu(Z)); 1: dZ = acc * silu'(Zin); 2: C = acc
-  const float* bias;
-  const float* Zin;
-  long ldz;
-  float* Cf;            // float32 output (Z, dZ or C)
-  uint16_t* Cb;         // bfloat16 output (H or dZ), may be null
-  long ldc;
+// bfloat16 copies of the weights: W1 padded to [256][32], W2, W3 [256][256], W4
+// [256], and, with `transposes`, W2 and W3 transposed. A block takes a 64 x 64
+// piece of W2 or W3 (blocks 0..31) or a share of the rest.
+constexpr int CONVERT_BLOCKS = 34;
+__global__ __launch_bounds__(256) void convert_weights_kernel(const float* __restrict__ p, uint16_t* __restrict__ wb,
+                                                              int transposes) {
+  const int t = (int)threadIdx.x, b = (int)blockIdx.x;
+  if (b >= 32) {
+    for (int i = (b - 32) * 256 + t; i < MLP_H * MLP_KPAD; i += 512) {
+      const int o = i / MLP_KPAD, k = i - o * MLP_KPAD;
+      wb[i] = k < MLP_IN ? f2bf(p[MLP_OFF_W1 + o * MLP_IN + k]) : (uint16_t)0;
+    }
+    if (b == 32) wb[MLP_WB_W4 + t] = f2bf(p[MLP_OFF_W4 + t]);
+    return;
+  }
+  __shared__ uint16_t tile[64][66];
+  const int r0 = (b & 15) / 4 * 64, c0 = (b & 3) * 64;
+  const float* __restrict__ W = p + (b < 16 ? MLP_OFF_W2 : MLP_OFF_W3);
+  uint16_t* __restrict__ o = wb + (b < 16 ? MLP_WB_W2 : MLP_WB_W3);
+  uint16_t* __restrict__ oT = wb + (b < 16 ? MLP_WB_W2T : MLP_WB_W3T);
+  const int c = t & 63;
+#pragma unroll
+  for (int k = 0; k < 16; ++k) {
+    const int r = (t >> 6) + 4 * k;
+    const uint16_t h = f2bf(W[(r0 + r) * MLP_H + c0 + c]);
+    o[(r0 + r) * MLP_H + c0 + c] = h;
+    tile[r][c] = h;
+  }
+  if (!transposes) return;   // uniform
+  __syncthreads();
+#pragma unroll
+  for (int k = 0; k < 16; ++k) {
+    const int r = (t >> 6) + 4 * k;
+    oT[(c0 + r) * MLP_H + r0 + c] = tile[c][r];
+  }
+}
+
+struct RowArgs {
+  const float* p;       // parameters
+  const float* norm;
+  const float* x;
+  const float* yt;      // targets (training)
+  const uint16_t* wb;
+  float* y;             // predictions (forward)
+  int B;
+  long ld;              // distance of two rows of the transposed buffers
+  uint16_t *X0T, *HT0, *HT1, *dZT0, *dZT1, *dZT2;
+  float *d, *sq, *cols;
 };
 
-// Lane l of a 16x16x32 MFMA holds A[m = l % 16][k = 8 (l / 16) + j] and
-// B[k = 8 (l / 16) + j][n = l % 16], j = 0..7, and receives
-// D[m = 4 (l / 16) + j][n = l % 16], j = 0..3.
-__global__ __launch_bounds__(256) void gemm_bf16_kernel(GemmArgs g) {
-  __shared__ uint16_t As[BM][LDSK];
-  __shared__ uint16_t Bt[BN][LDSK];   // B transposed: [n][k]
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const int bm = blockIdx.y * BM, bn = blockIdx.x * BN;
-  const int wm = (wave >> 1) * 32, wn = (wave & 1) * 32;
-  f32x4 acc[2][2];
+// MT x 16 rows per block, NW waves of 16 NT columns each. Lane l of a 16x16x32 MFMA
+// holds A[m = l % 16][k = 8 (l / 16) + j] and B[k = 8 (l / 16) + j][n = l % 16],
+// j = 0..7, and receives D[m = 4 (l / 16) + j][n = l % 16], j = 0..3. In training A is
+// the activations (a lane receives four rows of a column, for the transposed
+// copies and the column sums); otherwise A is the weights (four columns of a row,
+// one 8-byte write to LDS). The sums over k are the same. Rows past B compute with
+// x = 0; their H and dZ are written as zeros.
+constexpr int LDH = MLP_H + 8;   // 16 rows fall into different banks
+template <int MT, int NW, bool TRAIN>
+__global__ __launch_bounds__(64 * NW, 1) void mlp_rows_kernel(RowArgs a) {
+  constexpr int NT = 16 / NW;
+  __shared__ __align__(16) uint16_t buf[2][16 * MT][LDH];
+  __shared__ float dl[16 * MT];
+  const int lane = (int)threadIdx.x & 63, wave = (int)threadIdx.x >> 6;
+  const int c = lane & 15, g = lane >> 4, wn = wave * 16 * NT;
+  const int row0 = (int)blockIdx.x * 16 * MT;
+  const float* __restrict__ p = a.p;
+
+  bf16x8 wf[8][NT];   // the lane's pieces of one 256 x 256 layer
+  auto load_w = [&](long off) {
+    const uint16_t* __restrict__ w = a.wb + off + (long)(wn + c) * MLP_H + 8 * g;
 #pragma unroll
-  for (int i = 0; i < 2; ++i)
+    for (int ks = 0; ks < 8; ++ks)
 #pragma unroll
-    for (int j = 0; j < 2; ++j) acc[i][j] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
-  const int lr = tid >> 2, lk = (tid & 3) * 8;   // staging: one row (or column), eight k values
-  for (int k0 = 0; k0 < g.K; k0 += BK) {
-    {
-      const int m = bm + lr;
+      for (int t = 0; t < NT; ++t) wf[ks][t] = frag(w + (long)16 * t * MLP_H + 32 * ks);
+  };
+  auto mul = [&](bf16x8 h, bf16x8 w, f32x4 acc) { return TRAIN ? mfma(h, w, acc) : mfma(w, h, acc); };
+  auto gemm = [&](const uint16_t (*h)[LDH], f32x4 (&acc)[MT][NT]) {
 #pragma unroll
-      for (int j = 0; j < 8; ++j) {
-        const int k = k0 + lk + j;
-        As[lr][lk + j] = (m < g.M && k < g.K) ? g.A[(long)m * g.sam + (long)k * g.sak] : (uint16_t)0;
+    for (int mt = 0; mt < MT; ++mt)
+#pragma unroll
+      for (int t = 0; t < NT; ++t) acc[mt][t] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
+#pragma unroll
+    for (int ks = 0; ks < 8; ++ks)
+#pragma unroll
+      for (int mt = 0; mt < MT; ++mt) {
+        const bf16x8 hv = frag(&h[16 * mt + c][32 * ks + 8 * g]);
+#pragma unroll
+        for (int t = 0; t < NT; ++t) acc[mt][t] = mul(hv, wf[ks][t], acc[mt][t]);
       }
-      const int n = bn + lr;
+  };
+  // H = bf16(silu(z)) into LDS, and (training) transposed into HT, zero past B
+  auto activate = [&](f32x4 (&z)[MT][NT], int off_b, uint16_t (*h)[LDH], uint16_t* HT) {
 #pragma unroll
-      for (int j = 0; j < 8; ++j) {
-        const int k = k0 + lk + j;
-        Bt[lr][lk + j] = (n < g.N && k < g.K) ? g.B[(long)k * g.sbk + (long)n * g.sbn] : (uint16_t)0;
-      }
-    }
-    __syncthreads();
-    const int fr = lane & 15, fk = (lane >> 4) * 8;
-    bf16x8 a[2], b[2];
+    for (int t = 0; t < NT; ++t) {
+      float b[4];
 #pragma unroll
-    for (int i = 0; i < 2; ++i) {
-      const u16x8 va = *(const u16x8*)&As[wm + i * 16 + fr][fk];
-      const u16x8 vb = *(const u16x8*)&Bt[wn + i * 16 + fr][fk];
-      a[i] = __builtin_bit_cast(bf16x8, va);
-      b[i] = __builtin_bit_cast(bf16x8, vb);
-    }
+      for (int j = 0; j < 4; ++j) b[j] = p[off_b + wn + 16 * t + (TRAIN ? c : 4 * g + j)];
 #pragma unroll
-    for (int i = 0; i < 2; ++i)
+      for (int mt = 0; mt < MT; ++mt) {
+        u16x4 hv;
 #pragma unroll
-      for (int j = 0; j < 2; ++j) acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[i], b[j], acc[i][j], 0, 0, 0);
-    __syncthreads();
-  }
-  const int cn = lane & 15, cm = (lane >> 4) * 4;
+        for (int j = 0; j < 4; ++j) {
+          z[mt][t][j] += b[j];
+          hv[j] = f2bf(silu(z[mt][t][j]));
+        }
+        if (!TRAIN) {
+          *(u16x4*)&h[16 * mt + c][wn + 16 * t + 4 * g] = hv;
+          continue;
+        }
+        const int n = wn + 16 * t + c, r = 16 * mt + 4 * g;
 #pragma unroll
-  for (int i = 0; i < 2; ++i)
+        for (int j = 0; j < 4; ++j) h[r + j][n] = hv[j];
+        if (HT) {
 #pragma unroll
-    for (int j = 0; j < 2; ++j)
-#pragma unroll
-      for (int r = 0; r < 4; ++r) {
-        const int m = bm + wm + i * 16 + cm + r;
-        const int n = bn + wn + j * 16 + cn;
-        if (m >= g.M || n >= g.N) continue;
-        const float v = acc[i][j][r];
-        const long o = (long)m * g.ldc + n;
-        if (g.epi == 0) {
-          const float z = v + g.bias[n];
-          g.Cf[o] = z;
-          g.Cb[o] = f2bf(silu(z));
-        } else if (g.epi == 1) {
-          const float dz = v * dsilu(g.Zin[(long)m * g.ldz + n]);
-          g.Cf[o] = dz;
-          g.Cb[o] = f2bf(dz);
-        } else {
-          g.Cf[o] = v;
+          for (int j = 0; j < 4; ++j)
+            if (row0 + r + j >= a.B) hv[j] = 0;
+          *(u16x4*)(HT + n * a.ld + row0 + r) = hv;
         }
       }
-}
+    }
+  };
 
-// bfloat16 copies of the weights: W1 padded to [256][32], W2, W3 [256][256], W4 [256].
-__global__ void convert_weights_kernel(const float* __restrict__ p, uint16_t* __restrict__ wb) {
-  const int i = blockIdx.x * blockDim.x + threadIdx.x;
-  if (i < MLP_H * MLP_KPAD) {
-    const int o = i / MLP_KPAD, k = i - o * MLP_KPAD;
-    wb[i] = k < MLP_IN ? f2bf(p[MLP_OFF_W1 + o * MLP_IN + k]) : (uint16_t)0;
-  }
-  if (i < MLP_H * MLP_H) {
-    wb[MLP_WB_W2 + i] = f2bf(p[MLP_OFF_W2 + i]);
-    wb[MLP_WB_W3 + i] = f2bf(p[MLP_OFF_W3 + i]);
-  }
-  if (i < MLP_H) wb[MLP_WB_W4 + i] = f2bf(p[MLP_OFF_W4 + i]);
-}
-
-// X0[m][k] = bf16((x[m][k] - x_shift[k]) * x_scale[k]) for k < 17, zero up to 32.
-__global__ void input_kernel(const float* __restrict__ x, const float* __restrict__ norm, uint16_t* __restrict__ X0,
-                             int B) {
-  const int i = blockIdx.x * blockDim.x + threadIdx.x;
-  if (i >= B * MLP_KPAD) return;
-  const int m = i / MLP_KPAD, k = i - m * MLP_KPAD;
-  X0[i] = k < MLP_IN ? f2bf((x[(long)m * MLP_IN + k] - norm[k]) * norm[MLP_IN + k]) : (uint16_t)0;
-}
-
-// Head: out = H3 . W4 + b4, one wave per row. mode 0: y = y_shift + y_scale out.
-// mode 1 (training): t = (y - y_shift)/y_scale, d = 2 (out - t)/B, sq = (out - t)^2.
-__global__ __launch_bounds__(256) void head_kernel(const uint16_t* __restrict__ H3, const uint16_t* __restrict__ wb,
-                                                   const float* __restrict__ p, const float* __restrict__ norm,
-                                                   int B, int mode, float* __restrict__ y, const float* __restrict__ yt,
-                                                   float* __restrict__ d, float* __restrict__ sq) {
-  const int lane = threadIdx.x & 63;
-  const int m = blockIdx.x * 4 + (threadIdx.x >> 6);
-  if (m >= B) return;
-  float s = 0.0f;
+  load_w(MLP_WB_W2);
+  f32x4 z1[MT][NT], z2[MT][NT], z3[MT][NT];
+  {   // layer 1: x normalised and rounded in the operand layout
+    bf16x8 w1[NT];
 #pragma unroll
-  for (int j = 0; j < MLP_H / 64; ++j) {
-    const int n = lane + 64 * j;
-    s = fmaf(bf2f(H3[(long)m * MLP_H + n]), bf2f(wb[MLP_WB_W4 + n]), s);
-  }
-  for (int off = 32; off > 0; off >>= 1) s += __shfl_down(s, off, 64);
-  if (lane == 0) {
-    const float out = s + p[MLP_OFF_B4];
-    if (mode == 0) {
-      y[m] = norm[2 * MLP_IN] + norm[2 * MLP_IN + 1] * out;
-    } else {
-      const float t = (yt[m] - norm[2 * MLP_IN]) / norm[2 * MLP_IN + 1];
-      const float r = out - t;
-      d[m] = 2.0f * r / (float)B;
-      sq[m] = r * r;
+    for (int t = 0; t < NT; ++t) w1[t] = frag(a.wb + (wn + 16 * t + c) * MLP_KPAD + 8 * g);
+#pragma unroll
+    for (int mt = 0; mt < MT; ++mt) {
+      const int row = row0 + 16 * mt + c;
+      u16x8 xv;
+#pragma unroll
+      for (int j = 0; j < 8; ++j) {
+        const int k = 8 * g + j;
+        xv[j] = k < MLP_IN && row < a.B ? f2bf((a.x[(long)row * MLP_IN + k] - a.norm[k]) * a.norm[MLP_IN + k])
+                                        : (uint16_t)0;
+        if (TRAIN && wave == 0) a.X0T[k * a.ld + row] = xv[j];
+      }
+      const bf16x8 hv = __builtin_bit_cast(bf16x8, xv);
+#pragma unroll
+      for (int t = 0; t < NT; ++t) z1[mt][t] = mul(hv, w1[t], f32x4{0.0f, 0.0f, 0.0f, 0.0f});
     }
   }
-}
-
-// dZ3[m][n] = d[m] W4[n] silu'(Z3[m][n]), float32 and bfloat16.
-__global__ void head_bwd_kernel(const float* __restrict__ d, const uint16_t* __restrict__ wb,
-                                const float* __restrict__ Z3, float* __restrict__ dZ, uint16_t* __restrict__ dZb,
-                                int B) {
-  const int i = blockIdx.x * blockDim.x + threadIdx.x;
-  if (i >= B * MLP_H) return;
-  const int m = i / MLP_H, n = i - m * MLP_H;
-  const float v = d[m] * bf2f(wb[MLP_WB_W4 + n]) * dsilu(Z3[i]);
-  dZ[i] = v;
-  dZb[i] = f2bf(v);
-}
-
-// out[n] = sum_m w[m] * X[m][n] over M rows (w = 1 when null; X float32 or
-// bfloat16). One block per column, fixed-order tree: deterministic.
-__global__ __launch_bounds__(256) void colsum_kernel(const float* __restrict__ Xf, const uint16_t* __restrict__ Xb,
-                                                     const float* __restrict__ w, int M, long ld,
-                                                     float* __restrict__ out) {
-  __shared__ float red[256];
-  const int n = blockIdx.x;
-  float s = 0.0f;
-  for (int m = threadIdx.x; m < M; m += 256) {
-    const float x = Xf ? Xf[(long)m * ld + n] : bf2f(Xb[(long)m * ld + n]);
-    s += w ? w[m] * x : x;
-  }
-  red[threadIdx.x] = s;
+  activate(z1, MLP_OFF_B1, buf[0], a.HT0);
   __syncthreads();
-  for (int k = 128; k > 0; k >>= 1) {
-    if ((int)threadIdx.x < k) red[threadIdx.x] += red[threadIdx.x + k];
-    __syncthreads();
+  gemm(buf[0], z2);
+  load_w(MLP_WB_W3);
+  activate(z2, MLP_OFF_B2, buf[1], a.HT1);
+  __syncthreads();
+  gemm(buf[1], z3);
+  if (TRAIN) load_w(MLP_WB_W3T);
+  activate(z3, MLP_OFF_B3, buf[0], nullptr);
+  __syncthreads();
+
+  // head: out = H3 . W4 + b4, one row per wave at a time
+  float w4[4];
+#pragma unroll
+  for (int j = 0; j < 4; ++j) w4[j] = bf2f(a.wb[MLP_WB_W4 + lane + 64 * j]);
+  for (int r = wave; r < 16 * MT; r += NW) {
+    float s = 0.0f;
+#pragma unroll
+    for (int j = 0; j < 4; ++j) s = fmaf(bf2f(buf[0][r][lane + 64 * j]), w4[j], s);
+    for (int off = 32; off > 0; off >>= 1) s += __shfl_down(s, off, 64);
+    const int row = row0 + r;
+    if (lane == 0) {
+      const float out = s + p[MLP_OFF_B4];
+      if (!TRAIN) {
+        if (row < a.B) a.y[row] = a.norm[2 * MLP_IN] + a.norm[2 * MLP_IN + 1] * out;
+      } else {
+        float dv = 0.0f;
+        if (row < a.B) {
+          const float t = (a.yt[row] - a.norm[2 * MLP_IN]) / a.norm[2 * MLP_IN + 1];
+          const float e = out - t;
+          dv = 2.0f * e / (float)a.B;
+          a.d[row] = dv;
+          a.sq[row] = e * e;
+        }
+        dl[r] = dv;
+      }
+    }
   }
-  if (threadIdx.x == 0) out[n] = red[0];
+  if (!TRAIN) return;
+  __syncthreads();
+
+  float* __restrict__ cols = a.cols + (long)blockIdx.x * MLP_COLS;
+  // the sum of v over the block's rows of column n, from the 16 lanes' four rows each
+  auto column_sum = [&](float v, int slot) {
+    v += __shfl_xor(v, 16, 64);
+    v += __shfl_xor(v, 32, 64);
+    if (g == 0) cols[slot] = v;
+  };
+  // dZ in bfloat16 into LDS and transposed into dZT; its column sums in float32
+  auto propagate = [&](const f32x4 (&dz)[MT][NT], uint16_t (*h)[LDH], uint16_t* dZT, int slot) {
+#pragma unroll
+    for (int t = 0; t < NT; ++t) {
+      const int n = wn + 16 * t + c;
+      float s = 0.0f;
+#pragma unroll
+      for (int mt = 0; mt < MT; ++mt) {
+        u16x4 hv;
+        const int r = 16 * mt + 4 * g;
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+          const float v = row0 + r + j < a.B ? dz[mt][t][j] : 0.0f;
+          s += v;
+          hv[j] = f2bf(v);
+          if (h) h[r + j][n] = hv[j];
+        }
+        *(u16x4*)(dZT + n * a.ld + row0 + r) = hv;
+      }
+      column_sum(s, slot + n);
+    }
+  };
+
+  // layer 4: dW4[n] = sum_m d[m] H3[m][n]; dZ3 = d W4 silu'(Z3)
+#pragma unroll
+  for (int t = 0; t < NT; ++t) {
+    const int n = wn + 16 * t + c;
+    const float w = bf2f(a.wb[MLP_WB_W4 + n]);
+    float s = 0.0f;
+#pragma unroll
+    for (int mt = 0; mt < MT; ++mt)
+#pragma unroll
+      for (int j = 0; j < 4; ++j) {
+        const int r = 16 * mt + 4 * g + j;
+        if (row0 + r < a.B) s += dl[r] * bf2f(buf[0][r][n]);
+        z3[mt][t][j] = dl[r] * w * dsilu(z3[mt][t][j]);
+      }
+    column_sum(s, 3 * MLP_H + n);
+  }
+  propagate(z3, buf[1], a.dZT2, 2 * MLP_H);
+  __syncthreads();
+  gemm(buf[1], z3);   // dZ3 W3
+  load_w(MLP_WB_W2T);
+#pragma unroll
+  for (int mt = 0; mt < MT; ++mt)
+#pragma unroll
+    for (int t = 0; t < NT; ++t)
+#pragma unroll
+      for (int j = 0; j < 4; ++j) z2[mt][t][j] = z3[mt][t][j] * dsilu(z2[mt][t][j]);
+  propagate(z2, buf[0], a.dZT1, MLP_H);
+  __syncthreads();
+  gemm(buf[0], z2);   // dZ2 W2
+#pragma unroll
+  for (int mt = 0; mt < MT; ++mt)
+#pragma unroll
+    for (int t = 0; t < NT; ++t)
+#pragma unroll
+      for (int j = 0; j < 4; ++j) z1[mt][t][j] = z2[mt][t][j] * dsilu(z1[mt][t][j]);
+  propagate(z1, nullptr, a.dZT0, 0);
 }
 
-__global__ __launch_bounds__(256) void mean_kernel(const float* __restrict__ x, int n, float* __restrict__ out) {
-  __shared__ float red[256];
-  float s = 0.0f;
-  for (int i = threadIdx.x; i < n; i += 256) s += x[i];
-  red[threadIdx.x] = s;
-  __syncthreads();
-  for (int k = 128; k > 0; k >>= 1) {
-    if ((int)threadIdx.x < k) red[threadIdx.x] += red[threadIdx.x + k];
-    __syncthreads();
+// dW_l[o][i] = sum_b dZ_l[b][o] H_{l-1}[b][i] over one part of the rows. Wave item
+// (part, piece): pieces 0..15 of W3, 16..31 of W2 (64 x 64 each), 32..35 of W1
+// (64 x 32, columns past 17 dropped). Both operands are rows of the transposed
+// copies, 16 bytes per lane.
+constexpr int DW_PIECES = 36;
+template <int NT>
+__device__ __forceinline__ void dw_piece(const uint16_t* __restrict__ A, const uint16_t* __restrict__ Bm, long ld,
+                                         int k0, int k1, float* __restrict__ out, int ldo, int n_cols) {
+  const int lane = (int)threadIdx.x & 63, c = lane & 15, g = lane >> 4;
+  f32x4 acc[4][NT];
+#pragma unroll
+  for (int i = 0; i < 4; ++i)
+#pragma unroll
+    for (int j = 0; j < NT; ++j) acc[i][j] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
+  const uint16_t* __restrict__ pa = A + (long)c * ld + 8 * g;
+  const uint16_t* __restrict__ pb = Bm + (long)c * ld + 8 * g;
+  // U steps of 32 rows: all their loads first
+  auto steps = [&](int k, auto uc) {
+    constexpr int U = decltype(uc)::value;
+    bf16x8 av[U][4], bv[U][NT];
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+#pragma unroll
+      for (int i = 0; i < 4; ++i) av[u][i] = frag(pa + 16 * i * ld + k + 32 * u);
+#pragma unroll
+      for (int j = 0; j < NT; ++j) bv[u][j] = frag(pb + 16 * j * ld + k + 32 * u);
+    }
+#pragma unroll
+    for (int u = 0; u < U; ++u)
+#pragma unroll
+      for (int i = 0; i < 4; ++i)
+#pragma unroll
+        for (int j = 0; j < NT; ++j) acc[i][j] = mfma(av[u][i], bv[u][j], acc[i][j]);
+  };
+  int k = k0;
+  for (; k + 128 <= k1; k += 128) steps(k, std::integral_constant<int, 4>{});
+  for (; k < k1; k += 32) steps(k, std::integral_constant<int, 1>{});
+#pragma unroll
+  for (int i = 0; i < 4; ++i)
+#pragma unroll
+    for (int j = 0; j < NT; ++j)
+#pragma unroll
+      for (int r = 0; r < 4; ++r)
+        if (16 * j + c < n_cols) out[(long)(16 * i + 4 * g + r) * ldo + 16 * j + c] = acc[i][j][r];
+}
+
+__global__ __launch_bounds__(64) void mlp_dw_kernel(MlpScratch s, long ld, int Bp, int rows_per_part) {
+  const int part = (int)blockIdx.x / DW_PIECES, piece = (int)blockIdx.x - part * DW_PIECES;
+  const int k0 = part * rows_per_part, k1 = min(k0 + rows_per_part, Bp);
+  float* __restrict__ out = s.dw + (long)part * MLP_NPARAM;
+  if (piece < 32) {
+    const int l = piece < 16 ? 2 : 1, o = (piece & 15) / 4 * 64, i = (piece & 3) * 64;
+    dw_piece<4>(s.dZT[l] + o * ld, s.HT[l - 1] + i * ld, ld, k0, k1,
+                out + (l == 2 ? MLP_OFF_W3 : MLP_OFF_W2) + (long)o * MLP_H + i, MLP_H, 64);
+  } else {
+    const int o = (piece - 32) * 64;
+    dw_piece<2>(s.dZT[0] + o * ld, s.X0T, ld, k0, k1, out + MLP_OFF_W1 + (long)o * MLP_IN, MLP_IN, MLP_IN);
   }
-  if (threadIdx.x == 0) out[0] = red[0] / (float)n;
 }
 
 // Adam (Kingma & Ba 2015): m = b1 m + (1 - b1) g, v = b2 v + (1 - b2) g^2,
 // p -= lr (m / bc1) / (sqrt(v / bc2) + eps), bc = 1 - b^t. The factors 1 - b
 // and the bias corrections come from the host in float64 (1 - b2 rounded from a
 // float b2 would carry a 1e-5 relative error).
-__global__ void adam_kernel(float* __restrict__ p, const float* __restrict__ g, float* __restrict__ m,
-                            float* __restrict__ v, int n, float lr, float beta1, float omb1, float beta2, float omb2,
-                            float eps, float bc1, float bc2) {
-  const int i = blockIdx.x * blockDim.x + threadIdx.x;
-  if (i >= n) return;
-  const float gi = g[i];
-  const float mi = fmaf(beta1, m[i], omb1 * gi);
-  const float vi = fmaf(beta2, v[i], omb2 * gi * gi);
+__device__ __forceinline__ void adam_update(float* __restrict__ p, float gi, float* __restrict__ m,
+                                            float* __restrict__ v, int i, const AdamStep& a) {
+  const float mi = fmaf(a.beta1, m[i], a.omb1 * gi);
+  const float vi = fmaf(a.beta2, v[i], a.omb2 * gi * gi);
   m[i] = mi;
   v[i] = vi;
-  p[i] -= lr * (mi / bc1) / (sqrtf(vi / bc2) + eps);
+  p[i] -= a.lr * (mi / a.bc1) / (sqrtf(vi / a.bc2) + a.eps);
 }
 
-hipError_t gemm(const GemmArgs& a, hipStream_t st) {
-  dim3 grid((a.N + BN - 1) / BN, (a.M + BM - 1) / BM);
-  hipLaunchKernelGGL(gemm_bf16_kernel, grid, dim3(256), 0, st, a);
+__global__ __launch_bounds__(256) void adam_kernel(float* __restrict__ p, const float* __restrict__ g,
+                                                   float* __restrict__ m, float* __restrict__ v, int n, AdamStep a) {
+  const int i = blockIdx.x * blockDim.x + threadIdx.x;
+  if (i < n) adam_update(p, g[i], m, v, i, a);
+}
+
+// The gradient from its parts, each sum in a fixed order, and (ADAM) the update.
+// Blocks 0 .. SUM_COL_BLOCKS - 1: 64 column sums each (the biases and W4), four
+// threads per column over the row blocks; the next: db4 and the loss; the rest:
+// 256 weights each over the parts. The slow sums come first.
+constexpr int SUM_COL_BLOCKS = MLP_COLS / 64;
+constexpr int SUM_W = MLP_H * MLP_IN + 2 * MLP_H * MLP_H;
+static_assert(SUM_W % 256 == 0, "whole blocks of weights");
+constexpr int SUM_BLOCKS = SUM_COL_BLOCKS + 1 + SUM_W / 256;
+template <bool ADAM>
+__global__ __launch_bounds__(256) void mlp_sum_kernel(MlpScratch s, int B, int row_blocks, int parts,
+                                                      float* __restrict__ grad, float* __restrict__ loss,
+                                                      float* __restrict__ p, float* __restrict__ m,
+                                                      float* __restrict__ v, AdamStep a) {
+  __shared__ float red[2][256];
+  const int t = (int)threadIdx.x, b = (int)blockIdx.x;
+  auto put = [&](int i, float gi) {
+    if (ADAM)
+      adam_update(p, gi, m, v, i, a);
+    else
+      grad[i] = gi;
+  };
+  if (b < SUM_COL_BLOCKS) {
+    const int slot = b * 64 + (t & 63);
+    float acc = 0.0f;
+#pragma unroll 8
+    for (int r = t >> 6; r < row_blocks; r += 4) acc += s.cols[(long)r * MLP_COLS + slot];
+    red[0][t] = acc;
+    __syncthreads();
+    if (t < 64) {
+      const float gi = (red[0][t] + red[0][t + 64]) + (red[0][t + 128] + red[0][t + 192]);
+      const int l = slot / MLP_H, n = slot - l * MLP_H;
+      put((l == 0 ? MLP_OFF_B1 : l == 1 ? MLP_OFF_B2 : l == 2 ? MLP_OFF_B3 : MLP_OFF_W4) + n, gi);
+    }
+    return;
+  }
+  if (b == SUM_COL_BLOCKS) {
+    float sd = 0.0f, sl = 0.0f;
+#pragma unroll 4
+    for (int r = t; r < B; r += 256) {
+      sd += s.d[r];
+      sl += s.sq[r];
+    }
+    red[0][t] = sd;
+    red[1][t] = sl;
+    __syncthreads();
+    for (int k = 128; k > 0; k >>= 1) {
+      if (t < k) {
+        red[0][t] += red[0][t + k];
+        red[1][t] += red[1][t + k];
+      }
+      __syncthreads();
+    }
+    if (t == 0) {
+      put(MLP_OFF_B4, red[0][0]);
+      loss[0] = red[1][0] / (float)B;
+    }
+    return;
+  }
+  const int e = (b - SUM_COL_BLOCKS - 1) * 256 + t;
+  const int i = e < MLP_H * MLP_IN ? MLP_OFF_W1 + e
+                : e < MLP_H * MLP_IN + MLP_H * MLP_H ? MLP_OFF_W2 + (e - MLP_H * MLP_IN)
+                                                     : MLP_OFF_W3 + (e - MLP_H * MLP_IN - MLP_H * MLP_H);
+  float gi = 0.0f;
+#pragma unroll 8
+  for (int k = 0; k < parts; ++k) gi += s.dw[(long)k * MLP_NPARAM + i];
+  put(i, gi);
+}
+
+hipError_t convert_weights(const float* params, const MlpScratch& s, bool transposes, hipStream_t st) {
+  hipLaunchKernelGGL(convert_weights_kernel, dim3(CONVERT_BLOCKS), dim3(256), 0, st, params, s.wb, transposes ? 1 : 0);
   return hipGetLastError();
 }
 
-GemmArgs fwd_layer(const uint16_t* X, long ldx, const uint16_t* W, long ldw, int B, int K, const float* bias, float* Z,
-                   uint16_t* H) {
-  GemmArgs a{};
-  a.A = X; a.sam = ldx; a.sak = 1;                  // X [B][K]
-  a.B = W; a.sbk = 1; a.sbn = ldw;                  // B(k, n) = W[n][k]
-  a.M = B; a.N = MLP_H; a.K = K;
-  a.epi = 0; a.bias = bias; a.Cf = Z; a.Cb = H; a.ldc = MLP_H;
-  return a;
+// Rows per block: 16 while that leaves compute units idle otherwise, more for larger
+// batches, so that a block's weights serve more rows (training keeps Z of three
+// layers in registers: 32 at most). Eight waves hide the loads and the serial
+// parts of 16 rows better than four.
+template <int MT, bool TRAIN>
+hipError_t launch_rows(const RowArgs& a, int Bp, hipStream_t st) {
+  constexpr int NW = 8;
+  hipLaunchKernelGGL((mlp_rows_kernel<MT, NW, TRAIN>), dim3((unsigned)(Bp / (16 * MT))), dim3(64 * NW), 0, st, a);
+  return hipGetLastError();
+}
+
+// Everything but the last sums: the rows forward and back, and the parts of dW.
+hipError_t grad_parts(const float* params, const float* norm, const float* x, const float* yt, int B,
+                      const MlpScratch& s, int* row_blocks, int* parts, hipStream_t st) {
+  hipError_t e = convert_weights(params, s, true, st);
+  if (e != hipSuccess) return e;
+  const int Bp = mlp_padded_rows(B);
+  RowArgs a{};
+  a.p = params, a.norm = norm, a.x = x, a.yt = yt, a.wb = s.wb;
+  a.B = B, a.ld = mlp_transposed_stride(B);
+  a.X0T = s.X0T, a.HT0 = s.HT[0], a.HT1 = s.HT[1];
+  a.dZT0 = s.dZT[0], a.dZT1 = s.dZT[1], a.dZT2 = s.dZT[2];
+  a.d = s.d, a.sq = s.sq, a.cols = s.cols;
+  const bool two = Bp > 8192;
+  *row_blocks = Bp / (two ? 32 : 16);
+  if ((e = two ? launch_rows<2, true>(a, Bp, st) : launch_rows<1, true>(a, Bp, st)) != hipSuccess) return e;
+  // parts of at least 128 rows (four matrix steps), whole 32-row steps
+  int n = Bp / 128;
+  n = n < 1 ? 1 : n > MLP_MAX_SPLITS ? MLP_MAX_SPLITS : n;
+  const int rows = ((Bp + n - 1) / n + 31) / 32 * 32;
+  *parts = (Bp + rows - 1) / rows;
+  hipLaunchKernelGGL(mlp_dw_kernel, dim3((unsigned)(*parts * DW_PIECES)), dim3(64), 0, st, s, a.ld, Bp, rows);
+  return hipGetLastError();
 }
 
 }  // namespace
@@ -267,90 +517,46 @@ GemmArgs fwd_layer(const uint16_t* X, long ldx, const uint16_t* W, long ldw, int
 hipError_t mlp_forward(const float* params, const float* norm, const float* x, float* y, int B, const MlpScratch& s,
                        hipStream_t st) {
   if (B <= 0) return hipSuccess;
-  hipError_t e;
-  const int T = 256;
-  hipLaunchKernelGGL(convert_weights_kernel, dim3((MLP_H * MLP_H + T - 1) / T), dim3(T), 0, st, params, s.wb);
-  if ((e = hipGetLastError()) != hipSuccess) return e;
-  hipLaunchKernelGGL(input_kernel, dim3((B * MLP_KPAD + T - 1) / T), dim3(T), 0, st, x, norm, s.X0, B);
-  if ((e = hipGetLastError()) != hipSuccess) return e;
-  if ((e = gemm(fwd_layer(s.X0, MLP_KPAD, s.wb, MLP_KPAD, B, MLP_KPAD, params + MLP_OFF_B1, s.Z[0], s.H[0]), st)))
-    return e;
-  if ((e = gemm(fwd_layer(s.H[0], MLP_H, s.wb + MLP_WB_W2, MLP_H, B, MLP_H, params + MLP_OFF_B2, s.Z[1], s.H[1]), st)))
-    return e;
-  if ((e = gemm(fwd_layer(s.H[1], MLP_H, s.wb + MLP_WB_W3, MLP_H, B, MLP_H, params + MLP_OFF_B3, s.Z[2], s.H[2]), st)))
-    return e;
-  hipLaunchKernelGGL(head_kernel, dim3((B + 3) / 4), dim3(256), 0, st, s.H[2], s.wb, params, norm, B, 0, y, nullptr,
-                     nullptr, nullptr);
-  return hipGetLastError();
+  const hipError_t e = convert_weights(params, s, false, st);
+  if (e != hipSuccess) return e;
+  RowArgs a{};
+  a.p = params, a.norm = norm, a.x = x, a.wb = s.wb, a.y = y;
+  a.B = B;
+  const int Bp = mlp_padded_rows(B);
+  if (Bp <= 8192) return launch_rows<1, false>(a, Bp, st);
+  return Bp <= 16384 ? launch_rows<2, false>(a, Bp, st) : launch_rows<4, false>(a, Bp, st);
 }
 
 hipError_t mlp_grad(const float* params, const float* norm, const float* x, const float* yt, int B, float* grad,
                     float* loss, const MlpScratch& s, hipStream_t st) {
   if (B <= 0) return hipSuccess;
-  hipError_t e;
-  const int T = 256;
-  hipLaunchKernelGGL(convert_weights_kernel, dim3((MLP_H * MLP_H + T - 1) / T), dim3(T), 0, st, params, s.wb);
-  if ((e = hipGetLastError()) != hipSuccess) return e;
-  hipLaunchKernelGGL(input_kernel, dim3((B * MLP_KPAD + T - 1) / T), dim3(T), 0, st, x, norm, s.X0, B);
-  if ((e = hipGetLastError()) != hipSuccess) return e;
-  if ((e = gemm(fwd_layer(s.X0, MLP_KPAD, s.wb, MLP_KPAD, B, MLP_KPAD, params + MLP_OFF_B1, s.Z[0], s.H[0]), st)))
-    return e;
-  if ((e = gemm(fwd_layer(s.H[0], MLP_H, s.wb + MLP_WB_W2, MLP_H, B, MLP_H, params + MLP_OFF_B2, s.Z[1], s.H[1]), st)))
-    return e;
-  if ((e = gemm(fwd_layer(s.H[1], MLP_H, s.wb + MLP_WB_W3, MLP_H, B, MLP_H, params + MLP_OFF_B3, s.Z[2], s.H[2]), st)))
-    return e;
-  hipLaunchKernelGGL(head_kernel, dim3((B + 3) / 4), dim3(256), 0, st, s.H[2], s.wb, params, norm, B, 1, nullptr, yt,
-                     s.d, s.sq);
-  if ((e = hipGetLastError()) != hipSuccess) return e;
-  hipLaunchKernelGGL(mean_kernel, dim3(1), dim3(256), 0, st, s.sq, B, loss);
-  if ((e = hipGetLastError()) != hipSuccess) return e;
-  // layer 4: dW4[n] = sum_m d[m] H3[m][n], db4 = sum_m d[m], dZ3 = d W4 silu'(Z3)
-  hipLaunchKernelGGL(colsum_kernel, dim3(MLP_H), dim3(256), 0, st, nullptr, s.H[2], s.d, B, (long)MLP_H,
-                     grad + MLP_OFF_W4);
-  hipLaunchKernelGGL(colsum_kernel, dim3(1), dim3(256), 0, st, s.d, nullptr, nullptr, B, 1L, grad + MLP_OFF_B4);
-  float* dz = s.dZ;
-  float* dz_next = s.dZ2;
-  uint16_t* dzb = s.dZb;
-  uint16_t* dzb_next = s.dZb2;
-  hipLaunchKernelGGL(head_bwd_kernel, dim3((B * MLP_H + T - 1) / T), dim3(T), 0, st, s.d, s.wb, s.Z[2], dz, dzb, B);
-  if ((e = hipGetLastError()) != hipSuccess) return e;
-  const int offW[3] = {MLP_OFF_W1, MLP_OFF_W2, MLP_OFF_W3};
-  const int offB[3] = {MLP_OFF_B1, MLP_OFF_B2, MLP_OFF_B3};
-  const long wbo[3] = {0, MLP_WB_W2, MLP_WB_W3};
-  for (int l = 2; l >= 0; --l) {
-    // dW_l[o][i] = sum_b dZ_l[b][o] H_{l-1}[b][i]
-    const uint16_t* Hin = l == 0 ? s.X0 : s.H[l - 1];
-    const long ldh = l == 0 ? MLP_KPAD : MLP_H;
-    GemmArgs a{};
-    a.A = dzb; a.sam = 1; a.sak = MLP_H;
-    a.B = Hin; a.sbk = ldh; a.sbn = 1;
-    a.M = MLP_H; a.N = l == 0 ? MLP_IN : MLP_H; a.K = B;
-    a.epi = 2; a.Cf = grad + offW[l]; a.ldc = l == 0 ? MLP_IN : MLP_H;
-    if ((e = gemm(a, st))) return e;
-    hipLaunchKernelGGL(colsum_kernel, dim3(MLP_H), dim3(256), 0, st, dz, nullptr, nullptr, B, (long)MLP_H,
-                       grad + offB[l]);
-    if ((e = hipGetLastError()) != hipSuccess) return e;
-    if (l > 0) {
-      // dZ_{l-1} = (dZ_l W_l) * silu'(Z_{l-1})
-      GemmArgs b{};
-      b.A = dzb; b.sam = MLP_H; b.sak = 1;
-      b.B = s.wb + wbo[l]; b.sbk = MLP_H; b.sbn = 1;   // B(k = o, n = i) = W_l[o][i]
-      b.M = B; b.N = MLP_H; b.K = MLP_H;
-      b.epi = 1; b.Zin = s.Z[l - 1]; b.ldz = MLP_H; b.Cf = dz_next; b.Cb = dzb_next; b.ldc = MLP_H;
-      if ((e = gemm(b, st))) return e;
-      float* t = dz; dz = dz_next; dz_next = t;
-      uint16_t* tb = dzb; dzb = dzb_next; dzb_next = tb;
-    }
-  }
-  return hipSuccess;
+  int row_blocks = 0, parts = 0;
+  const hipError_t e = grad_parts(params, norm, x, yt, B, s, &row_blocks, &parts, st);
+  if (e != hipSuccess) return e;
+  hipLaunchKernelGGL((mlp_sum_kernel<false>), dim3(SUM_BLOCKS), dim3(256), 0, st, s, B, row_blocks, parts, grad, loss,
+                     nullptr, nullptr, nullptr, AdamStep{});
+  return hipGetLastError();
 }
 
-hipError_t mlp_adam(float* params, const float* grad, float* m, float* v, int n, int step, double lr, double beta1,
-                    double beta2, double eps, hipStream_t st) {
+AdamStep adam_factors(int step, double lr, double beta1, double beta2, double eps) {
   const double bc1 = 1.0 - std::pow(beta1, (double)step), bc2 = 1.0 - std::pow(beta2, (double)step);
-  hipLaunchKernelGGL(adam_kernel, dim3((n + 255) / 256), dim3(256), 0, st, params, grad, m, v, n, (float)lr,
-                     (float)beta1, (float)(1.0 - beta1), (float)beta2, (float)(1.0 - beta2), (float)eps, (float)bc1,
-                     (float)bc2);
+  return AdamStep{(float)lr,          (float)beta1, (float)(1.0 - beta1), (float)beta2,
+                  (float)(1.0 - beta2), (float)eps,   (float)bc1,           (float)bc2};
+}
+
+hipError_t mlp_adam(float* params, const float* grad, float* m, float* v, int n, const AdamStep& a, hipStream_t st) {
+  hipLaunchKernelGGL(adam_kernel, dim3((n + 255) / 256), dim3(256), 0, st, params, grad, m, v, n, a);
+  return hipGetLastError();
+}
+
+hipError_t mlp_train(float* params, float* m, float* v, const AdamStep& a, const float* norm, const float* x,
+                     const float* yt, int B, float* loss, const MlpScratch& s, hipStream_t st) {
+  if (B <= 0) return hipSuccess;
+  int row_blocks = 0, parts = 0;
+  const hipError_t e = grad_parts(params, norm, x, yt, B, s, &row_blocks, &parts, st);
+  if (e != hipSuccess) return e;
+  hipLaunchKernelGGL((mlp_sum_kernel<true>), dim3(SUM_BLOCKS), dim3(256), 0, st, s, B, row_blocks, parts, nullptr, loss,
+                     params, m, v, a);
   return hipGetLastError();
 }
 
