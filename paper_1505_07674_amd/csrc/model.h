@@ -15,16 +15,31 @@ struct ModelSpec {
   int sie_plane[MAX_SIE];         // per SIE: its lens plane (0 with one plane)
   double beta[MAX_PLANES][MAX_PLANES];  // distance ratios beta_ij, i < j < n_planes (0 with one plane)
 };
+struct SieConst {
+  double x, y, c, s;           // centre, cos and sin of the position angle
+  double q2, qp, k;            // q^2, q' = sqrt(1 - q^2), theta_E sqrt(q)/q'
+  double tesq, s2, te, q, iq2; // theta_E sqrt(q), 1 - q^2, theta_E, q, 1/q^2
+  double iqp, hs;              // 1/q', 1/(2 (1 - q^2)) (0 unless closed)
+  int closed;                  // 1: atan and atanh in closed form; 0: series in 1 - q^2 (nearly round lenses)
+  int pad[3];
+};
+struct SersicConst {
+  double x, y;                 // centre
+  double s11, s12, s21, s22;   // (X, Y) = S (offset from the centre), (R/R_e)^2 = X^2 + Y^2
+  double e, B, I;              // 1/(2n), b_n log2(e), I_e
+  double b, db, q, iRe, c, s, in;   // b_n, db_n/dn (0 unless asked for), q, 1/R_e, cos, sin, 1/n
+};
 struct ModelConst {
-  double sie[MAX_SIE][9];      // x_c, y_c, cos, sin, q^2, q', k = theta_E sqrt(q)/q' (theta_E when q = 1),
-                               // theta_E, q
+  SieConst sie[MAX_SIE];
+  SersicConst ser[MAX_SERSIC];
   double g1, g2;               // external shear (zero without one)
   double gam, c2g, s2g;        // gamma, cos 2 phi_gamma, sin 2 phi_gamma
-  double ser[MAX_SERSIC][11];  // x0, y0, cos, sin, q, 1/q, 1/R_e, 1/n, b_n, I_e, db_n/dn (0 unless asked for)
   double sky;                  // flat sky surface brightness (NaN marks an invalid point)
   int n_sie, n_sersic;
-  int sie_sphere[MAX_SIE];     // 1 where q = 1
   int plane[MAX_SERSIC];       // the Sersic's plane: 0 light at x, n_planes light at the source
 };
+// 1 - q^2 below which a lens is nearly round: u and v stay within 1/q, so the
+// arguments (1 - q^2) u^2 of the series stay below 0.053.
+constexpr double SIE_SERIES_S = 0.05;
 
 }  // namespace lensed

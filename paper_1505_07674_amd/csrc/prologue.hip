@@ -568,24 +568,26 @@ __global__ __launch_bounds__(64) void model_prologue_kernel(const float* __restr
   m.n_sie = spec.n_sie;
   m.n_sersic = spec.n_sersic;
   int o = 0;
-  for (int k = 0; k < MAX_SIE; ++k) {
-    for (int i = 0; i < 9; ++i) m.sie[k][i] = 0.0;
-    m.sie_sphere[k] = 0;
-    if (k >= spec.n_sie) continue;
+  for (int k = 0; k < spec.n_sie; ++k, o += 5) {
     const double te = t[o + 2], q = t[o + 3], ph = t[o + 4];
     valid = valid && q > 0.0 && q <= 1.0;
     const double s2 = (1.0 - q) * (1.0 + q), qp = sqrt(fmax(s2, 0.0));
-    m.sie[k][0] = t[o];
-    m.sie[k][1] = t[o + 1];
-    m.sie[k][2] = cos(ph);
-    m.sie[k][3] = sin(ph);
-    m.sie[k][4] = q * q;
-    m.sie[k][5] = qp;
-    m.sie_sphere[k] = s2 == 0.0;
-    m.sie[k][6] = s2 == 0.0 ? te : te * sqrt(q) / qp;
-    m.sie[k][7] = te;
-    m.sie[k][8] = q;
-    o += 5;
+    SieConst& c = m.sie[k];
+    c.x = t[o];
+    c.y = t[o + 1];
+    c.c = cos(ph);
+    c.s = sin(ph);
+    c.q2 = q * q;
+    c.qp = qp;
+    c.tesq = te * sqrt(q);
+    c.k = s2 == 0.0 ? te : te * sqrt(q) / qp;
+    c.s2 = s2;
+    c.te = te;
+    c.q = q;
+    c.iq2 = 1.0 / (q * q);
+    c.closed = s2 >= SIE_SERIES_S;
+    c.iqp = c.closed ? 1.0 / qp : 0.0;
+    c.hs = c.closed ? 0.5 / s2 : 0.0;
   }
   m.g1 = m.g2 = m.gam = m.c2g = m.s2g = 0.0;
   if (spec.shear) {
@@ -596,23 +598,26 @@ __global__ __launch_bounds__(64) void model_prologue_kernel(const float* __restr
     m.g2 = m.gam * m.s2g;
     o += 2;
   }
-  for (int j = 0; j < MAX_SERSIC; ++j) {
-    for (int i = 0; i < 11; ++i) m.ser[j][i] = 0.0;
-    m.plane[j] = 0;
-    if (j >= spec.n_sersic) continue;
+  for (int j = 0; j < spec.n_sersic; ++j, o += 7) {
     const double Re = t[o + 3], n = t[o + 4], q = t[o + 5], ph = t[o + 6];
     valid = valid && Re > 0.0 && n >= 0.2 && n <= 10.0 && q > 0.0 && q <= 1.0;
     m.plane[j] = spec.plane[j];
-    m.ser[j][0] = t[o];
-    m.ser[j][1] = t[o + 1];
-    m.ser[j][2] = cos(ph);
-    m.ser[j][3] = sin(ph);
-    m.ser[j][4] = q;
-    m.ser[j][5] = 1.0 / q;
-    m.ser[j][6] = 1.0 / Re;
-    m.ser[j][7] = 1.0 / n;
-    m.ser[j][9] = t[o + 2];   // b_n (slot 8) and db_n/dn (slot 10): model_bn_kernel
-    o += 7;
+    SersicConst& c = m.ser[j];
+    c.x = t[o];
+    c.y = t[o + 1];
+    c.c = cos(ph);
+    c.s = sin(ph);
+    const double ax = sqrt(q) / Re, ay = 1.0 / (sqrt(q) * Re);
+    c.s11 = ax * c.c;
+    c.s12 = ax * c.s;
+    c.s21 = -ay * c.s;
+    c.s22 = ay * c.c;
+    c.e = 0.5 / n;
+    c.I = t[o + 2];
+    c.q = q;
+    c.iRe = 1.0 / Re;
+    c.in = 1.0 / n;
+    c.b = c.B = c.db = 0.0;   // model_bn_kernel
   }
   m.sky = spec.sky ? (double)t[o] : 0.0;
   if (!valid) m.sky = __builtin_nan("");
@@ -638,8 +643,9 @@ __global__ __launch_bounds__(3 * MODEL_BN_PAIRS) void model_bn_kernel(const floa
   if (valid) root[v][c] = sersic_bn(v == 0 ? n : (v == 1 ? n + 1e-5 * n : n - 1e-5 * n));
   __syncthreads();
   if (!valid || v != 0) return;
-  out[p].ser[j][8] = root[0][c];
-  if (blockDim.x == 3 * MODEL_BN_PAIRS) out[p].ser[j][10] = (root[1][c] - root[2][c]) / (2e-5 * n);
+  out[p].ser[j].b = root[0][c];
+  out[p].ser[j].B = root[0][c] * LOG2E;
+  if (blockDim.x == 3 * MODEL_BN_PAIRS) out[p].ser[j].db = (root[1][c] - root[2][c]) / (2e-5 * n);
 }
 
 hipError_t launch_model_prologue(const float* theta, int n_points, int n_params, const ModelSpec& spec,
