@@ -671,8 +671,7 @@ int lensed_render_model(lensed_ctx* c, const lensed_system* sys, const lensed_mo
   const size_t npix = (size_t)sd.H * sd.W;
   const size_t off_mc = 0;
   const size_t off_psf = align_up(off_mc + sizeof(ModelConst), 256);
-  const size_t off_cc = align_up(off_psf + 3 * sizeof(float) * sd.ph * sd.pw, 256);
-  const size_t off_L = align_up(off_cc + sizeof(int), 256);
+  const size_t off_L = align_up(off_psf + 3 * sizeof(float) * sd.ph * sd.pw, 256);
   const size_t total = align_up(off_L + sizeof(float) * npix, 256);
   if ((rc = ensure_arena(c, total))) return rc;
   ModelConst* mc = (ModelConst*)(c->arena + off_mc);
@@ -681,9 +680,7 @@ int lensed_render_model(lensed_ctx* c, const lensed_system* sys, const lensed_mo
   WorkArgs w;
   std::memset(&w, 0, sizeof(w));
   w.single = sd;
-  // the 17-parameter prologue with no points normalises the PSF
-  LENSED_HIP(c, launch_prologue(theta, 0, nullptr, nullptr, nullptr, sd, nullptr, 1, (int*)(c->arena + off_cc), st));
-  LENSED_HIP(c, launch_model_prologue(theta, 1, spec_params(spec), spec, mc, st));
+  LENSED_HIP(c, launch_model_prologue(theta, 1, spec_params(spec), spec, mc, sd, nullptr, 1, st));
   LENSED_HIP(c, launch_model_render(w, spec, mc, L, sd.n_rtiles, st));
   if (apply_psf)
     LENSED_HIP(c, launch_psf_single(w, L, image, nullptr, 0, st));

@@ -90,10 +90,11 @@ hipError_t launch_render(const WorkArgs& w, const PointConst* pcs, const PointCo
                          hipEvent_t between = nullptr);
 
 // General models: per-point float64 constants from the parameters (n_params
-// per point, the layout of lensed_model), and the float64 render into L.
-// with_db: also db_n/dn of every Sersic (the adjoint needs it).
+// per point, the layout of lensed_model) and, as launch_prologue, the systems'
+// normalised PSFs; and the float64 render into L.
 hipError_t launch_model_prologue(const float* theta, int n_points, int n_params, const ModelSpec& spec,
-                                 ModelConst* out, hipStream_t stream, bool with_db = false);
+                                 ModelConst* out, const SysDesc& single, const SysDesc* table, int n_sys,
+                                 hipStream_t stream, bool adjoint_tables = false);
 hipError_t launch_model_render(const WorkArgs& w, const ModelSpec& spec, const ModelConst* mcs, float* L, int n_blocks,
                                hipStream_t stream);
 // Adjoint of a general model with one lens plane: per (point, render tile) and

@@ -486,14 +486,13 @@ hipError_t BatchPlan::enqueue(hipStream_t st, hipEvent_t* ev) const {
   std::memset(&none, 0, sizeof(none));
   hipError_t e;
   if (ev && (e = hipEventRecord(ev[0], st)) != hipSuccess) return e;
-  // the 17-parameter prologue also normalises the PSFs; with a general model it does only that
-  if ((e = launch_prologue(theta_, has_model_ ? 0 : n_points_, d_pc_, d_p64_, d_gc_, none, d_sys_,
-                           (int)systems_.size(), cusp_.count, st, d_gcorr_, d_point_sys_, grad_ != nullptr)) !=
-      hipSuccess)
-    return e;
-  if (has_model_ && (e = launch_model_prologue(theta_, n_points_, params_per_point_, spec_, d_mc_, st,
-                                                grad_ != nullptr)) != hipSuccess)
-    return e;
+  // the prologue also normalises the PSFs
+  const int n_sys = (int)systems_.size();
+  e = has_model_ ? launch_model_prologue(theta_, n_points_, params_per_point_, spec_, d_mc_, none, d_sys_, n_sys, st,
+                                         grad_ != nullptr)
+                 : launch_prologue(theta_, n_points_, d_pc_, d_p64_, d_gc_, none, d_sys_, n_sys, cusp_.count, st,
+                                   d_gcorr_, d_point_sys_, grad_ != nullptr);
+  if (e != hipSuccess) return e;
   // a gradient plan's support (the pixels g can reach, which are also the only
   // pixels its forward render needs), from the weights as they are now
   if (grad_ && (e = launch_grad_support(d_sys_, (int)systems_.size(), (int)max_pixels_, st)) != hipSuccess) return e;
