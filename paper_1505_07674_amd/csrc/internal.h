@@ -176,24 +176,35 @@ struct SysDesc {
   // Support of the adjoint's g = A^T rho in a gradient plan: every pixel within
   // the PSF box of a pixel with w > 0 (replicate padding only moves a tap
   // towards the image, so the clamped border taps stay inside that box).
-  // Rebuilt from the weights by every gradient launch (grad_support_*
-  // kernels): gsup[0 .. *gsup_n) its pixels in row-major order, gflags 2 H W
-  // bytes of scratch. nullptr: every pixel.
+  // Rebuilt from the weights by every gradient launch (support.h,
+  // grad_support_kernel): gsup[0 .. *gsup_n) its pixels in row-major order;
+  // gbits its bits, support_words 64-bit words a row; gcount the pixels and
+  // render units of each row's support_segments. nullptr: every pixel.
   int* gsup;
   int* gsup_n;
-  unsigned char* gflags;
+  unsigned long long* gbits;
+  int2* gcount;
   // Render units over the same support (a 17-parameter gradient plan renders
   // only these): the support kernels write the first pixel of each unit of
   // uppt pixels to uact, which `active` also points to, and their number to
   // n_active of the device copy of this descriptor. nullptr: not rebuilt.
   int* uact;
   int uppt;
-  // Per PSF output tile of a gradient plan: 1 if it holds a pixel with w > 0
-  // (set by the support kernels each launch, cleared by the PSF preparation);
-  // the PSF stage skips the others, whose chi^2 terms and rho are all zero.
-  // nullptr: every tile is convolved.
+  // Per PSF output tile of a gradient plan: PTILE_W if it holds a pixel with
+  // w > 0, PTILE_G if it holds one of the support (both rebuilt each launch).
+  // The PSF stage skips the tiles without the first, whose chi^2 terms and rho
+  // are all zero, and the adjoint those without the second, whose g nothing
+  // reads. nullptr: every tile is convolved.
   unsigned char* ptile_w;
 };
+
+constexpr int PTILE_W = 1, PTILE_G = 2;
+// 64-pixel words of a row of gbits, and their segments that gcount counts.
+constexpr int SUPPORT_SEG_WORDS = 8;
+__host__ __device__ inline int support_words(const SysDesc& sd) { return (sd.W + 63) / 64; }
+__host__ __device__ inline int support_segments(const SysDesc& sd) {
+  return (support_words(sd) + SUPPORT_SEG_WORDS - 1) / SUPPORT_SEG_WORDS;
+}
 
 // floor(n / W) for 0 <= n < 2^28 (every pixel index: H W <= 2^28) by one
 // 32 x 32 -> 64-bit product and a shift instead of an integer division

@@ -51,10 +51,12 @@ hipError_t for_item_parts(const WorkArgs& w, int n_blocks, F launch) {
 // point p is table[point_sys[p]] (table[0] without point_sys; single without
 // table); its amplitude mode decides whether theta[5] and theta[12] are I_e or
 // total magnitudes. adjoint_tables: the systems' adjk tables (set in their
-// descriptors) are filled too, as every gradient plan needs.
+// descriptors) are filled too, as every gradient plan needs, and with
+// support_blocks (the most of any system) the bits of the adjoint's support.
 hipError_t launch_prologue(const float* theta, int n_points, PointConst* pcs, PointConst64* p64s, GradConst* gcs,
                            const SysDesc& single, SysDesc* table, int n_sys, int* cusp_count, hipStream_t stream,
-                           double* grad_corr = nullptr, const int* point_sys = nullptr, bool adjoint_tables = false);
+                           double* grad_corr = nullptr, const int* point_sys = nullptr, bool adjoint_tables = false,
+                           int support_blocks = 0);
 
 // Unconvolved pixel luminosities into L (scratch or the caller's image): the
 // float32 render kernel, then the float64 cusp corrections of the pixels it
@@ -94,7 +96,7 @@ hipError_t launch_render(const WorkArgs& w, const PointConst* pcs, const PointCo
 // normalised PSFs; and the float64 render into L.
 hipError_t launch_model_prologue(const float* theta, int n_points, int n_params, const ModelSpec& spec,
                                  ModelConst* out, const SysDesc& single, const SysDesc* table, int n_sys,
-                                 hipStream_t stream, bool adjoint_tables = false);
+                                 hipStream_t stream, bool adjoint_tables = false, int support_blocks = 0);
 hipError_t launch_model_render(const WorkArgs& w, const ModelSpec& spec, const ModelConst* mcs, float* L, int n_blocks,
                                hipStream_t stream);
 // Adjoint of a general model with one lens plane: per (point, render tile) and
@@ -162,17 +164,19 @@ hipError_t launch_adjoint_psf(const WorkArgs& w, const float* R, float* G, int n
 hipError_t launch_grad_sky(const float* R, const int64_t* loff, const int* point_sys, const SysDesc* sys, int K,
                            int n_models, float* grad_sky, hipStream_t st);
 
-// Rebuilds the adjoint's support (SysDesc::gsup) of every system in the device
-// table sys[0 .. n_sys) whose gsup is set, from its weights: a row pass and a
-// column pass of the PSF-box dilation of w > 0 into gflags, then one block per
-// system compacts the flags into the pixel list and, where uact is set, into
-// the render units (writing n_active of the table entry). max_pixels bounds H W.
-hipError_t launch_grad_support(SysDesc* sys, int n_sys, int max_pixels, hipStream_t st);
-
-// Zeroes each point's unconvolved image L outside its system's support, for the
-// systems whose render units are rebuilt with it (uact set); w carries the
-// device system table, the point-to-system map and the image offsets.
-hipError_t launch_grad_clear(const WorkArgs& w, float* L, int n_points, hipStream_t st);
+// Turns the support bits that the prologue's launch made (support.h) into lists,
+// for every system in the device table sys[0 .. n_sys) whose gsup is set: its
+// pixels, and its render units (writing n_active of the table entry); and zeroes
+// each point's unconvolved image L outside its system's support. w carries the
+// system table, the point-to-system map and the image offsets; n the most of any
+// system.
+struct SupportSizes {
+  int blocks = 0;     // of the prologue's launch (support_blocks)
+  int segments = 0;   // row segments: entries of gcount
+  int words = 0;      // of gbits
+};
+hipError_t launch_grad_support(const WorkArgs& w, SysDesc* sys, int n_sys, const SupportSizes& n, float* L,
+                               int n_points, hipStream_t st);
 
 // Per-(point, render tile) sums of g d^2/N^2 times the 17 gradient moments of
 // the subsamples (each partial dI/dtheta is a fixed per-point combination of

@@ -6,6 +6,7 @@
 
 #include "plan.h"
 #include "stencil.h"
+#include "support.h"
 
 namespace lensed {
 
@@ -366,15 +367,30 @@ hipError_t BatchPlan::build(const lensed_system* systems, int n_systems, const f
     o_units[s] = off;
     off = align256(off + sizeof(int) * units[s].size());
   }
-  // the adjoint's support per system: its count (a 256-byte slot), pixel list
-  // and two flag planes, then the render units over it (aligned)
-  auto gsup_units_offset = [](size_t npix) { return align256(256 + sizeof(int) * npix + 2 * npix); };
-  max_pixels_ = 0;
+  // the adjoint's support per system: its count (a 256-byte slot), bits and
+  // counts, pixel list, the render units over it, and the PSF tiles' flags
+  struct Support {
+    size_t bits, counts, pixels, units, tiles, end;
+  };
+  auto support_layout = [](const SysDesc& d) {
+    const size_t npix = (size_t)d.H * d.W;
+    Support l;
+    l.bits = 256;
+    l.counts = align256(l.bits + sizeof(unsigned long long) * d.H * support_words(d));
+    l.pixels = align256(l.counts + sizeof(int2) * d.H * support_segments(d));
+    l.units = align256(l.pixels + sizeof(int) * npix);
+    l.tiles = align256(l.units + sizeof(int) * npix);
+    l.end = align256(l.tiles + d.n_ptiles);
+    return l;
+  };
+  support_ = SupportSizes();
   for (int s = 0; s < n_systems; ++s) {
-    const size_t npix = (size_t)desc[s].H * desc[s].W;
-    max_pixels_ = std::max<int64_t>(max_pixels_, (int64_t)npix);
     o_gsup[s] = off;
-    if (g) off = align256(align256(off + gsup_units_offset(npix) + sizeof(int) * npix) + desc[s].n_ptiles);
+    if (!g) continue;
+    off += support_layout(desc[s]).end;
+    support_.blocks = std::max(support_.blocks, support_blocks(desc[s]));
+    support_.segments = std::max(support_.segments, desc[s].H * support_segments(desc[s]));
+    support_.words = std::max(support_.words, desc[s].H * support_words(desc[s]));
   }
   hipError_t e = hipMalloc((void**)&mem_, off);
   if (e != hipSuccess) {
@@ -413,16 +429,18 @@ hipError_t BatchPlan::build(const lensed_system* systems, int n_systems, const f
     grad_ntiles_ = desc[0].n_rtiles;
     for (int s = 0; s < n_systems; ++s) {
       desc[s].adjk = (float*)(mem_ + o_adjk) + 16 * psf_off[s];
-      const size_t npix = (size_t)desc[s].H * desc[s].W;
-      desc[s].gsup_n = (int*)(mem_ + o_gsup[s]);
-      desc[s].gsup = (int*)(mem_ + o_gsup[s] + 256);
-      desc[s].gflags = (unsigned char*)(mem_ + o_gsup[s] + 256 + sizeof(int) * npix);
+      const Support l = support_layout(desc[s]);
+      char* base = (char*)mem_ + o_gsup[s];
+      desc[s].gsup_n = (int*)base;
+      desc[s].gbits = (unsigned long long*)(base + l.bits);
+      desc[s].gcount = (int2*)(base + l.counts);
+      desc[s].gsup = (int*)(base + l.pixels);
       // the forward render covers only the support too, in units rebuilt with it
-      desc[s].uact = (int*)(mem_ + o_gsup[s] + gsup_units_offset(npix));
+      desc[s].uact = (int*)(base + l.units);
       desc[s].active = desc[s].uact;
       desc[s].uppt = has_model_ ? 1 : class_ppt(render_class(desc[s]));
-      desc[s].n_active = 0;   // written by the support kernels before each render
-      desc[s].ptile_w = (unsigned char*)(mem_ + align256(o_gsup[s] + gsup_units_offset(npix) + sizeof(int) * npix));
+      desc[s].n_active = 0;   // written by the support kernel before each render
+      desc[s].ptile_w = (unsigned char*)(base + l.tiles);
     }
   }
 
@@ -489,14 +507,14 @@ hipError_t BatchPlan::enqueue(hipStream_t st, hipEvent_t* ev) const {
   // the prologue also normalises the PSFs
   const int n_sys = (int)systems_.size();
   e = has_model_ ? launch_model_prologue(theta_, n_points_, params_per_point_, spec_, d_mc_, none, d_sys_, n_sys, st,
-                                         grad_ != nullptr)
+                                         grad_ != nullptr, support_.blocks)
                  : launch_prologue(theta_, n_points_, d_pc_, d_p64_, d_gc_, none, d_sys_, n_sys, cusp_.count, st,
-                                   d_gcorr_, d_point_sys_, grad_ != nullptr);
+                                   d_gcorr_, d_point_sys_, grad_ != nullptr, support_.blocks);
   if (e != hipSuccess) return e;
   // a gradient plan's support (the pixels g can reach, which are also the only
   // pixels its forward render needs), from the weights as they are now
-  if (grad_ && (e = launch_grad_support(d_sys_, (int)systems_.size(), (int)max_pixels_, st)) != hipSuccess) return e;
-  if (grad_ && (e = launch_grad_clear(w, d_L_, n_points_, st)) != hipSuccess) return e;
+  if (grad_ && (e = launch_grad_support(w, d_sys_, n_sys, support_, d_L_, n_points_, st)) != hipSuccess)
+    return e;
   if (ev && (e = hipEventRecord(ev[1], st)) != hipSuccess) return e;
   WorkArgs wr = w;
   wr.items = d_ritems_;

@@ -20,6 +20,7 @@
 #include "internal.h"
 #include "kernels.h"
 #include "sie_poly.h"
+#include "support.h"
 
 namespace lensed {
 namespace {
@@ -243,8 +244,6 @@ __device__ void psf_adjoint_class(const SysDesc& sd, int cls, PsfScratch<true>& 
     const int r = i / SW, c = i - r * SW;
     s.sat[i] = r > 0 && c > 0 ? (double)sd.psf[(r - 1) * sd.pw + c - 1] : 0.0;
   }
-  if (cls == 0 && sd.ptile_w)   // the support kernels, which run next, mark the tiles with w > 0
-    for (int i = t; i < sd.n_ptiles; i += PROLOGUE_THREADS) sd.ptile_w[i] = 0;
   const double inv = psf_normalise(sd, s.part, cls == 0);   // its barrier ends the staging
   if (!sd.adjk) return;   // uniform over the block
   const int cr = cls >> 2, cc = cls & 3;
@@ -283,16 +282,32 @@ __device__ void psf_adjoint_class(const SysDesc& sd, int cls, PsfScratch<true>& 
   }
 }
 
-// Block `block` of the PSF blocks.
+// The blocks after the points': the PSFs', then (gradient plans) the supports',
+// `support` of them for each system.
+static_assert(PROLOGUE_THREADS == SUPPORT_THREADS, "one launch");
 template <bool ADJ>
-__device__ void psf_block(const SysDesc* table, const SysDesc& single, int block, PsfScratch<ADJ>& s) {
+union SystemScratch {
+  PsfScratch<ADJ> psf;
+  SupportScratch support;
+};
+template <bool ADJ>
+__device__ void system_block(const SysDesc* table, const SysDesc& single, int n_sys, int block, int support,
+                             SystemScratch<ADJ>& s) {
   if constexpr (ADJ) {
+    const int psf_blocks = n_sys * PSF_CLASSES;
+    if (block >= psf_blocks) {
+      const int k = block - psf_blocks;
+      const SysDesc sd = table ? table[k / support] : single;
+      support_block(sd, k % support, s.support);
+      return;
+    }
     const SysDesc sd = table ? table[block / PSF_CLASSES] : single;
-    psf_adjoint_class(sd, block % PSF_CLASSES, s);
+    psf_adjoint_class(sd, block % PSF_CLASSES, s.psf);
   } else {
-    psf_normalise(table ? table[block] : single, s.part, true);
+    psf_normalise(table ? table[block] : single, s.psf.part, true);
   }
 }
+inline int system_blocks(bool adj, int n_sys, int support) { return n_sys * (adj ? PSF_CLASSES + support : 1); }
 
 // Lanes of a point, and what they pass to each other.
 constexpr int PROLOGUE_LANES = 32;
@@ -313,18 +328,19 @@ struct PointScratch {
 template <bool ADJ>
 union PrologueScratch {
   PointScratch point[PROLOGUE_POINTS];
-  PsfScratch<ADJ> psf;
+  SystemScratch<ADJ> system;
 };
 
 template <bool ADJ>
 __global__ __launch_bounds__(PROLOGUE_THREADS) void prologue_kernel(
     const float* __restrict__ theta, int n_points, PointConst* __restrict__ pcs, PointConst64* __restrict__ p64s,
     GradConst* __restrict__ gcs, const SysDesc* __restrict__ table, const int* __restrict__ point_sys,
-    int* __restrict__ cusp_count, double* __restrict__ grad_corr, SysDesc single, int point_blocks) {
+    int* __restrict__ cusp_count, double* __restrict__ grad_corr, SysDesc single, int point_blocks,
+    int n_sys, int support) {
   if (cusp_count && blockIdx.x == 0 && threadIdx.x == 0) *cusp_count = 0;
   __shared__ PrologueScratch<ADJ> lds;
   if ((int)blockIdx.x >= point_blocks) {
-    psf_block<ADJ>(table, single, blockIdx.x - point_blocks, lds.psf);
+    system_block<ADJ>(table, single, n_sys, blockIdx.x - point_blocks, support, lds.system);
     return;
   }
   const int pl = threadIdx.x / PROLOGUE_LANES, j = threadIdx.x % PROLOGUE_LANES;
@@ -586,10 +602,11 @@ __global__ __launch_bounds__(PROLOGUE_THREADS) void model_prologue_kernel(const 
                                                                           int n_params, ModelSpec spec,
                                                                           ModelConst* __restrict__ out,
                                                                           const SysDesc* __restrict__ table,
-                                                                          SysDesc single, int point_blocks) {
+                                                                          SysDesc single, int point_blocks, int n_sys,
+                                                                          int support) {
   if ((int)blockIdx.x >= point_blocks) {
-    __shared__ PsfScratch<ADJ> lds;
-    psf_block<ADJ>(table, single, blockIdx.x - point_blocks, lds);
+    __shared__ SystemScratch<ADJ> lds;
+    system_block<ADJ>(table, single, n_sys, blockIdx.x - point_blocks, support, lds);
     return;
   }
   const int pl = threadIdx.x / PROLOGUE_LANES, j = threadIdx.x % PROLOGUE_LANES;
@@ -669,12 +686,12 @@ __global__ __launch_bounds__(PROLOGUE_THREADS) void model_prologue_kernel(const 
 
 template <bool ADJ>
 hipError_t model_prologue(const float* theta, int n_points, int n_params, const ModelSpec& spec, ModelConst* out,
-                          const SysDesc& single, const SysDesc* table, int n_sys, hipStream_t stream) {
+                          const SysDesc& single, const SysDesc* table, int n_sys, int support, hipStream_t stream) {
   const int point_blocks = (n_points + PROLOGUE_POINTS - 1) / PROLOGUE_POINTS;
-  const int blocks = point_blocks + n_sys * (ADJ ? PSF_CLASSES : 1);
+  const int blocks = point_blocks + system_blocks(ADJ, n_sys, support);
   if (blocks == 0) return hipSuccess;
   hipLaunchKernelGGL(model_prologue_kernel<ADJ>, dim3(blocks), dim3(PROLOGUE_THREADS), 0, stream, theta, n_points,
-                     n_params, spec, out, table, single, point_blocks);
+                     n_params, spec, out, table, single, point_blocks, n_sys, support);
   return hipGetLastError();
 }
 
@@ -682,23 +699,24 @@ hipError_t model_prologue(const float* theta, int n_points, int n_params, const 
 
 hipError_t launch_model_prologue(const float* theta, int n_points, int n_params, const ModelSpec& spec,
                                  ModelConst* out, const SysDesc& single, const SysDesc* table, int n_sys,
-                                 hipStream_t stream, bool adjoint_tables) {
-  return adjoint_tables ? model_prologue<true>(theta, n_points, n_params, spec, out, single, table, n_sys, stream)
-                        : model_prologue<false>(theta, n_points, n_params, spec, out, single, table, n_sys, stream);
+                                 hipStream_t stream, bool adjoint_tables, int support) {
+  return adjoint_tables
+             ? model_prologue<true>(theta, n_points, n_params, spec, out, single, table, n_sys, support, stream)
+             : model_prologue<false>(theta, n_points, n_params, spec, out, single, table, n_sys, support, stream);
 }
 
 hipError_t launch_prologue(const float* theta, int n_points, PointConst* pcs, PointConst64* p64s, GradConst* gcs,
                            const SysDesc& single, SysDesc* table, int n_sys, int* cusp_count, hipStream_t stream,
-                           double* grad_corr, const int* point_sys, bool adjoint_tables) {
+                           double* grad_corr, const int* point_sys, bool adjoint_tables, int support) {
   const int point_blocks = (n_points + PROLOGUE_POINTS - 1) / PROLOGUE_POINTS;
-  const int blocks = point_blocks + n_sys * (adjoint_tables ? PSF_CLASSES : 1);
+  const int blocks = point_blocks + system_blocks(adjoint_tables, n_sys, support);
   if (blocks == 0) return hipSuccess;
   if (adjoint_tables)
     hipLaunchKernelGGL(prologue_kernel<true>, dim3(blocks), dim3(PROLOGUE_THREADS), 0, stream, theta, n_points, pcs,
-                       p64s, gcs, table, point_sys, cusp_count, grad_corr, single, point_blocks);
+                       p64s, gcs, table, point_sys, cusp_count, grad_corr, single, point_blocks, n_sys, support);
   else
     hipLaunchKernelGGL(prologue_kernel<false>, dim3(blocks), dim3(PROLOGUE_THREADS), 0, stream, theta, n_points, pcs,
-                       p64s, gcs, table, point_sys, cusp_count, grad_corr, single, point_blocks);
+                       p64s, gcs, table, point_sys, cusp_count, grad_corr, single, point_blocks, n_sys, support);
   return hipGetLastError();
 }
 

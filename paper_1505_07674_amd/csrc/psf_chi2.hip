@@ -161,7 +161,7 @@ __global__ __launch_bounds__(PSF_MAX_THREADS, KP <= 24 ? 4 : 2) void psf_kernel(
   const int ty = tile / tiles_x, tx = tile - ty * tiles_x;
   const int x0 = tx * TW, y0 = ty * TH;
   const int tid = threadIdx.x;
-  if (sd.ptile_w && !sd.ptile_w[tile]) {   // no pixel with w > 0 (gradient plans): zero chi^2, zero rho
+  if (sd.ptile_w && !(sd.ptile_w[tile] & PTILE_W)) {   // no pixel with w > 0 (gradient plans): zero chi^2, zero rho
     if (mode == 2)
       for (int k = tid; k < TW * TH; k += blockDim.x) {
         const int gi = y0 + k / TW, gj = x0 + k % TW;
