@@ -12,9 +12,9 @@
 // parameters through beta = x - alpha(x) (Eq. 1) using the SIE Jacobian
 //   d alpha'/d x' = theta_E sqrt(q)/(psi r^2) [[y'^2, -x'y'], [-x'y', x'^2]].
 // Each partial is a fixed per-point linear combination of 17 moments (sums
-// over subsamples of products that vary per subsample, e.g. sum D h'_x^2),
-// so the kernels accumulate the moments and the final pass maps them to the
-// 17 partials in float64 (grad_from_moments). Sums are float32 per thread,
+// over subsamples of products that vary per subsample, without the per-point
+// factors), so the kernels accumulate the moments and the final pass maps them
+// to the 17 partials in float64 (grad_from_moments). Sums are float32 per thread,
 // combined across the block and across tiles in float64.
 #include <math.h>
 
@@ -196,26 +196,6 @@ __global__ __launch_bounds__(BORDER_SEG* BORDER_SUB) void adj_border_kernel(Work
 // Per-subsample partial derivatives.
 // ---------------------------------------------------------------------------
 
-// Sersic value and derivatives at scaled squared radius rho2.
-struct SersicD {
-  float I, E, D;     // value, I/I_e, dI/drho2
-  float dn;          // dI/dn
-};
-
-__device__ __forceinline__ SersicD sersic_d(float rho2, float e, float B, float Ie, float b, float db) {
-  SersicD r;
-  const float L2 = hw_log2(rho2);
-  const float t = hw_exp2(e * L2);
-  r.E = hw_exp2(fmaf(-B, t, B));
-  r.I = Ie * r.E;
-  const bool pos = rho2 > 0.0f;
-  r.D = pos ? -r.I * b * t * e * hw_rcp(rho2) : 0.0f;
-  // dI/dn = I [b'(1 - t) + b t ln(rho2) / (2 n^2)],  1/(2n^2) = 2 e^2
-  const float tl = pos ? t * (L2 * LN2F) : 0.0f;
-  r.dn = r.I * fmaf(db, 1.0f - t, b * tl * 2.0f * e * e);
-  return r;
-}
-
 // Series of d/ds [atan(sqrt(s) u)/sqrt(s)] and d/ds [atanh(sqrt(s) v)/sqrt(s)] for small s.
 __device__ __forceinline__ float datan_ds_series(float s, float u) {
   const float u2 = u * u, z = s * u2;
@@ -233,183 +213,226 @@ __device__ __forceinline__ float datanh_ds_series(float s, float v) {
   return v * v2 * poly;
 }
 
-constexpr float S_SERIES = 0.0625f;   // use the series for 1 - q^2 below this
-
-// Adds the 17 partial derivatives of I at subsample (x, y) to acc, times the
-// quadrature weight sw when WT (a Gauss-Kronrod node). With `override`, the
-// offset of beta from the source centre is (odx, ody) instead of the float32
-// lens equation (the float64 re-traced value near a cuspy source).
-// SER: 1 the series in s, 0 the closed form, -1 chosen here by s (a per-point
-// choice that a caller may take once outside its subsample loop).
-template <int MODE, bool WT = false, int SER = -1>
-__device__ __forceinline__ void subsample_grad(const PointConst& c, const GradUniform& U, float x, float y,
-                                               float (&acc)[NPAR], bool override = false, float odx = 0.0f,
-                                               float ody = 0.0f, float sw = 1.0f) {
-  // ---- SIE in its own frame
-  const float xp = fmaf(c.cL, x, c.sL * y);
-  const float yp = fmaf(c.cL, y, -c.sL * x);
-  const float yp2 = yp * yp;
-  const float psi2 = fmaf(c.q2 * xp, xp, yp2);
-  const float r2 = fmaf(xp, xp, yp2);
-  const bool live = psi2 > 0.0f;
-  const float ip = live ? hw_rsq(psi2) : 0.0f;
-  const float u0 = xp * ip, v0 = yp * ip;   // x'/psi, y'/psi
-  float a, b;                                // atan(q'u0)/q', atanh(q'v0)/q'
-  if (MODE == 0) {
-    a = u0;
-    b = v0;
-  } else if (MODE == 1) {
-    a = atan_small(c.qp * u0) * U.iqp;
-    b = atanh_poly(c.qp * v0) * U.iqp;
-  } else {
-    const float ir = live ? hw_rsq(r2) : 0.0f;
-    const float psi = psi2 * ip;
-    const float r = r2 * ir;
-    a = live ? 2.0f * atan_unit(c.qp * xp * hw_rcp(psi + r)) * U.iqp : 0.0f;
-    const float num = fmaf(c.qp, fabsf(yp), psi);
-    b = live ? copysignf(LN2F * hw_log2(num * ir * c.iq), yp) * U.iqp : 0.0f;
-  }
-  const float apx = U.tesq * a, apy = U.tesq * b;   // alpha' in the frame
-  // d/ds of a and b
-  float da, db;
-  if (SER == 1 || (SER < 0 && U.s < S_SERIES)) {
-    da = datan_ds_series(U.s, u0);
-    db = datanh_ds_series(U.s, v0);
-  } else {
-    const float pr = live ? psi2 * hw_rcp(r2) : 0.0f;   // psi^2 / r^2
-    da = (u0 * pr - a) * U.hs;
-    db = (v0 * pr * U.iq2 - b) * U.hs;
-  }
-  const float pr2 = live ? psi2 * hw_rcp(r2) : 0.0f;
-  // back to the image frame
-  const float ax = fmaf(c.cL, apx, -c.sL * apy), ay = fmaf(c.sL, apx, c.cL * apy);
-  // ---- lens equation and source
-  const float bx = fmaf(c.m11, x, fmaf(c.m12, y, -ax));
-  const float by = fmaf(c.m12, x, fmaf(c.m22, y, -ay));
-  const float dx = override ? odx : bx - c.sx0, dy = override ? ody : by - c.sy0;
-  const float sxp = fmaf(c.sc, dx, c.ss * dy);
-  const float syp = fmaf(c.sc, dy, -c.ss * dx);
-  const float sx2 = sxp * sxp, sy2 = syp * syp;
-  const float srho2 = fmaf(c.sqa, sx2, c.sqb * sy2);
-  SersicD Sd = sersic_d(srho2, c.se, c.sB, c.sI, U.bS, U.dbS);
-  if (WT) {
-    Sd.E *= sw;
-    Sd.D *= sw;
-    Sd.dn *= sw;
-  }
-  // dI/dbeta in the SIE frame: D times the source-frame gradient of rho^2,
-  // rotated by phi_S - phi_L
-  const float gxp = 2.0f * c.sqa * sxp, gyp = 2.0f * c.sqb * syp;
-  const float Gx = Sd.D * fmaf(gxp, U.kS1, -gyp * U.kS2);
-  const float Gy = Sd.D * fmaf(gxp, U.kS2, gyp * U.kS1);
-  // ---- lens light
-  const float hxp = fmaf(c.hc, x, c.hs * y);
-  const float hyp = fmaf(c.hc, y, -c.hs * x);
-  const float hx2 = hxp * hxp, hy2 = hyp * hyp;
-  const float hrho2 = fmaf(c.hqa, hx2, c.hqb * hy2);
-  SersicD Hd = sersic_d(hrho2, c.he, c.hB, c.hI, U.bH, U.dbH);
-  if (WT) {
-    Hd.E *= sw;
-    Hd.D *= sw;
-    Hd.dn *= sw;
-  }
-  // ---- accumulate the moments (grad_from_moments maps them to the partials)
-  const float u2pr = u0 * u0 * pr2;
-  acc[0] += fmaf(a, Gx, b * Gy);
-  acc[1] += fmaf(Gx, fmaf(2.0f, da, u0 * u2pr), Gy * fmaf(2.0f, db, v0 * u2pr * U.iq2));
-  acc[2] += fmaf(v0 - b, Gx, (a - u0) * Gy);
-  acc[3] += fmaf(Gx, xp, -Gy * yp);
-  acc[4] += fmaf(Gx, yp, Gy * xp);
-  acc[5] += Hd.E;
-  acc[6] += Hd.D * hx2;
-  acc[7] += Hd.dn;
-  acc[8] += Hd.D * hy2;
-  acc[9] += Hd.D * (hxp * hyp);
-  acc[10] += Gx;
-  acc[11] += Gy;
-  acc[12] += Sd.E;
-  acc[13] += Sd.D * sx2;
-  acc[14] += Sd.dn;
-  acc[15] += Sd.D * sy2;
-  acc[16] += Sd.D * (sxp * syp);
+template <int DEG>
+__device__ __forceinline__ float grad_poly(const float* p, float z) {
+  float v = p[DEG];
+#pragma unroll
+  for (int k = DEG - 1; k >= 0; --k) v = fmaf(v, z, p[k]);
+  return v;
 }
 
-// The 17 partials from the moments, for one point, in float64:
-//   M0 = sum a G'x + b G'y,  M1 = sum G'x (2 da + u0^3 pr) + G'y (2 db + v0 u0^2 pr / q^2),
-//   M2 = sum (v0 - b) G'x + (a - u0) G'y,  M3 = sum G'x x' - G'y y',  M4 = sum G'x y' + G'y x'
-// (G' = dI/dbeta in the SIE frame, x' the SIE frame), M10, M11 = sum G', and
-// per Sersic the value, dI/dn and D times x'^2, y'^2, x'y' in its own frame.
-__device__ void grad_from_moments(const double (&M)[NPAR], const PointConst& c, const GradConst& gc, double (&g)[NPAR]) {
+// Offset of subsample k of N, hN = 1/(2N): (k + 1/2)/N - 1/2 = (2k + 1 - N)/(2N), exactly
+// 0 at the middle of an odd N (a light centre there is a singular point). The
+// gradient needs the abscissae to float32 accuracy, not bit for bit those of the
+// render; but the cusp correction takes back what grad_kernel added, so the two
+// share every expression from here to the moments, without contractions that a
+// compiler might make in one of them only.
+__device__ __forceinline__ float grad_offset(int k, int N, float hN) { return (float)(2 * k + 1 - N) * hN; }
+
+// What depends on the row of subsamples only.
+struct GradRow {
+  float sLy, cLy, rX, rY, h12y, h22y;
+  __device__ __forceinline__ GradRow(const GradUniform& U, float y)
+      : sLy(U.sL * y), cLy(U.cL * y), rX(fmaf(U.B1, y, U.C1)), rY(fmaf(U.B2, y, U.C2)), h12y(U.h12 * y), h22y(U.h22 * y) {}
+};
+
+// One Sersic at frame coordinates (X, Y): E = I/I_e, Et = E t and D = E t/R^2
+// (dI/dR^2 = -I_e b e D; 0 at the centre, where t = 0), and its five moments.
+template <bool WT>
+__device__ __forceinline__ float sersic_moments(float X, float Y, float e, float B, float sw, float* acc) {
+  #pragma clang fp contract(off)
+  const float R2 = fmaf(X, X, Y * Y);
+  const float L2 = hw_log2(R2);
+  const float t = hw_exp2(e * L2);
+  float E = hw_exp2(fmaf(-B, t, B));
+  if (WT) E *= sw;
+  const float Et = E * t;
+  const float D = Et * hw_rcp(fmaxf(R2, 1e-37f));
+  const float DX = D * X;
+  acc[0] += E;
+  acc[1] += Et;
+  acc[2] = fmaf(Et, fmaxf(L2, -200.0f), acc[2]);
+  acc[3] = fmaf(DX, X, acc[3]);
+  acc[4] = fmaf(DX, Y, acc[4]);
+  return D;
+}
+
+// Adds the 17 moments of the subsample (x, row) to acc, times the quadrature
+// weight sw when WT (a Gauss-Kronrod node). RM is the point's rmode, SER its
+// choice of the series in s. With AT, (oX, oY) is the source frame instead of
+// the float32 lens equation (the float64 re-traced value near a cuspy source);
+// without LIGHT the lens light is left out.
+// x'^2 carries SIE_TINY so that the lens centre needs no branch, as in the
+// forward render. With G = D (gXx X + gYx Y, gXy X + gYy Y), which is dI/d beta
+// in the SIE frame up to the per-point factor -2 I_e b e:
+//   0: a Gx + b Gy   1: the q derivative beyond moment 0   2: (v0 - b) Gx + (a - u0) Gy
+//   3: Gx x' - Gy y'   4: Gx y' + Gy x'   5, 6: G   7..11 lens light, 12..16 source:
+//   E, E t, E t log2(R^2), D X^2, D X Y
+// (D Y^2 is E t - D X^2). The q derivative is Gx (2 da + u0^3 pr) + Gy (2 db +
+// v0 u0^2 pr/q^2), pr = psi^2/r^2; with da = (u0 pr - a)/(2s) and db = (v0 pr/q^2 -
+// b)/(2s) that is (Gx u0 + Gy v0/q^2) pr (u0^2 + 1/s) - (moment 0)/s.
+template <int RM, bool SER, bool WT, bool AT = false, bool LIGHT = true>
+__device__ __forceinline__ void subsample_grad(const GradUniform& U, const GradRow& row, float x, float sw,
+                                               float (&acc)[NPAR], float oX = 0.0f, float oY = 0.0f) {
+#pragma clang fp contract(off)
+  const float xp = fmaf(U.cL, x, row.sLy);
+  const float yp = fmaf(-U.sL, x, row.cLy);
+  const float yp2 = yp * yp;
+  const float x2t = fmaf(xp, xp, SIE_TINY);
+  const float r2 = x2t + yp2;
+  const float psi2 = RM == 0 ? r2 : fmaf(U.q2, x2t, yp2);
+  const float ip = hw_rsq(psi2);
+  const float u0 = xp * ip, v0 = yp * ip;
+  float a, b, pr;
+  if (RM == 0) {
+    a = u0;
+    b = v0;
+    pr = 1.0f;
+  } else if (RM == 1) {
+    a = u0 * grad_poly<ATAN_SMALL_POLY_DEGREE>(U.P, u0 * u0);
+    b = v0 * grad_poly<ATANH_POLY_DEGREE>(U.Q, v0 * v0);
+    pr = psi2 * hw_rcp(r2);
+  } else {
+    const float ir = hw_rsq(r2);
+    const float psi = psi2 * ip;
+    const float w = xp * hw_rcp(fmaf(r2, ir, psi));
+    a = w * grad_poly<RM == 2 ? ATAN_SMALL_POLY_DEGREE : ATAN_UNIT_POLY_DEGREE>(U.P, w * w);
+    b = copysignf(fmaf(U.kb, hw_log2(fmaf(U.qp, fabsf(yp), psi) * ir), U.kc), yp);
+    const float pq = psi * ir;
+    pr = pq * pq;
+  }
+  const float X = AT ? oX : fmaf(U.Xa, a, fmaf(U.Xb, b, fmaf(U.A1, x, row.rX)));
+  const float Y = AT ? oY : fmaf(U.Ya, a, fmaf(U.Yb, b, fmaf(U.A2, x, row.rY)));
+  const float D = sersic_moments<WT>(X, Y, U.se, U.sB, sw, acc + 12);
+  const float DX = D * X, DY = D * Y;
+  const float Gx = fmaf(U.gXx, DX, U.gYx * DY), Gy = fmaf(U.gXy, DX, U.gYy * DY);
+  acc[0] = fmaf(b, Gy, fmaf(a, Gx, acc[0]));
+  if (SER) {
+    const float u2pr = u0 * u0 * pr;
+    const float da = datan_ds_series(U.s, u0), db = datanh_ds_series(U.s, v0);
+    acc[1] = fmaf(Gx, fmaf(2.0f, da, u0 * u2pr), acc[1]);
+    acc[1] = fmaf(Gy, fmaf(2.0f, db, v0 * u2pr * U.iq2), acc[1]);
+  } else {
+    acc[1] = fmaf(fmaf(Gx, u0, Gy * (v0 * U.iq2)), pr * fmaf(u0, u0, U.hs2), acc[1]);
+  }
+  acc[2] = fmaf(a - u0, Gy, fmaf(v0 - b, Gx, acc[2]));
+  acc[3] = fmaf(-Gy, yp, fmaf(Gx, xp, acc[3]));
+  acc[4] = fmaf(Gy, xp, fmaf(Gx, yp, acc[4]));
+  acc[5] += Gx;
+  acc[6] += Gy;
+  if (LIGHT) (void)sersic_moments<WT>(fmaf(U.h11, x, row.h12y), fmaf(U.h21, x, row.h22y), U.he, U.hB, sw, acc + 7);
+}
+
+// Calls f with the point's mode as a type: the choices are per point, taken once
+// outside the subsample loops. s < GRAD_SERIES_S implies mode 0 or 1.
+template <int RM_, bool SER_>
+struct GradMode {
+  static constexpr int RM = RM_;
+  static constexpr bool SER = SER_;
+};
+template <class F>
+__device__ __forceinline__ void with_mode(int rmode, int series, F f) {
+  switch (rmode) {
+    case 0: f(GradMode<0, true>()); break;
+    case 1:
+      if (series) f(GradMode<1, true>());
+      else f(GradMode<1, false>());
+      break;
+    case 2: f(GradMode<2, false>()); break;
+    default: f(GradMode<3, false>()); break;
+  }
+}
+
+// The 17 partials from the moments, for one point, in float64. D of the moments
+// stands for dI/dR^2 = -I_e b e D of the light, R^2 = X^2 + Y^2 in its frame.
+__device__ void grad_from_moments(const double (&M)[NPAR], const GradConst& gc, double (&g)[NPAR]) {
   const double te = gc.theta[0], q = gc.theta[1], sq = sqrt(q), gam = gc.theta[3];
-  const double cL = c.cL, sL = c.sL;
+  const double cL = gc.u.cL, sL = gc.u.sL;
+  const double nh = gc.theta[7], ns = gc.theta[14], qh = gc.theta[8], qs = gc.theta[15];
+  const double Ih = gc.Ih, Is = gc.Is, bh = gc.bh, bs = gc.bs;
+  const double kh = -Ih * bh * (0.5 / nh), ks = -Is * bs * (0.5 / ns);
+  const double G = 2.0 * ks;
+  const double M0 = G * M[0], M1 = G * (M[1] - (double)gc.u.hs2 * M[0]), M2 = G * M[2], M3 = G * M[3], M4 = G * M[4];
+  const double Gx = G * M[5], Gy = G * M[6];
   // the shear angle relative to the SIE frame
   const double ph = 2.0 * ((double)gc.theta[4] - (double)gc.theta[2]);
   const double c2 = cos(ph), s2 = sin(ph);
-  g[0] = -sq * M[0];
-  g[1] = -te * (0.5 / sq * M[0] - sq * q * M[1]);
-  g[2] = -te * sq * M[2];
-  g[3] = -(c2 * M[3] + s2 * M[4]);
-  g[4] = -2.0 * gam * (c2 * M[4] - s2 * M[3]);
-  const double hqa = c.hqa, hqb = c.hqb, sqa = c.sqa, sqb = c.sqb;
-  g[5] = M[5];
-  g[6] = -2.0 / gc.theta[6] * (hqa * M[6] + hqb * M[8]);
-  g[7] = M[7];
-  g[8] = (hqa * M[6] - hqb * M[8]) / gc.theta[8];
-  g[9] = 2.0 * (hqa - hqb) * M[9];
-  g[10] = -(cL * M[10] - sL * M[11]);
-  g[11] = -(sL * M[10] + cL * M[11]);
-  g[12] = M[12];
-  g[13] = -2.0 / gc.theta[13] * (sqa * M[13] + sqb * M[15]);
-  g[14] = M[14];
-  g[15] = (sqa * M[13] - sqb * M[15]) / gc.theta[15];
-  g[16] = 2.0 * (sqa - sqb) * M[16];
+  g[0] = -sq * M0;
+  g[1] = -te * (0.5 / sq * M0 - sq * q * M1);
+  g[2] = -te * sq * M2;
+  g[3] = -(c2 * M3 + s2 * M4);
+  g[4] = -2.0 * gam * (c2 * M4 - s2 * M3);
+  g[10] = -(cL * Gx - sL * Gy);
+  g[11] = -(sL * Gx + cL * Gy);
+  // per light: dR^2/dR_e = -2 R^2/R_e, dR^2/dq = (X^2 - Y^2)/q, dR^2/dphi = 2 (q - 1/q) X Y, and
+  // dI/dn = I [b'(1 - t) + b t ln(R^2)/(2 n^2)]
+  const double ln2 = 0.693147180559945309417;
+  const double *mh = M + 7, *ms = M + 12;
+  g[5] = mh[0];
+  g[6] = -2.0 / gc.theta[6] * kh * mh[1];
+  g[7] = Ih * ((double)gc.dbh * (mh[0] - mh[1]) + bh * (0.5 / (nh * nh)) * ln2 * mh[2]);
+  g[8] = kh * (2.0 * mh[3] - mh[1]) / qh;
+  g[9] = 2.0 * kh * (qh - 1.0 / qh) * mh[4];
+  g[12] = ms[0];
+  g[13] = -2.0 / gc.theta[13] * ks * ms[1];
+  g[14] = Is * ((double)gc.dbs * (ms[0] - ms[1]) + bs * (0.5 / (ns * ns)) * ln2 * ms[2]);
+  g[15] = ks * (2.0 * ms[3] - ms[1]) / qs;
+  g[16] = 2.0 * ks * (qs - 1.0 / qs) * ms[4];
 }
 
-// The subsample offsets (k + 1/2)/N - 1/2 by a multiply with 1/N (to a float32
-// rounding of the quotient: the gradient needs the abscissae to float32
-// accuracy, not bit for bit those of the render).
-template <int MODE, int SER>
-__device__ __forceinline__ void pixel_grad(const PointConst& c, const GradUniform& U, int N, const PixelGeom& g,
+// A pixel's subsamples: the N x N midpoints, or the Cartesian square of a
+// Gauss-Kronrod rule's N nodes, each weighted by w_i w_j (the pixel weight d^2
+// multiplies later).
+template <bool GK>
+__device__ __forceinline__ void pixel_grad(int rmode, const GradUniform& U, int rule, int N, const PixelGeom& g,
                                            float (&acc)[NPAR]) {
-  const float iN = 1.0f / (float)N;
-  for (int ky = 0; ky < N; ++ky) {
-    const float y = fmaf(g.uy + fmaf((float)ky + 0.5f, iN, -0.5f), g.d, g.cy);
-    for (int kx = 0; kx < N; ++kx) {
-      const float x = fmaf(g.ux + fmaf((float)kx + 0.5f, iN, -0.5f), g.d, g.cx);
-      subsample_grad<MODE, false, SER>(c, U, x, y, acc);
+  with_mode(rmode, U.series, [&](auto mode) {
+    using M = decltype(mode);
+    if (GK) {
+      const GkRule& R = kGkRules[rule - 1];
+      for (int ky = 0; ky < N; ++ky) {
+        const GradRow row(U, fmaf(g.uy + R.x[ky], g.d, g.cy));
+        for (int kx = 0; kx < N; ++kx)
+          subsample_grad<M::RM, M::SER, true>(U, row, fmaf(g.ux + R.x[kx], g.d, g.cx), R.w[kx] * R.w[ky], acc);
+      }
+    } else {
+      const float hN = 0.5f / (float)N;
+      for (int ky = 0; ky < N; ++ky) {
+        const GradRow row(U, fmaf(g.uy + grad_offset(ky, N, hN), g.d, g.cy));
+        for (int kx = 0; kx < N; ++kx)
+          subsample_grad<M::RM, M::SER, false>(U, row, fmaf(g.ux + grad_offset(kx, N, hN), g.d, g.cx), 1.0f, acc);
+      }
     }
-  }
+  });
 }
 
-// The same over the Cartesian square of a Gauss-Kronrod rule (K nodes), each
-// subsample weighted by w_i w_j (the pixel weight d^2 multiplies later).
-template <int MODE>
-__device__ __forceinline__ void pixel_grad_gk(const PointConst& c, const GradUniform& U, int rule, int K,
-                                              const PixelGeom& g, float (&acc)[NPAR]) {
-  const GkRule& R = kGkRules[rule - 1];
-  for (int ky = 0; ky < K; ++ky) {
-    const float y = fmaf(g.uy + R.x[ky], g.d, g.cy);
-    for (int kx = 0; kx < K; ++kx) {
-      const float x = fmaf(g.ux + R.x[kx], g.d, g.cx);
-      subsample_grad<MODE, true>(c, U, x, y, acc, false, 0.0f, 0.0f, R.w[kx] * R.w[ky]);
-    }
-  }
+// Sum over the 16 lanes of a row (row rotations), in each of them.
+template <int R>
+__device__ __forceinline__ double add_rotated(double v) {
+  const int lo = __builtin_amdgcn_mov_dpp(__double2loint(v), 0x120 + R, 0xf, 0xf, true);
+  const int hi = __builtin_amdgcn_mov_dpp(__double2hiint(v), 0x120 + R, 0xf, 0xf, true);
+  return v + __hiloint2double(hi, lo);
+}
+__device__ __forceinline__ double row_sum(double v) {
+  return add_rotated<1>(add_rotated<2>(add_rotated<4>(add_rotated<8>(v))));
 }
 
 // One thread per pixel, one block per (point, render tile): sums
 // g_pix * d^2/N^2 * dI/dtheta over the pixel's subsamples, then over the block.
-// The series-or-closed-form choice of the SIE's d/ds is per point, taken once
-// outside the subsample loops. Six waves per SIMD (at most 80 VGPRs, no
-// spills) hide the latency of the transcendental chains better than five.
-// (A kernel per N with the midpoint loops unrolled issued 7 % fewer
-// instructions but needed 96 VGPRs, and five waves ran 6 % slower.)
+// What bounds it: the issue rate, about 100 vector instructions a subsample (12 of
+// them transcendental) in the modes with a logarithm; 174 before the source frame,
+// the deflection polynomials and every per-point factor of the partials were folded
+// into constants, and the q derivative and Y^2 taken from other moments. 1024 points
+// of 200 x 200 pixels (41 % of them in the support), N = 4: 1107 -> 745 us, 30 us of it
+// from the block sums by 16 lanes a moment instead of a wave. Six waves per SIMD hide
+// the transcendental chains; five and seven measured the same.
 __global__ __launch_bounds__(RENDER_BLOCK, 6) void grad_kernel(WorkArgs w, const PointConst* __restrict__ pcs,
                                                              const GradConst* __restrict__ gcs,
                                                              const float* __restrict__ G,
                                                              const int* __restrict__ gpbase,
                                                              float2* __restrict__ gpart) {
-  static_assert(RENDER_BLOCK == 256, "the block sums read four entries per lane");
-  __shared__ float part[NPAR][RENDER_BLOCK];
+  static_assert(RENDER_BLOCK == 256, "the block sums take 16 entries per lane");
+  __shared__ float part[NPAR][RENDER_BLOCK + 16];   // four moments' 16 entries in different banks
   int point, tile;
   resolve(w, point, tile);
   const SysDesc sd = w.sys_table ? w.sys_table[w.point_sys ? w.point_sys[point] : 0] : w.single;
@@ -441,44 +464,32 @@ __global__ __launch_bounds__(RENDER_BLOCK, 6) void grad_kernel(WorkArgs w, const
       geo.d = sd.d;
       geo.cx = sd.cx;
       geo.cy = sd.cy;
-      if (sd.rule == 0) {
-        const bool ser = U.s < S_SERIES;
-        switch (c.sie_mode) {
-          case 0: pixel_grad<0, 1>(c, U, sd.N, geo, acc); break;   // q = 1: s = 0
-          case 1:
-            if (ser) pixel_grad<1, 1>(c, U, sd.N, geo, acc);
-            else pixel_grad<1, 0>(c, U, sd.N, geo, acc);
-            break;
-          default:
-            if (ser) pixel_grad<2, 1>(c, U, sd.N, geo, acc);
-            else pixel_grad<2, 0>(c, U, sd.N, geo, acc);
-            break;
-        }
-      } else {
-        switch (c.sie_mode) {
-          case 0: pixel_grad_gk<0>(c, U, sd.rule, sd.N, geo, acc); break;
-          case 1: pixel_grad_gk<1>(c, U, sd.rule, sd.N, geo, acc); break;
-          default: pixel_grad_gk<2>(c, U, sd.rule, sd.N, geo, acc); break;
-        }
-      }
+      if (sd.rule == 0)
+        pixel_grad<false>(c.rmode, U, 0, sd.N, geo, acc);
+      else
+        pixel_grad<true>(c.rmode, U, sd.rule, sd.N, geo, acc);
       const float wgt = (float)sd.wgt * gp;
 #pragma unroll
       for (int k = 0; k < NPAR; ++k) acc[k] *= wgt;
     }
   }
-  // block sums of the 17 moments: the threads' float32 sums go to LDS, wave w
-  // adds moments w, w + 4, ... in float64 (four entries per lane, then a fixed
-  // shuffle tree; float64 holds the sum of 256 float32 values exactly enough
-  // that no cancellation is lost), stored as a float32 pair hi + lo
+  // block sums of the 17 moments: the threads' float32 sums go to LDS, 16 lanes
+  // add a moment's in float64 (16 entries each, then row rotations; float64 holds
+  // the sum of 256 float32 values exactly enough that no cancellation is lost),
+  // stored as a float32 pair hi + lo
 #pragma unroll
   for (int k = 0; k < NPAR; ++k) part[k][threadIdx.x] = acc[k];
   __syncthreads();
-  const int lane = threadIdx.x & 63, wid = threadIdx.x >> 6;
-  for (int k = wid; k < NPAR; k += RENDER_BLOCK / 64) {
-    double v = ((double)part[k][lane] + (double)part[k][lane + 64]) +
-               ((double)part[k][lane + 128] + (double)part[k][lane + 192]);
-    for (int off = 32; off > 0; off >>= 1) v += __shfl_down(v, off, 64);
-    if (lane == 0) {
+  const int j = (int)threadIdx.x & 15;
+  for (int k = (int)threadIdx.x >> 4; k < NPAR; k += RENDER_BLOCK / 16) {
+    double v0 = 0.0, v1 = 0.0;
+#pragma unroll
+    for (int i = 0; i < 16; i += 2) {
+      v0 += (double)part[k][16 * i + j];
+      v1 += (double)part[k][16 * i + 16 + j];
+    }
+    const double v = row_sum(v0 + v1);
+    if (j == 0) {
       const float hi = (float)v;
       gpart[(size_t)(base + tile) * NPAR + k] = make_float2(hi, (float)(v - (double)hi));
     }
@@ -524,7 +535,8 @@ __global__ __launch_bounds__(64 * GCUSP_WAVES) void grad_cusp_kernel(WorkArgs w,
   __shared__ unsigned short queue[GCUSP_WAVES][GCUSP_CHUNK * 64];   // lane | subsample << 6
   const int n = *cl.count;
   const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
-  const int wave = blockIdx.x * GCUSP_WAVES + wv;
+  // a scalar, so that an entry's point and its constants are read with uniform addresses
+  const int wave = uniform((int)blockIdx.x * GCUSP_WAVES + wv);
   unsigned short* __restrict__ qu = queue[wv];
   for (int i = wave; i < n; i += gridDim.x * GCUSP_WAVES) {
     const CuspEntry e = cl.entries[i];
@@ -565,33 +577,29 @@ __global__ __launch_bounds__(64 * GCUSP_WAVES) void grad_cusp_kernel(WorkArgs w,
           const int ky = (s0 + j) / N, kx = s0 + j - ky * N;
           const int qpix = unit_pixel(sd, e.unit0 + pl, e.ppt) + e.half;
           const PixelGeom gq = gcusp_geom(sd, qpix);
-          const float y = fmaf(gq.uy + (Rg ? Rg->x[ky] : sub_offset_rt(ky, N)), gq.d, gq.cy);
-          const float x = fmaf(gq.ux + (Rg ? Rg->x[kx] : sub_offset_rt(kx, N)), gq.d, gq.cx);
+          const float hN = 0.5f / (float)N;
+          const float y = fmaf(gq.uy + (Rg ? Rg->x[ky] : grad_offset(ky, N, hN)), gq.d, gq.cy);
+          const float x = fmaf(gq.ux + (Rg ? Rg->x[kx] : grad_offset(kx, N, hN)), gq.d, gq.cx);
           const double oy = Rg ? Rg->xd[ky] : ((double)ky + 0.5) / N - 0.5;
           const double ox = Rg ? Rg->xd[kx] : ((double)kx + 0.5) / N - 0.5;
           const float sw = Rg ? Rg->w[kx] * Rg->w[ky] : 1.0f;
           float dx, dy;
           source_offset_f64(p64s[e.point], gq, ox, oy, dx, dy);
-          float a64[NPAR], a32[NPAR];
+          float diff[NPAR];   // moments at the float32 offset minus those at the float64 one
 #pragma unroll
-          for (int k = 0; k < NPAR; ++k) a64[k] = a32[k] = 0.0f;
-          switch (c.sie_mode) {
-            case 0:
-              subsample_grad<0, true>(c, U, x, y, a32, false, 0.0f, 0.0f, sw);
-              subsample_grad<0, true>(c, U, x, y, a64, true, dx, dy, sw);
-              break;
-            case 1:
-              subsample_grad<1, true>(c, U, x, y, a32, false, 0.0f, 0.0f, sw);
-              subsample_grad<1, true>(c, U, x, y, a64, true, dx, dy, sw);
-              break;
-            default:
-              subsample_grad<2, true>(c, U, x, y, a32, false, 0.0f, 0.0f, sw);
-              subsample_grad<2, true>(c, U, x, y, a64, true, dx, dy, sw);
-              break;
-          }
-          const float wg = (float)sd.wgt * G[goff + qpix];
+          for (int k = 0; k < NPAR; ++k) diff[k] = 0.0f;
+          const float X = fmaf(U.s11, dx, U.s12 * dy), Y = fmaf(U.s21, dx, U.s22 * dy);
+          with_mode(c.rmode, U.series, [&](auto mode) {
+            using M = decltype(mode);
+            const GradRow row(U, y);
+            subsample_grad<M::RM, M::SER, true, true, false>(U, row, x, sw, diff, X, Y);
 #pragma unroll
-          for (int k = 0; k < NPAR; ++k) acc[k] = fmaf(a64[k] - a32[k], wg, acc[k]);
+            for (int k = 0; k < NPAR; ++k) diff[k] = -diff[k];
+            subsample_grad<M::RM, M::SER, true, false, false>(U, row, x, sw, diff);
+          });
+          const float wg = -(float)sd.wgt * G[goff + qpix];
+#pragma unroll
+          for (int k = 0; k < NPAR; ++k) acc[k] = fmaf(diff[k], wg, acc[k]);
         }
       }
       gcusp_lds_sync();
@@ -620,7 +628,7 @@ constexpr int FGRAD_THREADS = 256;
 // adds g_beta . d beta / d theta_k to the five lens entries.
 __global__ __launch_bounds__(FGRAD_THREADS) void finalize_grad_kernel(
     const float2* __restrict__ gpart, const int* __restrict__ gpbase, int ntiles, const double* __restrict__ corr,
-    const PointConst* __restrict__ pcs, const GradConst* __restrict__ gcs, float* __restrict__ grad, int point_base) {
+    const GradConst* __restrict__ gcs, float* __restrict__ grad, int point_base) {
   __shared__ double M[NPAR];
   const int p = point_base + (int)blockIdx.x;
   const int base = gpbase ? gpbase[p] : 0;
@@ -638,7 +646,7 @@ __global__ __launch_bounds__(FGRAD_THREADS) void finalize_grad_kernel(
   if (threadIdx.x != 0) return;
   double g[NPAR];
   const GradConst& gc = gcs[p];
-  grad_from_moments(M, pcs[p], gc, g);
+  grad_from_moments(M, gc, g);
   if (gc.srcpos) {
     const float* J = gc.src_jac;
     const double gx = g[10], gy = g[11];
@@ -877,13 +885,13 @@ hipError_t launch_grad(const WorkArgs& w, const PointConst* pcs, const PointCons
 }
 
 hipError_t launch_finalize_grad(const float2* gpart, const int* gpbase, int ntiles, int n_points, const double* corr,
-                                const PointConst* pcs, const GradConst* gcs, float* grad, hipStream_t st) {
+                                const GradConst* gcs, float* grad, hipStream_t st) {
   if (n_points <= 0) return hipSuccess;
   // at most 2^20 blocks per launch (the grid stays far below 2^32 work-items)
   for (int p0 = 0; p0 < n_points; p0 += 1 << 20) {
     const int np = n_points - p0 < (1 << 20) ? n_points - p0 : (1 << 20);
     hipLaunchKernelGGL(finalize_grad_kernel, dim3((unsigned)np), dim3(FGRAD_THREADS), 0, st, gpart, gpbase, ntiles,
-                       corr, pcs, gcs, grad, p0);
+                       corr, gcs, grad, p0);
     const hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
   }

@@ -61,17 +61,11 @@ __device__ __forceinline__ int render_variant(int row, int col) {
 // folded constants from rv. Invalid points carry NaN in the amplitudes and in
 // the lens matrix, which turns every result of that point into NaN.
 struct PointHead {
-  int sie_mode;        // 0: isothermal sphere (q = 1); 1: atanh by polynomial (q' <= 1/2); 2: atanh by log
-  float cL, sL;        // frame rotation of the SIE
-  float q2;            // q_L^2
-  float qp;            // q' = sqrt(1 - q_L^2)
-  float kc, ks;        // k cos(phi_L), k sin(phi_L), k = theta_E sqrt(q)/q' (mode 0: kc = theta_E)
-  float iq;            // 1/q_L
-  float m11, m12, m22; // beta = M x - alpha_SIE(x), M = 1 - shear matrix
-  // lens light: I = hI * exp2(hB (1 - t)), t = exp2(he * log2(hqa x'^2 + hqb y'^2))
-  float hc, hs, hqa, hqb, he, hB, hI;
-  // source: same, about (sx0, sy0)
-  float sx0, sy0, sc, ss, sqa, sqb, se, sB, sI;
+  float hI, sI;        // amplitudes I_e of the lens light and the source
+  // low parts of the two amplitudes (I_e - float(I_e)), non-zero only when I_e
+  // is derived in float64 from a magnitude: they keep the float32 rounding of
+  // the amplitude from scaling every pixel of a component the same way
+  float hIlo, sIlo;
   // source subsamples with R^2/R_e^2 below this are re-traced in float64 (0 = never)
   float cusp_r2;
   // rmode: 0 sphere, 1 polynomials (q' <= 1/2), 2 log + half-angle atan with
@@ -83,13 +77,9 @@ struct PointHead {
   // atanh (poly[6..10]); coefficient k is c_k q'^(2k+1). The leading q' is per
   // variant.
   float poly[11];
-  // low parts of the two amplitudes (I_e - float(I_e)), non-zero only when I_e
-  // is derived in float64 from a magnitude: they keep the float32 rounding of
-  // the amplitude from scaling every pixel of a component the same way
-  float hIlo, sIlo;
-  float pad[22];
+  float pad[15];
 };
-static_assert(sizeof(PointHead) == 64 * 4, "PointHead layout");
+static_assert(sizeof(PointHead) == 32 * 4, "PointHead layout");
 
 struct PointConst : PointHead {
   RenderVariant rv[RENDER_VARIANTS];
@@ -109,25 +99,36 @@ struct PointConst64 {
 };
 static_assert(sizeof(PointConst64) == 16 * 8, "PointConst64 layout");
 
-// Per-point values of the gradient's per-subsample arithmetic, derived in
-// float64 by the prologue and read with uniform addresses (scalar registers).
+// Per-point values of the gradient's per-subsample arithmetic, folded in
+// float64 by the prologue, rounded once and read with uniform addresses (scalar
+// registers). With (x', y') = R(-phi_L) (x, y), (u0, v0) = (x', y')/psi and
+// a = atan(q' u0)/q', b = atanh(q' v0)/q' (u0 and v0 for a sphere):
+//   source frame  X = A1 x + (B1 y + C1) + Xa a + Xb b,  Y the same with A2..Yb,
+//   lens light    X = h11 x + h12 y,  Y = h21 x + h22 y,
+// each with R^2/R_e^2 = X^2 + Y^2.
 struct GradUniform {
-  float tesq;          // theta_E sqrt(q)
-  float iqp;           // 1/q' (0 when q = 1)
-  float s;             // 1 - q^2
-  float hs;            // 1/(2 s) (0 when s = 0)
-  float iq2;           // 1/q^2
-  float bH, bS;        // natural-log Sersic constants b_n of the lens light and the source
-  float dbH, dbS;      // db_n/dn
-  float kS1, kS2;      // cos, sin (phi_S - phi_L): source-frame gradient into the SIE frame
+  float cL, sL, q2, qp;
+  float A1, A2, B1, B2, C1, C2;
+  float Xa, Xb, Ya, Yb;
+  float gXx, gYx, gXy, gYy;   // d(R^2/R_e^2)/d beta in the SIE frame: 2 (gXx X + gYx Y, gXy X + gYy Y)
+  float h11, h12, h21, h22;
+  float he, hB, se, sB;       // 1/(2n), b_n log2(e)
+  float s11, s12, s21, s22;   // source frame of an offset from the source centre
+  float kb, kc;               // modes 2, 3: b = sign(y') (kb log2((psi + q'|y'|)/r) + kc)
+  float s, hs2, iq2;          // 1 - q^2; 1/s (0 where the series in s is taken); 1/q^2
+  int series;                 // 1: d/ds of a and b by the series in s
+  // a = u0 P(u0^2) (mode 1) or w P(w^2), w = x'/(psi + r) (modes 2, 3); mode 1: b = v0 Q(v0^2)
+  float P[9], Q[6];
 };
+// 1 - q^2 below which d/ds of a and b takes the series.
+constexpr double GRAD_SERIES_S = 0.0625;
 
 // Extra per-point values needed by the adjoint.
 struct GradConst {
   float theta[NPAR];   // raw parameters
-  float dB_dn_h;       // d(b_n log2 e)/dn for the lens light
-  float dB_dn_s;       // same for the source
   float bh, bs;        // b_n of lens light and source
+  float dbh, dbs;      // db_n/dn
+  float Ih, Is;        // amplitudes I_e (NaN: an invalid point)
   // Magnitude parametrisation (amp != 0): theta[5] and theta[12] are total
   // magnitudes; I_e * d ln I_e / d(m, R_e, n) of the lens light [0..2] and of
   // the source [3..5], which carry d log L / d I_e over to the parameters.
@@ -140,9 +141,9 @@ struct GradConst {
   float src_jac[14];
   int srcpos;
   GradUniform u;
-  float pad[10];
+  float pad[16];
 };
-static_assert(sizeof(GradConst) == 64 * 4, "GradConst layout");
+static_assert(sizeof(GradConst) == 112 * 4, "GradConst layout");
 
 // Geometry and schedule of one system (one observation).
 struct SysDesc {

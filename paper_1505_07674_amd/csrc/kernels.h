@@ -193,6 +193,6 @@ hipError_t launch_grad(const WorkArgs& w, const PointConst* pcs, const PointCons
 // d log L / d I_e over to d/dm, d/dR_e and d/dn, with an image-plane source
 // position d/dbeta over to the image-plane point and the lens (gcs).
 hipError_t launch_finalize_grad(const float2* gpart, const int* gpbase, int ntiles, int n_points, const double* corr,
-                                const PointConst* pcs, const GradConst* gcs, float* grad, hipStream_t st);
+                                const GradConst* gcs, float* grad, hipStream_t st);
 
 }  // namespace lensed

@@ -571,7 +571,7 @@ hipError_t BatchPlan::enqueue(hipStream_t st, hipEvent_t* ev) const {
       if ((e = launch_grad(wg, d_pc_, d_p64_, d_gc_, d_L_, d_gpbase_, d_gpart_, n_gitems_, cusp_, d_gcorr_, st,
                            ev ? ev[7] : nullptr)) != hipSuccess)
         return e;
-      if ((e = launch_finalize_grad(d_gpart_, d_gpbase_, grad_ntiles_, n_points_, d_gcorr_, d_pc_, d_gc_, grad_,
+      if ((e = launch_finalize_grad(d_gpart_, d_gpbase_, grad_ntiles_, n_points_, d_gcorr_, d_gc_, grad_,
                                     st)) != hipSuccess)
         return e;
     }

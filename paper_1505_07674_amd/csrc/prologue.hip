@@ -312,7 +312,7 @@ inline int system_blocks(bool adj, int n_sys, int support) { return n_sys * (adj
 // Lanes of a point, and what they pass to each other.
 constexpr int PROLOGUE_LANES = 32;
 constexpr int PROLOGUE_POINTS = PROLOGUE_THREADS / PROLOGUE_LANES;
-enum Trig { T_L, T_SHEAR, T_H, T_S, T_SL, N_TRIG };   // phi_L, 2 phi_gamma, phi of the lights, phi_S - phi_L
+enum Trig { T_L, T_SHEAR, T_H, T_S, N_TRIG };   // phi_L, 2 phi_gamma, phi of the lights
 enum Comp { C_H, C_S, C_SIE, N_COMP };
 struct PointScratch {
   double2 cs[N_TRIG];          // (cos, sin)
@@ -365,7 +365,7 @@ __global__ __launch_bounds__(PROLOGUE_THREADS) void prologue_kernel(
   // lane j: angle j; light j (0 lens, 1 source) and SIE (2)
   {
     const double arg = j == T_L ? phL : j == T_SHEAR ? 2.0 * (double)t[4] : j == T_H ? (double)t[9]
-                     : j == T_S ? (double)t[16] : j == T_SL ? (double)t[16] - phL : 0.0;
+                     : j == T_S ? (double)t[16] : 0.0;
     double sn, cn;
     sincos(arg, &sn, &cn);
     if (j < N_TRIG) s.cs[j] = make_double2(cn, sn);
@@ -406,46 +406,16 @@ __global__ __launch_bounds__(PROLOGUE_THREADS) void prologue_kernel(
     PointHead c;
     const double cL = s.cs[T_L].x, sL = s.cs[T_L].y;
     const double k = s2 == 0.0 ? te : s.comp[C_SIE][0];
-    c.cL = (float)cL;
-    c.sL = (float)sL;
-    c.q2 = (float)(q * q);
-    c.qp = (float)qp;
-    c.iq = (float)s.comp[C_SIE][1];
-    if (s2 == 0.0) {
-      c.sie_mode = 0;
-      c.kc = (float)te;
-      c.ks = 0.0f;
-    } else {
-      c.sie_mode = qp <= 0.5 ? 1 : 2;
-      c.kc = (float)(k * cL);
-      c.ks = (float)(k * sL);
-    }
     const double g1 = g * s.cs[T_SHEAR].x, g2 = g * s.cs[T_SHEAR].y;
-    c.m11 = (float)(1.0 - g1);
-    c.m12 = (float)(-g2);
-    c.m22 = (float)(1.0 + g1);
-
     const double bh = s.bn[C_H].b, bs = s.bn[C_S].b;
     // amplitudes: I_e given, or from total magnitudes
     const double Ih = valid && amp ? s.amp[C_H].I : (double)t[5], Is = valid && amp ? s.amp[C_S].I : (double)t[12];
     // source centre: given, or the image of an image-plane point (Sec. 5)
     const double xs = valid && srcpos ? s.maps[14].x : (double)t[10], ys = valid && srcpos ? s.maps[14].y : (double)t[11];
-    c.hc = (float)s.cs[T_H].x;
-    c.hs = (float)s.cs[T_H].y;
-    c.hqa = (float)s.comp[C_H][2];
-    c.hqb = (float)s.comp[C_H][3];
-    c.he = (float)s.comp[C_H][4];
-    c.hB = (float)(bh * LOG2E);
     c.hI = (float)Ih;
-    c.sx0 = (float)xs;
-    c.sy0 = (float)ys;
-    c.sc = (float)s.cs[T_S].x;
-    c.ss = (float)s.cs[T_S].y;
-    c.sqa = (float)s.comp[C_S][2];
-    c.sqb = (float)s.comp[C_S][3];
-    c.se = (float)s.comp[C_S][4];
-    c.sB = (float)(bs * LOG2E);
     c.sI = (float)Is;
+    c.hIlo = (float)(Ih - (double)c.hI);
+    c.sIlo = (float)(Is - (double)c.sI);
     // re-trace in float64 near a cuspy (n > 1) source centre (source-plane radius)
     {
       const double Re = t[13], rc = (srcpos ? CUSP_RADIUS_IMAGE_PLANE_ARCSEC : CUSP_RADIUS_ARCSEC) / Re;
@@ -485,9 +455,11 @@ __global__ __launch_bounds__(PROLOGUE_THREADS) void prologue_kernel(
     f[3] = s.comp[C_SIE][1];
     f[4] = qp;
     const double m11 = 1.0 - g1, m12 = -g2, m22 = 1.0 + g1;
+    const double s11 = s.comp[C_S][0] * s.cs[T_S].x, s12 = s.comp[C_S][0] * s.cs[T_S].y;
+    const double s21 = -s.comp[C_S][1] * s.cs[T_S].y, s22 = s.comp[C_S][1] * s.cs[T_S].x;
+    const double h11 = s.comp[C_H][0] * s.cs[T_H].x, h12 = s.comp[C_H][0] * s.cs[T_H].y;
+    const double h21 = -s.comp[C_H][1] * s.cs[T_H].y, h22 = s.comp[C_H][1] * s.cs[T_H].x;
     {
-      const double a = s.comp[C_S][0], b = s.comp[C_S][1], cs = s.cs[T_S].x, sn = s.cs[T_S].y;
-      const double s11 = a * cs, s12 = a * sn, s21 = -b * sn, s22 = b * cs;
       // the source frame of the lens equation in one step (float64 products, one rounding each)
       f[5] = s11 * m11 + s12 * m12;            // A1
       f[6] = s21 * m11 + s22 * m12;            // A2
@@ -504,14 +476,10 @@ __global__ __launch_bounds__(PROLOGUE_THREADS) void prologue_kernel(
       f[25] = s21;
       f[26] = s22;
     }
-    {
-      // lens light about the origin: R^2/R_e^2 = X^2 + Y^2 = (ha x + hb y) x + hc y^2
-      const double a = s.comp[C_H][0], b = s.comp[C_H][1], cs = s.cs[T_H].x, sn = s.cs[T_H].y;
-      const double h11 = a * cs, h12 = a * sn, h21 = -b * sn, h22 = b * cs;
-      f[15] = h11 * h11 + h21 * h21;           // ha
-      f[16] = 2.0 * (h11 * h12 + h21 * h22);   // hb
-      f[17] = h12 * h12 + h22 * h22;           // hc
-    }
+    // lens light about the origin: R^2/R_e^2 = X^2 + Y^2 = (ha x + hb y) x + hc y^2
+    f[15] = h11 * h11 + h21 * h21;             // ha
+    f[16] = 2.0 * (h11 * h12 + h21 * h22);     // hb
+    f[17] = h12 * h12 + h22 * h22;             // hc
     f[18] = s.comp[C_H][4];                    // he
     f[19] = bh * LOG2E;                        // hB
     f[20] = s.comp[C_S][4];                    // se
@@ -519,14 +487,8 @@ __global__ __launch_bounds__(PROLOGUE_THREADS) void prologue_kernel(
     f[22] = tac;
     if (!valid) f[5] = f[6] = __builtin_nan("");
     for (int i = 0; i < 32; ++i) s.folded[i] = f[i];
-    c.hIlo = (float)(Ih - (double)c.hI);
-    c.sIlo = (float)(Is - (double)c.sI);
-    for (int i = 0; i < 22; ++i) c.pad[i] = 0.0f;
-    if (!valid) {
-      const float nan = __builtin_nanf("");
-      c.m11 = c.m12 = c.m22 = nan;
-      c.hI = c.sI = nan;
-    }
+    for (float& v : c.pad) v = 0.0f;
+    if (!valid) c.hI = c.sI = __builtin_nanf("");
     static_cast<PointHead&>(pcs[p]) = c;
     if (p64s) {
       PointConst64 e;
@@ -551,11 +513,12 @@ __global__ __launch_bounds__(PROLOGUE_THREADS) void prologue_kernel(
     if (ADJ && gcs) {
       GradConst gc;
       for (int i = 0; i < NPAR; ++i) gc.theta[i] = t[i];
-      const double dbh = s.bn[C_H].db, dbs = s.bn[C_S].db;
       gc.bh = (float)bh;
       gc.bs = (float)bs;
-      gc.dB_dn_h = valid ? (float)(dbh * LOG2E) : __builtin_nanf("");
-      gc.dB_dn_s = valid ? (float)(dbs * LOG2E) : __builtin_nanf("");
+      gc.dbh = (float)s.bn[C_H].db;
+      gc.dbs = (float)s.bn[C_S].db;
+      gc.Ih = c.hI;
+      gc.Is = c.sI;
       gc.amp_chain[0] = (float)s.amp[C_H].dm;
       gc.amp_chain[1] = (float)s.amp[C_H].dR;
       gc.amp_chain[2] = (float)s.amp[C_H].dn;
@@ -566,18 +529,53 @@ __global__ __launch_bounds__(PROLOGUE_THREADS) void prologue_kernel(
       for (int i = 0; i < 14; ++i) gc.src_jac[i] = s.jac[i];
       gc.srcpos = srcpos;
       GradUniform& u = gc.u;
-      u.tesq = (float)(te * s.comp[C_SIE][5]);
-      u.iqp = s2 == 0.0 ? 0.0f : (float)s.comp[C_SIE][3];
+      const double tesq = te * s.comp[C_SIE][5], qp2 = qp * qp;
+      u.cL = (float)cL;
+      u.sL = (float)sL;
+      u.q2 = (float)(q * q);
+      u.qp = (float)qp;
+      u.A1 = (float)f[5];
+      u.A2 = (float)f[6];
+      u.B1 = (float)f[7];
+      u.B2 = (float)f[8];
+      u.C1 = (float)f[9];
+      u.C2 = (float)f[10];
+      // S R(phi_L): the SIE frame into the source frame
+      u.gXx = (float)(s11 * cL + s12 * sL);
+      u.gXy = (float)(s12 * cL - s11 * sL);
+      u.gYx = (float)(s21 * cL + s22 * sL);
+      u.gYy = (float)(s22 * cL - s21 * sL);
+      u.Xa = (float)(-tesq * (s11 * cL + s12 * sL));
+      u.Xb = (float)(-tesq * (s12 * cL - s11 * sL));
+      u.Ya = (float)(-tesq * (s21 * cL + s22 * sL));
+      u.Yb = (float)(-tesq * (s22 * cL - s21 * sL));
+      u.h11 = valid ? (float)h11 : __builtin_nanf("");
+      u.h12 = (float)h12;
+      u.h21 = (float)h21;
+      u.h22 = (float)h22;
+      u.he = (float)s.comp[C_H][4];
+      u.hB = (float)(bh * LOG2E);
+      u.se = (float)s.comp[C_S][4];
+      u.sB = (float)(bs * LOG2E);
+      u.s11 = (float)s11;
+      u.s12 = (float)s12;
+      u.s21 = (float)s21;
+      u.s22 = (float)s22;
+      u.series = s2 < GRAD_SERIES_S;
       u.s = (float)s2;
-      u.hs = s2 == 0.0 ? 0.0f : (float)s.comp[C_SIE][4];
+      u.hs2 = u.series ? 0.0f : (float)(2.0 * s.comp[C_SIE][4]);
       u.iq2 = (float)s.comp[C_SIE][2];
-      u.bH = (float)bh;
-      u.bS = (float)bs;
-      u.dbH = (float)dbh;
-      u.dbS = (float)dbs;
-      u.kS1 = (float)s.cs[T_SL].x;
-      u.kS2 = (float)s.cs[T_SL].y;
-      for (int i = 0; i < 10; ++i) gc.pad[i] = 0.0f;
+      const bool log_form = c.rmode >= 2;
+      u.kb = log_form ? (float)(0.693147180559945309417 * s.comp[C_SIE][3]) : 0.0f;
+      u.kc = log_form ? (float)(-log(q) * s.comp[C_SIE][3]) : 0.0f;
+      double pw = log_form ? 2.0 : 1.0;
+      for (int i = 0; i <= 8; ++i, pw *= qp2)
+        u.P[i] = c.rmode == 3                       ? (float)(ATAN_UNIT_POLY_D[i] * pw)
+                 : i <= ATAN_SMALL_POLY_DEGREE ? (float)(ATAN_SMALL_POLY_D[i <= ATAN_SMALL_POLY_DEGREE ? i : 0] * pw)
+                                               : 0.0f;
+      pw = 1.0;
+      for (int i = 0; i <= ATANH_POLY_DEGREE; ++i, pw *= qp2) u.Q[i] = (float)(ATANH_POLY_D[i] * pw);
+      for (float& v : gc.pad) v = 0.0f;
       gcs[p] = gc;
     }
   }

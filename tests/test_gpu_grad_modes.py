@@ -1,0 +1,55 @@
+"""The gradient's arithmetic on both sides of every per-point choice it makes: sphere,
+series in 1 - q^2, polynomials, logarithm with the short and the long arctangent; one to
+several subsamples per row and a Gauss-Kronrod rule; Sersic indices from flat to cuspy;
+a light centre exactly on a subsample. Against the oracle's exact gradient, 1e-4 of the
+norm (test_gpu_grad.py)."""
+import math
+
+import numpy as np
+import pytest
+import torch
+
+import paper_1505_07674_amd as lensed
+from paper_1505_07674_amd import mocks
+
+from helpers import f32
+from test_gpu_grad import check, oracle_grads, small_obs, small_spec
+import oracle
+
+pytestmark = pytest.mark.gpu
+DEV = torch.device("cuda:0")
+SERIES = math.sqrt(1 - 0.0625)      # 1 - q^2 at the end of the series
+POLY = math.sqrt(1 - 0.25)          # q' = 1/2
+QS = [1.0, 1 - 1e-6, SERIES * (1 + 1e-6), SERIES * (1 - 1e-6), POLY * (1 + 1e-6), POLY * (1 - 1e-6), 0.5 + 1e-6,
+      0.5 - 1e-6, 0.2]
+NS = [0.2, 0.5, 1.0, 1.5, 4.0, 6.0, 3.0, 0.8, 2.5]
+
+
+def edge_points(spec, seed):
+    pts = mocks.points(spec, len(QS), seed=seed).astype(np.float32)
+    pts[:, 1] = QS
+    pts[:, 7], pts[:, 14] = NS, NS[::-1]
+    return pts
+
+
+@pytest.mark.parametrize("N", [1, 2, 5])
+def test_modes_midpoint(N):
+    spec = small_spec(H=41, W=39, N=N, center=(0.0, 0.0))   # a pixel's centre on the lens light's
+    check(spec, small_obs(spec), edge_points(spec, 70 + N), loglike_bar=False)
+
+
+def test_modes_gauss_kronrod():
+    spec = small_spec(H=31, W=30)
+    t = lambda a: torch.from_numpy(np.ascontiguousarray(a, np.float32)).to(DEV)
+    obs = small_obs(spec)
+    gsys = lensed.System(t(spec.psf), t(obs.data), t(obs.weight), pixscale=spec.pixscale, rule="g3k7",
+                         center=(spec.center_x, spec.center_y))
+    osys = oracle.System(spec.height, spec.width, f32(spec.pixscale), 1, spec.psf.astype(np.float64),
+                         obs.data.astype(np.float64), obs.weight.astype(np.float64), center_x=f32(spec.center_x),
+                         center_y=f32(spec.center_y), rule="g3k7")
+    pts = edge_points(spec, 77)
+    _, g = lensed.loglike_grad(t(pts), gsys)
+    _, want = oracle_grads(osys, pts)
+    rel = np.linalg.norm(g.cpu().numpy().astype(np.float64) - want, axis=1) / np.linalg.norm(want, axis=1)
+    print(rel, flush=True)
+    assert np.all(rel <= 1e-4)
