@@ -408,13 +408,21 @@ __device__ __forceinline__ void pixel_grad(int rmode, const GradUniform& U, int 
 
 // Sum over the 16 lanes of a row (row rotations), in each of them.
 template <int R>
+__device__ __forceinline__ float add_rotated(float v) {
+  return v + __builtin_bit_cast(float, __builtin_amdgcn_mov_dpp(__builtin_bit_cast(int, v), 0x120 + R, 0xf, 0xf, true));
+}
+template <int R>
 __device__ __forceinline__ double add_rotated(double v) {
   const int lo = __builtin_amdgcn_mov_dpp(__double2loint(v), 0x120 + R, 0xf, 0xf, true);
   const int hi = __builtin_amdgcn_mov_dpp(__double2hiint(v), 0x120 + R, 0xf, 0xf, true);
   return v + __hiloint2double(hi, lo);
 }
-__device__ __forceinline__ double row_sum(double v) {
+template <class T>
+__device__ __forceinline__ T row_sum(T v) {
   return add_rotated<1>(add_rotated<2>(add_rotated<4>(add_rotated<8>(v))));
+}
+__device__ __forceinline__ float lane_value(float v, int lane) {
+  return __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, v), lane));
 }
 
 // One thread per pixel, one block per (point, render tile): sums
@@ -504,9 +512,14 @@ __global__ __launch_bounds__(RENDER_BLOCK, 6) void grad_kernel(WorkArgs w, const
 constexpr int GCUSP_WAVES = 4;
 constexpr int GCUSP_BLOCKS = 1024;
 
-// The subsamples inside the radius are first found in float32 and queued per
-// wave in LDS, then each lane takes one queued subsample at a time, so the
-// float64 re-tracing and the two sets of partials run with every lane busy.
+// As in the forward correction, the entry's flagged pixels go to LDS, the (pixel,
+// subsample) pairs inside the radius are found 64 at a time in float32 and queued,
+// and the queue is re-traced 64 at a time, so that every stage runs with every lane
+// busy. What bounds it: at few points the latency of one entry's chain, at many the
+// registers of the moments (four waves per SIMD). 1024 points of 200 x 200 pixels,
+// N = 4: 93 -> 24 us (32 us at three waves); 16 points of 87 x 101, N = 3: 16.4 -> 7.5 us.
+// (Each lane testing its own pixel's subsamples one after another, with few of the 64
+// pixels flagged, took 73 us with the same re-tracing.)
 constexpr int GCUSP_CHUNK = 16;   // subsamples per pass
 
 __device__ __forceinline__ void gcusp_lds_sync() {
@@ -527,31 +540,32 @@ __device__ __forceinline__ PixelGeom gcusp_geom(const SysDesc& sd, int pix) {
   return geo;
 }
 
-__global__ __launch_bounds__(64 * GCUSP_WAVES) void grad_cusp_kernel(WorkArgs w, const PointConst* __restrict__ pcs,
+__global__ __launch_bounds__(64 * GCUSP_WAVES, 4) void grad_cusp_kernel(WorkArgs w, const PointConst* __restrict__ pcs,
                                                                      const PointConst64* __restrict__ p64s,
                                                                      const GradConst* __restrict__ gcs,
                                                                      const float* __restrict__ G, CuspList cl,
                                                                      double* __restrict__ corr) {
-  __shared__ unsigned short queue[GCUSP_WAVES][GCUSP_CHUNK * 64];   // lane | subsample << 6
+  __shared__ unsigned short queue[GCUSP_WAVES][GCUSP_CHUNK * 64];   // flagged pixel | subsample << 6
+  __shared__ int fpix[GCUSP_WAVES][64];                             // the entry's flagged pixels
   const int n = *cl.count;
   const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
   // a scalar, so that an entry's point and its constants are read with uniform addresses
   const int wave = uniform((int)blockIdx.x * GCUSP_WAVES + wv);
   unsigned short* __restrict__ qu = queue[wv];
+  int* __restrict__ fp = fpix[wv];
   for (int i = wave; i < n; i += gridDim.x * GCUSP_WAVES) {
     const CuspEntry e = cl.entries[i];
     const bool mine = (e.mask >> lane) & 1ull;
-    const SysDesc sd = w.sys_table ? w.sys_table[w.point_sys ? w.point_sys[e.point] : 0] : w.single;
-    const int64_t loff = w.point_loff ? w.point_loff[e.point] : 0;
-    const int64_t goff = w.point_goff ? w.point_goff[e.point] : loff;   // the composite model's g
-    const PointConst& c = pcs[e.point];
-    const GradConst& gc = gcs[e.point];
+    const int F = __popcll(e.mask);
+    const int point = uniform(e.point);
+    const SysDesc& sd = w.sys_table ? w.sys_table[w.point_sys ? w.point_sys[point] : 0] : w.single;
+    const int64_t loff = w.point_loff ? w.point_loff[point] : 0;
+    const int64_t goff = w.point_goff ? w.point_goff[point] : loff;   // the composite model's g
+    const PointConst& c = pcs[point];
+    const GradConst& gc = gcs[point];
     const GradUniform& U = gc.u;
-    const int lpix = mine ? unit_pixel(sd, e.unit0 + lane, e.ppt) + e.half : 0;   // this lane's pixel
-    const PixelGeom geo = gcusp_geom(sd, lpix);
-    // the render constants the forward render used for this lane's pixel
-    const int prow = row_of(sd, lpix);
-    const RenderVariant& kv = c.rv[render_variant(prow, lpix - prow * sd.W)];
+    if (mine) fp[__popcll(e.mask & ((1ull << lane) - 1ull))] = unit_pixel(sd, e.unit0 + lane, e.ppt) + e.half;
+    gcusp_lds_sync();
     const int N = sd.N, NN = N * N;
     const GkRule* Rg = sd.rule > 0 ? &kGkRules[sd.rule - 1] : nullptr;
     float acc[NPAR];
@@ -560,22 +574,32 @@ __global__ __launch_bounds__(64 * GCUSP_WAVES) void grad_cusp_kernel(WorkArgs w,
     for (int s0 = 0; s0 < NN; s0 += GCUSP_CHUNK) {
       const int ns = min(GCUSP_CHUNK, NN - s0);
       int qn = 0;
-      for (int j = 0; j < ns; ++j) {
-        const int ky = (s0 + j) / N, kx = s0 + j - ky * N;
-        const float y = fmaf(geo.uy + (Rg ? Rg->x[ky] : sub_offset_rt(ky, N)), geo.d, geo.cy);
-        const float x = fmaf(geo.ux + (Rg ? Rg->x[kx] : sub_offset_rt(kx, N)), geo.d, geo.cx);
-        const bool within = mine && render_source_R2(c, kv, x, y) < c.cusp_r2;
-        const unsigned long long b = __ballot(within);
-        if (within) qu[qn + __popcll(b & ((1ull << lane) - 1ull))] = (unsigned short)(lane | (j << 6));
-        qn += __popcll(b);
+      for (int b = 0; b < F * ns; b += 64) {
+        const int item = b + lane;
+        bool within = false;
+        int f = 0, j = 0;
+        if (item < F * ns) {
+          f = item / ns;
+          j = item - f * ns;
+          const int ky = (s0 + j) / N, kx = s0 + j - ky * N;
+          const PixelGeom geo = gcusp_geom(sd, fp[f]);
+          const int prow = row_of(sd, fp[f]);
+          const float y = fmaf(geo.uy + (Rg ? Rg->x[ky] : sub_offset_rt(ky, N)), geo.d, geo.cy);
+          const float x = fmaf(geo.ux + (Rg ? Rg->x[kx] : sub_offset_rt(kx, N)), geo.d, geo.cx);
+          // with the render constants the forward render used for the pixel
+          within = render_source_R2(c, c.rv[render_variant(prow, fp[f] - prow * sd.W)], x, y) < c.cusp_r2;
+        }
+        const unsigned long long bal = __ballot(within);
+        if (within) qu[qn + __popcll(bal & ((1ull << lane) - 1ull))] = (unsigned short)(f | (j << 6));
+        qn += __popcll(bal);
       }
       gcusp_lds_sync();
       for (int q0 = 0; q0 < qn; q0 += 64) {
         if (q0 + lane < qn) {
           const int item = qu[q0 + lane];
-          const int pl = item & 63, j = item >> 6;
+          const int j = item >> 6;
           const int ky = (s0 + j) / N, kx = s0 + j - ky * N;
-          const int qpix = unit_pixel(sd, e.unit0 + pl, e.ppt) + e.half;
+          const int qpix = fp[item & 63];
           const PixelGeom gq = gcusp_geom(sd, qpix);
           const float hN = 0.5f / (float)N;
           const float y = fmaf(gq.uy + (Rg ? Rg->x[ky] : grad_offset(ky, N, hN)), gq.d, gq.cy);
@@ -584,7 +608,7 @@ __global__ __launch_bounds__(64 * GCUSP_WAVES) void grad_cusp_kernel(WorkArgs w,
           const double ox = Rg ? Rg->xd[kx] : ((double)kx + 0.5) / N - 0.5;
           const float sw = Rg ? Rg->w[kx] * Rg->w[ky] : 1.0f;
           float dx, dy;
-          source_offset_f64(p64s[e.point], gq, ox, oy, dx, dy);
+          source_offset_f64(p64s[point], gq, ox, oy, dx, dy);
           float diff[NPAR];   // moments at the float32 offset minus those at the float64 one
 #pragma unroll
           for (int k = 0; k < NPAR; ++k) diff[k] = 0.0f;
@@ -604,13 +628,16 @@ __global__ __launch_bounds__(64 * GCUSP_WAVES) void grad_cusp_kernel(WorkArgs w,
       }
       gcusp_lds_sync();
     }
-    // every lane of an entry belongs to the same point
+    // every lane of an entry belongs to the same point; a lane per moment adds its sum
+    float mine_sum = 0.0f;
 #pragma unroll
     for (int k = 0; k < NPAR; ++k) {
-      float v = acc[k];
-      for (int off = 32; off > 0; off >>= 1) v += __shfl_down(v, off, 64);
-      if (lane == 0 && v != 0.0f) atomicAdd(&corr[(size_t)e.point * NPAR + k], (double)v);
+      const float v = row_sum(acc[k]);
+      const float sum = (lane_value(v, 0) + lane_value(v, 16)) + (lane_value(v, 32) + lane_value(v, 48));
+      mine_sum = lane == k ? sum : mine_sum;
     }
+    if (lane < NPAR && mine_sum != 0.0f) atomicAdd(&corr[(size_t)point * NPAR + lane], (double)mine_sum);
+    gcusp_lds_sync();   // the queue and the pixel list are written anew
   }
 }
 

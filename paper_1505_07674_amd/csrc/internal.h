@@ -90,10 +90,11 @@ static_assert(sizeof(PointConst) == sizeof(PointHead) + RENDER_VARIANTS * sizeof
 // to the centre of a cuspy (n > 1) source, where the float32 rounding of the
 // ray position (~1e-7 arcsec) is amplified by the steep profile.
 struct PointConst64 {
-  double cL, sL, q2, qp, k, te;   // SIE frame, k = theta_E sqrt(q)/q'
+  double cL, sL, q2, qp, s2;      // SIE frame; q^2, q' and 1 - q^2
+  double f;                       // deflection factor of sie_ab: theta_E sqrt(q)/q' closed, else theta_E sqrt(q)
   double m11, m12, m22;           // 1 - shear matrix
   double sx0, sy0;                // source centre
-  int mode;                       // 0: isothermal sphere
+  int closed;                     // sie_ab's form
   int pad0;
   double pad[4];
 };

@@ -38,8 +38,5 @@ struct ModelConst {
   int n_sie, n_sersic;
   int plane[MAX_SERSIC];       // the Sersic's plane: 0 light at x, n_planes light at the source
 };
-// 1 - q^2 below which a lens is nearly round: u and v stay within 1/q, so the
-// arguments (1 - q^2) u^2 of the series stay below 0.053.
-constexpr double SIE_SERIES_S = 0.05;
 
 }  // namespace lensed

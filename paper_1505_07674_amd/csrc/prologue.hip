@@ -19,6 +19,7 @@
 #include "bn_poly.h"
 #include "internal.h"
 #include "kernels.h"
+#include "sie64.h"
 #include "sie_poly.h"
 #include "support.h"
 
@@ -496,9 +497,9 @@ __global__ __launch_bounds__(PROLOGUE_THREADS) void prologue_kernel(
       e.sL = sL;
       e.q2 = q * q;
       e.qp = qp;
-      e.te = te;
-      e.k = k;
-      e.mode = s2 == 0.0 ? 0 : 1;
+      e.s2 = s2;
+      e.closed = s2 >= SIE_SERIES_S;
+      e.f = e.closed ? k : te * s.comp[C_SIE][5];
       e.pad0 = 0;
       e.m11 = m11;
       e.m12 = m12;

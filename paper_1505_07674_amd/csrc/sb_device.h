@@ -21,6 +21,7 @@
 
 #include "gk_rules.h"
 #include "internal.h"
+#include "sie64.h"
 #include "sie_poly.h"
 
 namespace lensed {
@@ -64,22 +65,9 @@ __device__ __forceinline__ void source_offset_f64(const PointConst64& e, const P
                                                   float& dx, float& dy) {
   const double x = (double)g.cx + ((double)g.ux + ox) * (double)g.d;
   const double y = (double)g.cy + ((double)g.uy + oy) * (double)g.d;
-  double ax = 0.0, ay = 0.0;
-  if (e.mode == 0) {
-    const double r = sqrt(x * x + y * y);
-    if (r > 0.0) {
-      ax = e.te * x / r;
-      ay = e.te * y / r;
-    }
-  } else {
-    const double xp = e.cL * x + e.sL * y, yp = -e.sL * x + e.cL * y;
-    const double psi = sqrt(e.q2 * xp * xp + yp * yp);
-    if (psi > 0.0) {
-      const double a1 = e.k * atan(e.qp * xp / psi), a2 = e.k * atanh(e.qp * yp / psi);
-      ax = e.cL * a1 - e.sL * a2;
-      ay = e.sL * a1 + e.cL * a2;
-    }
-  }
+  const double xp = e.cL * x + e.sL * y, yp = e.cL * y - e.sL * x;
+  const SieAB o = e.closed ? sie_ab<true>(e.q2, e.qp, e.s2, xp, yp) : sie_ab<false>(e.q2, e.qp, e.s2, xp, yp);
+  const double ax = e.f * (e.cL * o.a - e.sL * o.b), ay = e.f * (e.sL * o.a + e.cL * o.b);
   dx = (float)(e.m11 * x + e.m12 * y - ax - e.sx0);
   dy = (float)(e.m12 * x + e.m22 * y - ay - e.sy0);
 }
