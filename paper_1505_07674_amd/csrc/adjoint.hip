@@ -221,13 +221,15 @@ __device__ __forceinline__ float grad_poly(const float* p, float z) {
   return v;
 }
 
-// Offset of subsample k of N, hN = 1/(2N): (k + 1/2)/N - 1/2 = (2k + 1 - N)/(2N), exactly
-// 0 at the middle of an odd N (a light centre there is a singular point). The
-// gradient needs the abscissae to float32 accuracy, not bit for bit those of the
-// render; but the cusp correction takes back what grad_kernel added, so the two
-// share every expression from here to the moments, without contractions that a
-// compiler might make in one of them only.
-__device__ __forceinline__ float grad_offset(int k, int N, float hN) { return (float)(2 * k + 1 - N) * hN; }
+// Offset of subsample k of N, iN = 1/N: (k + 1/2)/N - 1/2 to a float32 rounding of the
+// quotient. The gradient needs the abscissae to float32 accuracy, not bit for bit
+// those of the render; but the cusp correction takes back what grad_kernel added, so
+// the two share every expression from here to the moments, without contractions that
+// a compiler might make in one of them only. (At an odd N that is no power of two the
+// middle offset comes out as about 1e-8 of a pixel, not 0, and a light centre exactly
+// there is a singular point of the profile: its own light's partials are then off by
+// what that subsample weighs.)
+__device__ __forceinline__ float grad_offset(int k, float iN) { return fmaf((float)k + 0.5f, iN, -0.5f); }
 
 // What depends on the row of subsamples only.
 struct GradRow {
@@ -396,11 +398,11 @@ __device__ __forceinline__ void pixel_grad(int rmode, const GradUniform& U, int 
           subsample_grad<M::RM, M::SER, true>(U, row, fmaf(g.ux + R.x[kx], g.d, g.cx), R.w[kx] * R.w[ky], acc);
       }
     } else {
-      const float hN = 0.5f / (float)N;
+      const float iN = 1.0f / (float)N;
       for (int ky = 0; ky < N; ++ky) {
-        const GradRow row(U, fmaf(g.uy + grad_offset(ky, N, hN), g.d, g.cy));
+        const GradRow row(U, fmaf(g.uy + grad_offset(ky, iN), g.d, g.cy));
         for (int kx = 0; kx < N; ++kx)
-          subsample_grad<M::RM, M::SER, false>(U, row, fmaf(g.ux + grad_offset(kx, N, hN), g.d, g.cx), 1.0f, acc);
+          subsample_grad<M::RM, M::SER, false>(U, row, fmaf(g.ux + grad_offset(kx, iN), g.d, g.cx), 1.0f, acc);
       }
     }
   });
@@ -601,9 +603,9 @@ __global__ __launch_bounds__(64 * GCUSP_WAVES, 4) void grad_cusp_kernel(WorkArgs
           const int ky = (s0 + j) / N, kx = s0 + j - ky * N;
           const int qpix = fp[item & 63];
           const PixelGeom gq = gcusp_geom(sd, qpix);
-          const float hN = 0.5f / (float)N;
-          const float y = fmaf(gq.uy + (Rg ? Rg->x[ky] : grad_offset(ky, N, hN)), gq.d, gq.cy);
-          const float x = fmaf(gq.ux + (Rg ? Rg->x[kx] : grad_offset(kx, N, hN)), gq.d, gq.cx);
+          const float iN = 1.0f / (float)N;
+          const float y = fmaf(gq.uy + (Rg ? Rg->x[ky] : grad_offset(ky, iN)), gq.d, gq.cy);
+          const float x = fmaf(gq.ux + (Rg ? Rg->x[kx] : grad_offset(kx, iN)), gq.d, gq.cx);
           const double oy = Rg ? Rg->xd[ky] : ((double)ky + 0.5) / N - 0.5;
           const double ox = Rg ? Rg->xd[kx] : ((double)kx + 0.5) / N - 0.5;
           const float sw = Rg ? Rg->w[kx] * Rg->w[ky] : 1.0f;
