@@ -278,7 +278,7 @@ int lensed_render(lensed_ctx* c, const lensed_system* sys, const float* theta, f
   const size_t off_p64 = align_up(off_pc + sizeof(PointConst), 256);
   const size_t off_psf = align_up(off_p64 + sizeof(PointConst64), 256);
   const size_t off_cc = align_up(off_psf + 3 * sizeof(float) * sd.ph * sd.pw, 256);
-  const size_t off_ce = align_up(off_cc + sizeof(int), 256);
+  const size_t off_ce = align_up(off_cc + 2 * sizeof(int), 256);
   const size_t off_L = align_up(off_ce + sizeof(CuspEntry) * (size_t)sd.n_rtiles * (RENDER_BLOCK / 64), 256);
   const size_t total = align_up(off_L + sizeof(float) * npix, 256);
   if ((rc = ensure_arena(c, total))) return rc;
@@ -293,7 +293,7 @@ int lensed_render(lensed_ctx* c, const lensed_system* sys, const float* theta, f
   LENSED_HIP(c, launch_prologue(theta, 1, pc, p64, nullptr, sd, nullptr, 1, cl.count, st));
   LENSED_HIP(c, launch_render(w, pc, p64, L, sd.n_rtiles, cl, st));
   if (apply_psf)
-    LENSED_HIP(c, launch_psf_single(w, L, image, nullptr, 0, st));
+    LENSED_HIP(c, launch_psf_single(w, L, image, nullptr, 0, nullptr, nullptr, st));
   return LENSED_OK;
 }
 
@@ -316,7 +316,7 @@ int lensed_render_composite(lensed_ctx* c, const lensed_system* sys, const float
   const size_t off_p64 = align_up(off_pc + sizeof(PointConst) * K, 256);
   const size_t off_psf = align_up(off_p64 + sizeof(PointConst64) * K, 256);
   const size_t off_cc = align_up(off_psf + 3 * sizeof(float) * sd.ph * sd.pw, 256);
-  const size_t off_ce = align_up(off_cc + sizeof(int), 256);
+  const size_t off_ce = align_up(off_cc + 2 * sizeof(int), 256);
   const size_t off_L = align_up(off_ce + sizeof(CuspEntry) * (size_t)sd.n_rtiles * (RENDER_BLOCK / 64), 256);
   const size_t total = align_up(off_L + sizeof(float) * npix * K, 256);
   if ((rc = ensure_arena(c, total))) return rc;
@@ -330,7 +330,7 @@ int lensed_render_composite(lensed_ctx* c, const lensed_system* sys, const float
   w.single = sd;
   LENSED_HIP(c, launch_prologue(theta, K, pc, p64, nullptr, sd, nullptr, 1, cl.count, st));
   for (int j = 0; j < K; ++j) {       // one component at a time: its cusp list starts empty
-    if (j > 0) LENSED_HIP(c, launch_zero_count(cl.count, st));
+    if (j > 0 && !render_single(sd)) LENSED_HIP(c, launch_zero_count(cl.count, st));
     w.point0 = j;
     LENSED_HIP(c, launch_render(w, pc, p64, L + (size_t)j * npix, sd.n_rtiles, cl, st));
   }
@@ -338,7 +338,7 @@ int lensed_render_composite(lensed_ctx* c, const lensed_system* sys, const float
   LENSED_HIP(c, launch_sum_images(L, (int64_t)npix, K, sky_px, apply_psf ? L : image, st));
   w.point0 = 0;
   if (apply_psf)
-    LENSED_HIP(c, launch_psf_single(w, L, image, nullptr, 0, st));
+    LENSED_HIP(c, launch_psf_single(w, L, image, nullptr, 0, nullptr, nullptr, st));
   return LENSED_OK;
 }
 
@@ -357,7 +357,7 @@ int lensed_render_error(lensed_ctx* c, const lensed_system* sys, const float* th
   const size_t off_p64 = align_up(off_pc + sizeof(PointConst), 256);
   const size_t off_psf = align_up(off_p64 + sizeof(PointConst64), 256);
   const size_t off_cc = align_up(off_psf + 3 * sizeof(float) * sd.ph * sd.pw, 256);
-  const size_t total = align_up(off_cc + sizeof(int), 256);
+  const size_t total = align_up(off_cc + 2 * sizeof(int), 256);
   if ((rc = ensure_arena(c, total))) return rc;
   PointConst* pc = (PointConst*)(c->arena + off_pc);
   PointConst64* p64 = (PointConst64*)(c->arena + off_p64);
@@ -399,7 +399,7 @@ int lensed_loglike(lensed_ctx* c, const lensed_system* sys, const float* theta, 
   const size_t off_p64 = align_up(off_pc + sizeof(PointConst), 256);
   const size_t off_psf = align_up(off_p64 + sizeof(PointConst64), 256);
   const size_t off_cc = align_up(off_psf + 3 * sizeof(float) * sd.ph * sd.pw, 256);
-  const size_t off_ce = align_up(off_cc + sizeof(int), 256);
+  const size_t off_ce = align_up(off_cc + 2 * sizeof(int), 256);
   const size_t off_L = align_up(off_ce + sizeof(CuspEntry) * (size_t)sd.n_rtiles * (RENDER_BLOCK / 64), 256);
   const size_t off_part = align_up(off_L + sizeof(float) * npix, 256);
   const size_t total = align_up(off_part + sizeof(float2) * sd.n_ptiles, 256);
@@ -415,8 +415,7 @@ int lensed_loglike(lensed_ctx* c, const lensed_system* sys, const float* theta, 
   w.single = sd;
   LENSED_HIP(c, launch_prologue(theta, 1, pc, p64, nullptr, sd, nullptr, 1, cl.count, st));
   LENSED_HIP(c, launch_render(w, pc, p64, L, sd.n_rtiles, cl, st));
-  LENSED_HIP(c, launch_psf_single(w, L, nullptr, part, 1, st));
-  LENSED_HIP(c, launch_finalize(part, nullptr, nullptr, 1, sd.n_ptiles, logl, st));
+  LENSED_HIP(c, launch_psf_single(w, L, nullptr, part, 1, cl.count + 1, logl, st));
   return LENSED_OK;
 }
 
@@ -683,7 +682,7 @@ int lensed_render_model(lensed_ctx* c, const lensed_system* sys, const lensed_mo
   LENSED_HIP(c, launch_model_prologue(theta, 1, spec_params(spec), spec, mc, sd, nullptr, 1, st));
   LENSED_HIP(c, launch_model_render(w, spec, mc, L, sd.n_rtiles, st));
   if (apply_psf)
-    LENSED_HIP(c, launch_psf_single(w, L, image, nullptr, 0, st));
+    LENSED_HIP(c, launch_psf_single(w, L, image, nullptr, 0, nullptr, nullptr, st));
   return LENSED_OK;
 }
 

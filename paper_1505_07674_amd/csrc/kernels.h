@@ -46,7 +46,7 @@ hipError_t for_item_parts(const WorkArgs& w, int n_blocks, F launch) {
   return hipSuccess;
 }
 
-// Also clears *cusp_count (may be nullptr) and, when gcs is given, the 17
+// Also clears cusp_count[0] and [1] (may be nullptr) and, when gcs is given, the 17
 // cusp-correction accumulators of every point in grad_corr. The system of
 // point p is table[point_sys[p]] (table[0] without point_sys; single without
 // table); its amplitude mode decides whether theta[5] and theta[12] are I_e or
@@ -58,13 +58,18 @@ hipError_t launch_prologue(const float* theta, int n_points, PointConst* pcs, Po
                            double* grad_corr = nullptr, const int* point_sys = nullptr, bool adjoint_tables = false,
                            int support_blocks = 0);
 
-// Unconvolved pixel luminosities into L (scratch or the caller's image): the
-// float32 render kernel, then the float64 cusp corrections of the pixels it
-// flagged. cl.entries needs one slot per render wave (n_blocks * 4); cl.count
-// must be zero when the render kernel starts (the prologue clears it). A
-// non-null `between` is recorded on the stream after the render kernel.
+// Whether one image of this size leaves the chip mostly idle, so that latency and
+// launches count and not registers or occupancy: 2^18 pixels are 4 waves per SIMD.
+constexpr int64_t SINGLE_MAX_PIXELS = 1 << 18;
+inline bool render_single(const SysDesc& sd) { return (int64_t)sd.H * sd.W <= SINGLE_MAX_PIXELS; }
+
+// Unconvolved pixel luminosities of w.single into L (scratch or the caller's
+// image): one kernel if render_single, else the float32 render kernel, then the
+// float64 cusp corrections of the pixels it flagged. cl.entries needs one slot per
+// render wave (n_blocks * 4); cl.count must be zero when the render kernel starts
+// (the prologue clears it).
 hipError_t launch_render(const WorkArgs& w, const PointConst* pcs, const PointConst64* p64s, float* L, int n_blocks,
-                         const CuspList& cl, hipStream_t stream, hipEvent_t between = nullptr);
+                         const CuspList& cl, hipStream_t stream);
 
 // Schedule class of a system's render: N (1..RENDER_MAX_CLASS) for the N x N
 // midpoint rule, each its own kernel with the rule unrolled; 0 for the
@@ -86,7 +91,8 @@ struct RenderSchedule {
   int ppt, block;
 };
 // Batched form: one launch per span, then one cusp-correction pass over all of
-// them. cl.entries needs one slot per render wave and pixel of a thread.
+// them. cl.entries needs one slot per render wave and pixel of a thread. A
+// non-null `between` is recorded on the stream after the render kernels.
 hipError_t launch_render(const WorkArgs& w, const PointConst* pcs, const PointConst64* p64s, float* L,
                          const RenderSpan* spans, int n_spans, const CuspList& cl, hipStream_t stream,
                          hipEvent_t between = nullptr);
@@ -142,8 +148,10 @@ hipError_t launch_rule_error(const WorkArgs& w, const PointConst* pcs, float* E,
 hipError_t launch_psf(const WorkArgs& w, const float* L, float* out, float2* partials, int mode, int n_blocks, int TW,
                       int TH, int max_ph, int max_pw, int group, hipStream_t stream);
 // One image (w.single, with a tile of TileCache::latency_best) on an idle chip.
-hipError_t launch_psf_single(const WorkArgs& w, const float* L, float* out, float2* partials, int mode,
-                             hipStream_t stream);
+// With logl also its log L from the partials; *done must be 0 (the prologue clears
+// the word after the cusp count) and is used up.
+hipError_t launch_psf_single(const WorkArgs& w, const float* L, float* out, float2* partials, int mode, int* done,
+                             double* logl, hipStream_t stream);
 // Rows of a Kahan chain in a launch of many images whose PSFs have the given
 // square size (0: not all of one square size); one image at a time always has 4.
 inline int psf_group(int square_psf) { return square_psf == 21 ? 8 : 4; }

@@ -47,7 +47,7 @@ extern "C" int lensed_loglike_noalloc(const lensed_system* sys, const float* the
   const size_t off_p64 = up256(off_pc + sizeof(PointConst));
   const size_t off_psf = up256(off_p64 + sizeof(PointConst64));
   const size_t off_cc = up256(off_psf + 3 * sizeof(float) * sd.ph * sd.pw);
-  const size_t off_ce = up256(off_cc + sizeof(int));
+  const size_t off_ce = up256(off_cc + 2 * sizeof(int));
   const size_t off_L = up256(off_ce + sizeof(CuspEntry) * (size_t)sd.n_rtiles * (RENDER_BLOCK / 64));
   // the per-tile sums take the place of the cusp work list, which the PSF stage no
   // longer needs (every tile has at least 128 pixels, and the list 24 bytes per 64)
@@ -69,8 +69,7 @@ extern "C" int lensed_loglike_noalloc(const lensed_system* sys, const float* the
   w.single = sd;
   if (launch_prologue(theta, 1, pc, p64, nullptr, sd, nullptr, 1, cl.count, st) != hipSuccess ||
       launch_render(w, pc, p64, L, sd.n_rtiles, cl, st) != hipSuccess ||
-      launch_psf_single(w, L, nullptr, part, 1, st) != hipSuccess ||
-      launch_finalize(part, nullptr, nullptr, 1, sd.n_ptiles, logl, st) != hipSuccess)
+      launch_psf_single(w, L, nullptr, part, 1, cl.count + 1, logl, st) != hipSuccess)
     return LENSED_HIP_ERROR;
   return LENSED_OK;
 }

@@ -19,7 +19,6 @@ struct TileShape {
   int TW, TH;
 };
 // The tiles of psf_single_kernel (one image at a time).
-constexpr int64_t SINGLE_MAX_PIXELS = 1 << 18;
 inline bool is_single_tile(TileShape t) { return (t.TW == 32 && t.TH == 16) || (t.TW == 16 && t.TH == 8); }
 
 // Chooses the TW x TH output tile of the PSF/chi^2 kernel for a launch. The

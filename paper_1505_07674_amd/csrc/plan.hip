@@ -346,7 +346,7 @@ hipError_t BatchPlan::build(const lensed_system* systems, int n_systems, const f
   const size_t o_mc = off; off = align256(off + (has_model_ ? sizeof(ModelConst) * n_points : 0));
   const size_t o_p64 = off; off = align256(off + sizeof(PointConst64) * n_points);
   const size_t o_psf = off; off = align256(off + 3 * sizeof(float) * psf_total);
-  const size_t o_cc = off; off = align256(off + sizeof(int));
+  const size_t o_cc = off; off = align256(off + 2 * sizeof(int));
   const size_t o_ce = off; off = align256(off + sizeof(CuspEntry) * (size_t)cusp_slots);
   const size_t o_L = off; off = align256(off + sizeof(float) * (size_t)Ltot);
   const size_t o_part = off; off = align256(off + sizeof(float2) * (size_t)ptot);

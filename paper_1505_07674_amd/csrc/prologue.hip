@@ -338,7 +338,7 @@ __global__ __launch_bounds__(PROLOGUE_THREADS) void prologue_kernel(
     GradConst* __restrict__ gcs, const SysDesc* __restrict__ table, const int* __restrict__ point_sys,
     int* __restrict__ cusp_count, double* __restrict__ grad_corr, SysDesc single, int point_blocks,
     int n_sys, int support) {
-  if (cusp_count && blockIdx.x == 0 && threadIdx.x == 0) *cusp_count = 0;
+  if (cusp_count && blockIdx.x == 0 && threadIdx.x < 2) cusp_count[threadIdx.x] = 0;
   __shared__ PrologueScratch<ADJ> lds;
   if ((int)blockIdx.x >= point_blocks) {
     system_block<ADJ>(table, single, n_sys, blockIdx.x - point_blocks, support, lds.system);

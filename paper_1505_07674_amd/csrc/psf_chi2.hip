@@ -191,13 +191,30 @@ __global__ __launch_bounds__(PSF_MAX_THREADS, KP <= 24 ? 4 : 2) void psf_kernel(
                 partials + (w.point_pbase ? w.point_pbase[point] : 0) + tile);
 }
 
+// The lanes of a wave stride over a point's tile sums, then a fixed shuffle tree in
+// float64; lane 0 returns log L.
+__device__ __forceinline__ double loglike_sum(const float2* partials, int n) {
+  double s = 0.0;
+  for (int t = (int)threadIdx.x & 63; t < n; t += 64) {
+    const float2 v = partials[t];
+    s += (double)v.x + (double)v.y;
+  }
+  for (int off = 32; off > 0; off >>= 1) s += __shfl_down(s, off, 64);
+  return -0.5 * s;
+}
+
 // One image at a time: the tiles of w.single, two rows of one column per thread
-// (stencil_pair).
+// (stencil_pair). With logl, the block that finishes last (by *done, which starts
+// at 0) also adds the tile sums: 3 us more here, a launch and its gap less. 21 x 21 taps
+// on 200 x 200 pixels: half of the 9 us is the stencil, whose reads fill the LDS port
+// (the taps through scalar registers instead took 12 us, a column ahead 13 us).
 template <int PH>
 __global__ __launch_bounds__(PSF_MAX_THREADS) void psf_single_kernel(WorkArgs w, const float* __restrict__ L,
                                                                      float* __restrict__ out,
-                                                                     float2* __restrict__ partials, int mode) {
+                                                                     float2* partials, int mode, int* done,
+                                                                     double* __restrict__ logl) {
   extern __shared__ __align__(16) float S[];
+  __shared__ bool last;
   const SysDesc& sd = w.single;
   const int H = sd.H, W = sd.W, TW = sd.TW, TH = sd.TH, ph = PH > 0 ? PH : sd.ph, pw = PH > 0 ? PH : sd.pw;
   const int tile = blockIdx.x, ty = tile / sd.tiles_x, x0 = (tile - ty * sd.tiles_x) * TW, y0 = ty * TH;
@@ -215,11 +232,20 @@ __global__ __launch_bounds__(PSF_MAX_THREADS) void psf_single_kernel(WorkArgs w,
   __syncthreads();
   tile_epilogue(S, cs, H, W, TW, TH, x0, y0, uniform_in(sd.data), uniform_in(sd.weight), uniform_out(out), mode, 4,
                 partials + tile);
+  if (!logl) return;
+  if (threadIdx.x == 0) {   // the thread that stored the tile's sum
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "agent");
+    last = __hip_atomic_fetch_add(done, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == (int)gridDim.x - 1;
+  }
+  __syncthreads();
+  if (!last || threadIdx.x >= 64) return;
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
+  const double v = loglike_sum(partials, (int)gridDim.x);
+  if (threadIdx.x == 0) *logl = v;
 }
 
-// log L of one point per wave: the lanes stride over its tiles, then a fixed
-// shuffle tree in float64. (One thread per point waits for one load after another:
-// 5.2 us for the 49 tiles of a single 200 x 200 image, 9.2 us for 91.)
+// log L of one point per wave. (One thread per point waits for one load after
+// another: 5.2 us for the 49 tiles of a single 200 x 200 image, 9.2 us for 91.)
 constexpr int FINALIZE_WAVES = 4;
 __global__ __launch_bounds__(64 * FINALIZE_WAVES) void finalize_kernel(const float2* __restrict__ partials,
                                                                        const int* __restrict__ pbase,
@@ -229,13 +255,8 @@ __global__ __launch_bounds__(64 * FINALIZE_WAVES) void finalize_kernel(const flo
   if (p >= n_points) return;   // a whole wave
   const int base = pbase ? pbase[p] : 0;
   const int nt = ntiles ? ntiles[p] : single_ntiles;
-  double s = 0.0;
-  for (int t = lane; t < nt; t += 64) {
-    const float2 v = partials[base + t];
-    s += (double)v.x + (double)v.y;
-  }
-  for (int off = 32; off > 0; off >>= 1) s += __shfl_down(s, off, 64);
-  if (lane == 0) logl[p] = -0.5 * s;
+  const double v = loglike_sum(partials + base, nt);
+  if (lane == 0) logl[p] = v;
 }
 
 }  // namespace
@@ -258,20 +279,22 @@ hipError_t launch_psf(const WorkArgs& w, const float* L, float* out, float2* par
   });
 }
 
-hipError_t launch_psf_single(const WorkArgs& w, const float* L, float* out, float2* partials, int mode,
-                             hipStream_t stream) {
+hipError_t launch_psf_single(const WorkArgs& w, const float* L, float* out, float2* partials, int mode, int* done,
+                             double* logl, hipStream_t stream) {
   const SysDesc& sd = w.single;
-  if (!is_single_tile(TileShape{sd.TW, sd.TH}))
-    return launch_psf(w, L, out, partials, mode, sd.n_ptiles, sd.TW, sd.TH, sd.ph, sd.pw, 4, stream);
+  if (!is_single_tile(TileShape{sd.TW, sd.TH})) {
+    const hipError_t e = launch_psf(w, L, out, partials, mode, sd.n_ptiles, sd.TW, sd.TH, sd.ph, sd.pw, 4, stream);
+    return e != hipSuccess || !logl ? e : launch_finalize(partials, nullptr, nullptr, 1, sd.n_ptiles, logl, stream);
+  }
   const int threads = single_threads(sd.TW, sd.TH);
   const size_t lds = single_lds_bytes(sd.TW, sd.TH, sd.ph, sd.pw);
   const dim3 grid((unsigned)sd.n_ptiles), block((unsigned)threads);
   if (sd.ph == 21 && sd.pw == 21)
-    hipLaunchKernelGGL((psf_single_kernel<21>), grid, block, lds, stream, w, L, out, partials, mode);
+    hipLaunchKernelGGL((psf_single_kernel<21>), grid, block, lds, stream, w, L, out, partials, mode, done, logl);
   else if (sd.ph == 7 && sd.pw == 7)
-    hipLaunchKernelGGL((psf_single_kernel<7>), grid, block, lds, stream, w, L, out, partials, mode);
+    hipLaunchKernelGGL((psf_single_kernel<7>), grid, block, lds, stream, w, L, out, partials, mode, done, logl);
   else
-    hipLaunchKernelGGL((psf_single_kernel<0>), grid, block, lds, stream, w, L, out, partials, mode);
+    hipLaunchKernelGGL((psf_single_kernel<0>), grid, block, lds, stream, w, L, out, partials, mode, done, logl);
   return hipGetLastError();
 }
 

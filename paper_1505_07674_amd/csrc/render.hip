@@ -124,23 +124,28 @@ __global__ __launch_bounds__(RENDER_BLOCK_MAX, NC > 0 && NC <= 4 ? 8 : 1) void r
   if (PPT == 2) push_cusp(cl, cusp1, point, unit0, PPT, 1);
 }
 
-// Adds the float64 cusp corrections to the flagged pixels; a fixed grid of
-// waves walks the list written by render_kernel (each pixel appears at most
-// once), one entry per wave at a time. Only a few pixels of a flagged wave, and
-// a part of their subsamples, lie inside the re-tracing radius. The wave lists
-// the entry's F flagged pixels in LDS and tests the F x (subsamples) pairs 64
-// at a time (float32, as the render saw them), queueing those inside the
-// radius; then it re-traces the queue in float64 64 at a time with every lane
-// busy. Lane f < F then adds its pixel's corrections in the rule's order (zero
-// outside the radius), as a serial loop over its subsamples would.
-// What bounds it: one entry's chain of dependent loads, tests and float64 operations
+// The float64 cusp corrections of a wave's flagged pixels. Only a few pixels of a
+// flagged wave, and a part of their subsamples, lie inside the re-tracing radius.
+// With the F flagged pixels in LDS, the wave tests the F x (subsamples) pairs 64 at
+// a time (float32, as the render saw them), queueing those inside the radius; then
+// it re-traces the queue in float64 64 at a time with every lane busy. Lane f < F
+// then adds its pixel's corrections in the rule's order (zero outside the radius),
+// as a serial loop over its subsamples would; cusp_sum returns them.
+// What bounds it: one chain of dependent loads, tests and float64 operations
 // at few points; registers at many: the point and its constants are scalars, and the
 // re-tracing takes sie_ab instead of the library's atan and atanh, which lets four
 // waves share a SIMD instead of three. 4096 points of 200 x 200 pixels, N = 4:
-// 141 -> 93 us; 1024 of 120 x 120 with g3k7 81 -> 58 us; one point 7.5 -> 7.0 us.
+// 141 -> 93 us; 1024 of 120 x 120 with g3k7 81 -> 58 us.
 constexpr int CUSP_WAVES = 4;
 constexpr int CUSP_BLOCKS = 2048;
 constexpr int CUSP_CHUNK = 16;   // subsamples per pass
+
+// LDS of a wave.
+struct CuspScratch {
+  float dval[CUSP_CHUNK * 64];             // [subsample][flagged pixel]
+  unsigned short queue[CUSP_CHUNK * 64];   // flagged pixel | subsample << 6
+  int pix[64];                             // the flagged pixels
+};
 
 // LDS written by some lanes of a wave and read by others: order the accesses
 // and wait for the writes.
@@ -156,19 +161,81 @@ __device__ __forceinline__ void subsample_xy(const GkRule* R, int N, int kx, int
   x = R ? fmaf(g.ux + R->x[kx], g.d, g.cx) : fmaf(g.ux + sub_offset_rt(kx, N), g.d, g.cx);
 }
 
+__device__ __forceinline__ float cusp_sum(const SysDesc& sd, const PointConst& c, const PointConst64& c64, int F,
+                                          int lane, CuspScratch& S) {
+  const GkRule* R = sd.rule > 0 ? &kGkRules[sd.rule - 1] : nullptr;
+  const int N = sd.N, NN = N * N;
+  float acc = 0.0f;
+  for (int s0 = 0; s0 < NN; s0 += CUSP_CHUNK) {
+    const int ns = min(CUSP_CHUNK, NN - s0);
+    for (int j = 0; j < ns; ++j) S.dval[j * 64 + lane] = 0.0f;
+    // the (flagged pixel, subsample) pairs of the chunk inside the radius, queued in pair order
+    int qn = 0;
+    for (int b = 0; b < F * ns; b += 64) {
+      const int item = b + lane;
+      bool within = false;
+      int f = 0, j = 0;
+      if (item < F * ns) {
+        f = item / ns;
+        j = item - f * ns;
+        const int ky = (s0 + j) / N, kx = s0 + j - ky * N;
+        int v;
+        const PixelGeom g = pixel_geom(sd, S.pix[f], &v);
+        float x, y;
+        subsample_xy(R, N, kx, ky, g, x, y);
+        within = render_source_R2(c, c.rv[v], x, y) < c.cusp_r2;
+      }
+      const unsigned long long bal = __ballot(within);
+      if (within) S.queue[qn + __popcll(bal & ((1ull << lane) - 1ull))] = (unsigned short)(f | (j << 6));
+      qn += __popcll(bal);
+    }
+    wave_lds_sync();
+    // float64 re-tracing of the queue, 64 subsamples at a time
+    for (int q0 = 0; q0 < qn; q0 += 64) {
+      if (q0 + lane < qn) {
+        const int it = S.queue[q0 + lane];
+        const int f = it & 63, j = it >> 6;
+        const int ky = (s0 + j) / N, kx = s0 + j - ky * N;
+        int vq;
+        const PixelGeom gq = pixel_geom(sd, S.pix[f], &vq);
+        const RenderVariant& kq = c.rv[vq];
+        float x, y;
+        subsample_xy(R, N, kx, ky, gq, x, y);
+        const float sR2 = render_source_R2(c, kq, x, y);
+        const double ox = R ? R->xd[kx] : ((double)kx + 0.5) / N - 0.5;
+        const double oy = R ? R->xd[ky] : ((double)ky + 0.5) / N - 0.5;
+        float dx, dy;
+        source_offset_f64(c64, gq, ox, oy, dx, dy);
+        const float exact = sersic_shape(source_R2(kq, dx, dy), kq.se, kq.sB);
+        const float d = exact - sersic_shape(sR2, kq.se, kq.sB);
+        S.dval[j * 64 + f] = R ? R->w[kx] * R->w[ky] * d : d;
+      }
+    }
+    wave_lds_sync();
+    if (lane < F)
+      for (int j = 0; j < ns; ++j) acc += S.dval[j * 64 + lane];
+    wave_lds_sync();
+  }
+  return acc;
+}
+
+// A pixel's luminosity L with its correction.
+__device__ __forceinline__ float cusp_corrected(float L, const PointConst& c, float acc, const SysDesc& sd) {
+  return (float)((double)L + (double)(c.sI * acc) * sd.wgt);
+}
+
+// Adds the corrections to the pixels flagged by render_kernel; a fixed grid of
+// waves walks its list (each pixel appears at most once), one entry per wave at
+// a time.
 __global__ __launch_bounds__(64 * CUSP_WAVES, 4) void cusp_kernel(WorkArgs w, const PointConst* __restrict__ pcs,
                                                                const PointConst64* __restrict__ p64s,
                                                                float* __restrict__ L, CuspList cl) {
-  __shared__ float dval[CUSP_WAVES][CUSP_CHUNK * 64];             // [subsample][flagged pixel]
-  __shared__ unsigned short queue[CUSP_WAVES][CUSP_CHUNK * 64];   // flagged pixel | subsample << 6
-  __shared__ int fpix[CUSP_WAVES][64];                            // the entry's flagged pixels
+  __shared__ CuspScratch lds[CUSP_WAVES];
   const int n = *cl.count;
   const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
   // a scalar, so that an entry's point and its constants are read with uniform addresses
   const int wave = __builtin_amdgcn_readfirstlane((int)blockIdx.x * CUSP_WAVES + wv);
-  float* __restrict__ dv = dval[wv];
-  unsigned short* __restrict__ qu = queue[wv];
-  int* __restrict__ fp = fpix[wv];
+  CuspScratch& S = lds[wv];
   for (int i = wave; i < n; i += gridDim.x * CUSP_WAVES) {
     const CuspEntry e = cl.entries[i];
     const bool mine = (e.mask >> lane) & 1ull;
@@ -176,66 +243,60 @@ __global__ __launch_bounds__(64 * CUSP_WAVES, 4) void cusp_kernel(WorkArgs w, co
     const int point = __builtin_amdgcn_readfirstlane(e.point);
     const SysDesc& sd = w.sys_table ? w.sys_table[w.point_sys ? w.point_sys[point] : 0] : w.single;
     const int64_t loff = w.point_loff ? w.point_loff[point] : 0;
-    if (mine) fp[__popcll(e.mask & ((1ull << lane) - 1ull))] = unit_pixel(sd, e.unit0 + lane, e.ppt) + e.half;
+    if (mine) S.pix[__popcll(e.mask & ((1ull << lane) - 1ull))] = unit_pixel(sd, e.unit0 + lane, e.ppt) + e.half;
     wave_lds_sync();
+    const int pix = lane < F ? S.pix[lane] : 0;   // the flagged pixel whose sum this lane keeps
     const PointConst& c = pcs[point];
-    const PointConst64& c64 = p64s[point];
-    const GkRule* R = sd.rule > 0 ? &kGkRules[sd.rule - 1] : nullptr;
-    const int N = sd.N, NN = N * N;
-    const int pix = lane < F ? fp[lane] : 0;   // the flagged pixel whose sum this lane keeps
-    float acc = 0.0f;
-    for (int s0 = 0; s0 < NN; s0 += CUSP_CHUNK) {
-      const int ns = min(CUSP_CHUNK, NN - s0);
-      for (int j = 0; j < ns; ++j) dv[j * 64 + lane] = 0.0f;
-      // the (flagged pixel, subsample) pairs of the chunk inside the radius, queued in pair order
-      int qn = 0;
-      for (int b = 0; b < F * ns; b += 64) {
-        const int item = b + lane;
-        bool within = false;
-        int f = 0, j = 0;
-        if (item < F * ns) {
-          f = item / ns;
-          j = item - f * ns;
-          const int ky = (s0 + j) / N, kx = s0 + j - ky * N;
-          int v;
-          const PixelGeom g = pixel_geom(sd, fp[f], &v);
-          float x, y;
-          subsample_xy(R, N, kx, ky, g, x, y);
-          within = render_source_R2(c, c.rv[v], x, y) < c.cusp_r2;
-        }
-        const unsigned long long bal = __ballot(within);
-        if (within) qu[qn + __popcll(bal & ((1ull << lane) - 1ull))] = (unsigned short)(f | (j << 6));
-        qn += __popcll(bal);
-      }
-      wave_lds_sync();
-      // float64 re-tracing of the queue, 64 subsamples at a time
-      for (int q0 = 0; q0 < qn; q0 += 64) {
-        if (q0 + lane < qn) {
-          const int it = qu[q0 + lane];
-          const int f = it & 63, j = it >> 6;
-          const int ky = (s0 + j) / N, kx = s0 + j - ky * N;
-          int vq;
-          const PixelGeom gq = pixel_geom(sd, fp[f], &vq);
-          const RenderVariant& kq = c.rv[vq];
-          float x, y;
-          subsample_xy(R, N, kx, ky, gq, x, y);
-          const float sR2 = render_source_R2(c, kq, x, y);
-          const double ox = R ? R->xd[kx] : ((double)kx + 0.5) / N - 0.5;
-          const double oy = R ? R->xd[ky] : ((double)ky + 0.5) / N - 0.5;
-          float dx, dy;
-          source_offset_f64(c64, gq, ox, oy, dx, dy);
-          const float exact = sersic_shape(source_R2(kq, dx, dy), kq.se, kq.sB);
-          const float d = exact - sersic_shape(sR2, kq.se, kq.sB);
-          dv[j * 64 + f] = R ? R->w[kx] * R->w[ky] * d : d;
-        }
-      }
-      wave_lds_sync();
-      if (lane < F)
-        for (int j = 0; j < ns; ++j) acc += dv[j * 64 + lane];
-      wave_lds_sync();
-    }
-    if (lane < F) L[loff + pix] = (float)((double)L[loff + pix] + (double)(c.sI * acc) * sd.wgt);
+    const float acc = cusp_sum(sd, c, p64s[point], F, lane, S);
+    if (lane < F) L[loff + pix] = cusp_corrected(L[loff + pix], c, acc, sd);
   }
+}
+
+// One image at a time: a pixel per thread, and each wave corrects its own flagged
+// pixels before it stores them, in place of the list and cusp_kernel. The registers
+// of the corrections do not matter where the chip is mostly idle (render_single),
+// the launch does: 200 x 200 pixels, N = 4, 12.5 us in two kernels, 7.6 us in one. With
+// the tile sums added in the PSF's launch, log L of one point is three launches
+// instead of five: 64 x 64 pixels 22 -> 13 us a call, 200 x 200 25.5 -> 23 us.
+constexpr int RENDER_SINGLE_BLOCK = 64 * CUSP_WAVES;
+template <int NC>
+__global__ __launch_bounds__(RENDER_SINGLE_BLOCK) void render_single_kernel(WorkArgs w,
+                                                                            const PointConst* __restrict__ pcs,
+                                                                            const PointConst64* __restrict__ p64s,
+                                                                            float* __restrict__ L) {
+  __shared__ CuspScratch lds[CUSP_WAVES];
+  const SysDesc& sd = w.single;
+  const int pix = (int)blockIdx.x * RENDER_SINGLE_BLOCK + (int)threadIdx.x;
+  const bool active = pix < sd.H * sd.W;
+  const PointConst& c = pcs[w.point0];
+  bool cusp = false;
+  float value = 0.0f;
+  if (active) {
+    int v;
+    const PixelGeom g = pixel_geom(sd, pix, &v);
+    const RenderVariant& k = c.rv[v];
+    float acc;
+    switch (c.rmode) {
+      case 0: acc = pixel_sum_class<NC, 0>(c, k, sd.rule, sd.N, g, cusp); break;
+      case 1: acc = pixel_sum_class<NC, 1>(c, k, sd.rule, sd.N, g, cusp); break;
+      case 2: acc = pixel_sum_class<NC, 2>(c, k, sd.rule, sd.N, g, cusp); break;
+      default: acc = pixel_sum_class<NC, 3>(c, k, sd.rule, sd.N, g, cusp); break;
+    }
+    value = (float)((double)acc * sd.wgt);
+  }
+  const unsigned long long mask = __ballot(cusp);
+  if (mask != 0ull) {
+    const int lane = threadIdx.x & 63;
+    CuspScratch& S = lds[threadIdx.x >> 6];
+    const int slot = __popcll(mask & ((1ull << lane) - 1ull));
+    if (cusp) S.pix[slot] = pix;
+    wave_lds_sync();
+    const float acc = cusp_sum(sd, c, p64s[w.point0], __popcll(mask), lane, S);
+    // lane f holds the sum of the f-th flagged pixel
+    const float own = __shfl(acc, slot, 64);
+    if (cusp) value = cusp_corrected(value, c, own, sd);
+  }
+  if (active) L[pix] = value;
 }
 
 // |Kronrod - embedded Gauss| x pixel weight for every pixel of one point (the
@@ -387,9 +448,29 @@ hipError_t launch_render(const WorkArgs& w, const PointConst* pcs, const PointCo
 }
 
 hipError_t launch_render(const WorkArgs& w, const PointConst* pcs, const PointConst64* p64s, float* L, int n_blocks,
-                         const CuspList& cl, hipStream_t stream, hipEvent_t between) {
-  const RenderSpan span{render_class(w.single), 1, 0, n_blocks, RENDER_BLOCK};
-  return launch_render(w, pcs, p64s, L, &span, 1, cl, stream, between);
+                         const CuspList& cl, hipStream_t stream) {
+  const int klass = render_class(w.single);
+  if (!render_single(w.single)) {
+    const RenderSpan span{klass, 1, 0, n_blocks, RENDER_BLOCK};
+    return launch_render(w, pcs, p64s, L, &span, 1, cl, stream);
+  }
+  const int64_t npix = (int64_t)w.single.H * w.single.W;
+  const dim3 grid((unsigned)((npix + RENDER_SINGLE_BLOCK - 1) / RENDER_SINGLE_BLOCK)), block(RENDER_SINGLE_BLOCK);
+  switch (klass) {
+#define LENSED_RENDER_CLASS(NC)                                                                \
+  case NC: hipLaunchKernelGGL((render_single_kernel<NC>), grid, block, 0, stream, w, pcs, p64s, L); break;
+    LENSED_RENDER_CLASS(1)
+    LENSED_RENDER_CLASS(2)
+    LENSED_RENDER_CLASS(3)
+    LENSED_RENDER_CLASS(4)
+    LENSED_RENDER_CLASS(5)
+    LENSED_RENDER_CLASS(6)
+    LENSED_RENDER_CLASS(7)
+    LENSED_RENDER_CLASS(8)
+#undef LENSED_RENDER_CLASS
+    default: hipLaunchKernelGGL((render_single_kernel<0>), grid, block, 0, stream, w, pcs, p64s, L); break;
+  }
+  return hipGetLastError();
 }
 
 }  // namespace lensed
