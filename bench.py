@@ -252,13 +252,13 @@ def next_rows(lensed, mocks, dev, stream, spec, obs, steps=3):
                                             "kernel": "model_render (float64 rays, float32 profile fractions)",
                                             "ops_per_subsample": GENERAL41_OPS_PER_SUBSAMPLE,
                                             "subsamples_per_launch": subs}}
-    # and its adjoint (one component per pass, float64 dual numbers)
+    # and its adjoint (closed-form float64 moments, two lenses or two light components per pass)
     P = 64
     th = th[:P].contiguous()
     log(f"general model (41 parameters) gradients: {P} points")
     ms, st = timed(lambda: lensed.loglike_model_grad(th, gs, model, ctx=ctx), P, ctx)
     out["general_model_41_grad"] = {"value": P / (ms / 1e3), "unit": "gradients/s", "points": P, "params": 41,
-                                    "passes": 2 + 4 + 1, "stage_ms_per_step": st}
+                                    "passes": 1 + 2, "stage_ms_per_step": st}
     ctx.close()
     return out
 

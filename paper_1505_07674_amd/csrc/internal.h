@@ -77,9 +77,9 @@ struct PointHead {
   // atanh (poly[6..10]); coefficient k is c_k q'^(2k+1). The leading q' is per
   // variant.
   float poly[11];
-  float pad[15];
+  float pad[47];   // the variants start at a multiple of 256 bytes
 };
-static_assert(sizeof(PointHead) == 32 * 4, "PointHead layout");
+static_assert(sizeof(PointHead) == 64 * 4, "PointHead layout");
 
 struct PointConst : PointHead {
   RenderVariant rv[RENDER_VARIANTS];
