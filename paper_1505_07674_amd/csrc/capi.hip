@@ -329,8 +329,9 @@ int lensed_render_composite(lensed_ctx* c, const lensed_system* sys, const float
   std::memset(&w, 0, sizeof(w));
   w.single = sd;
   LENSED_HIP(c, launch_prologue(theta, K, pc, p64, nullptr, sd, nullptr, 1, cl.count, st));
+  const RenderSpan span{render_class(sd), 1, 0, sd.n_rtiles, RENDER_BLOCK};
   for (int j = 0; j < K; ++j) {       // one component at a time: its cusp list starts empty
-    if (j > 0 && !render_single(sd)) LENSED_HIP(c, launch_zero_count(cl.count, st));
+    if (j > 0 && !render_fused(&span, 1)) LENSED_HIP(c, launch_zero_count(cl.count, st));
     w.point0 = j;
     LENSED_HIP(c, launch_render(w, pc, p64, L + (size_t)j * npix, sd.n_rtiles, cl, st));
   }

@@ -58,16 +58,10 @@ hipError_t launch_prologue(const float* theta, int n_points, PointConst* pcs, Po
                            double* grad_corr = nullptr, const int* point_sys = nullptr, bool adjoint_tables = false,
                            int support_blocks = 0);
 
-// Whether one image of this size leaves the chip mostly idle, so that latency and
-// launches count and not registers or occupancy: 2^18 pixels are 4 waves per SIMD.
-constexpr int64_t SINGLE_MAX_PIXELS = 1 << 18;
-inline bool render_single(const SysDesc& sd) { return (int64_t)sd.H * sd.W <= SINGLE_MAX_PIXELS; }
-
 // Unconvolved pixel luminosities of w.single into L (scratch or the caller's
-// image): one kernel if render_single, else the float32 render kernel, then the
-// float64 cusp corrections of the pixels it flagged. cl.entries needs one slot per
-// render wave (n_blocks * 4); cl.count must be zero when the render kernel starts
-// (the prologue clears it).
+// image), with the float64 cusp corrections; as the batched form below, with one
+// pixel per thread. cl.entries needs one slot per render wave (n_blocks * 4);
+// cl.count must be zero when the render kernel starts (the prologue clears it).
 hipError_t launch_render(const WorkArgs& w, const PointConst* pcs, const PointConst64* p64s, float* L, int n_blocks,
                          const CuspList& cl, hipStream_t stream);
 
@@ -90,11 +84,17 @@ constexpr int RENDER_BLOCK_MAX = 512;
 struct RenderSchedule {
   int ppt, block;
 };
-// Batched form: one launch per span, then one cusp-correction pass over all of
-// them. cl.entries needs one slot per render wave and pixel of a thread. A
-// non-null `between` is recorded on the stream after the render kernels.
+// Whether a launch of these spans takes render_fused_kernel: at most four waves per
+// SIMD, one pixel per thread.
+bool render_fused(const RenderSpan* spans, int n_spans);
+// Batched form: one launch per span. Each wave corrects its own pixels where the
+// launch leaves the chip mostly idle (render_fused), else the render kernels list
+// the flagged ones and one more pass over the list corrects them. cl.entries needs
+// one slot per render wave and pixel of a thread; the list is complete afterwards if
+// keep_list or not render_fused, else empty. A non-null `between` is recorded on the
+// stream after the render kernels.
 hipError_t launch_render(const WorkArgs& w, const PointConst* pcs, const PointConst64* p64s, float* L,
-                         const RenderSpan* spans, int n_spans, const CuspList& cl, hipStream_t stream,
+                         const RenderSpan* spans, int n_spans, const CuspList& cl, bool keep_list, hipStream_t stream,
                          hipEvent_t between = nullptr);
 
 // General models: per-point float64 constants from the parameters (n_params

@@ -18,7 +18,8 @@ namespace lensed {
 struct TileShape {
   int TW, TH;
 };
-// The tiles of psf_single_kernel (one image at a time).
+// The tiles of psf_single_kernel (one image at a time, up to four waves of pixels per SIMD).
+constexpr int64_t SINGLE_MAX_PIXELS = 1 << 18;
 inline bool is_single_tile(TileShape t) { return (t.TW == 32 && t.TH == 16) || (t.TW == 16 && t.TH == 8); }
 
 // Chooses the TW x TH output tile of the PSF/chi^2 kernel for a launch. The

@@ -523,7 +523,7 @@ hipError_t BatchPlan::enqueue(hipStream_t st, hipEvent_t* ev) const {
     if ((e = launch_model_render(wr, spec_, d_mc_, d_L_, n_ritems_, st)) != hipSuccess) return e;
     if (ev && (e = hipEventRecord(ev[2], st)) != hipSuccess) return e;
   } else {
-    if ((e = launch_render(wr, d_pc_, d_p64_, d_L_, rspans_.data(), (int)rspans_.size(), cusp_, st,
+    if ((e = launch_render(wr, d_pc_, d_p64_, d_L_, rspans_.data(), (int)rspans_.size(), cusp_, grad_ != nullptr, st,
                            ev ? ev[2] : nullptr)) != hipSuccess)
       return e;
     if (ev && n_ritems_ <= 0 && (e = hipEventRecord(ev[2], st)) != hipSuccess) return e;

@@ -252,26 +252,34 @@ __global__ __launch_bounds__(64 * CUSP_WAVES, 4) void cusp_kernel(WorkArgs w, co
   }
 }
 
-// One image at a time: a pixel per thread, and each wave corrects its own flagged
-// pixels before it stores them, in place of the list and cusp_kernel. The registers
-// of the corrections do not matter where the chip is mostly idle (render_single),
-// the launch does: 200 x 200 pixels, N = 4, 12.5 us in two kernels, 7.6 us in one. With
-// the tile sums added in the PSF's launch, log L of one point is three launches
-// instead of five: 64 x 64 pixels 22 -> 13 us a call, 200 x 200 25.5 -> 23 us.
-constexpr int RENDER_SINGLE_BLOCK = 64 * CUSP_WAVES;
-template <int NC>
-__global__ __launch_bounds__(RENDER_SINGLE_BLOCK) void render_single_kernel(WorkArgs w,
-                                                                            const PointConst* __restrict__ pcs,
-                                                                            const PointConst64* __restrict__ p64s,
-                                                                            float* __restrict__ L) {
+// render_kernel<NC, 1> and cusp_kernel in one: each wave corrects its own flagged
+// pixels before it stores them; with keep_list it also appends them to the list, for
+// the gradient's correction. The registers of the corrections do not matter where
+// the launch has at most four waves per SIMD (FUSED_MAX_WAVES), the second launch
+// does: one image of 200 x 200 pixels, N = 4, 12.5 us in two kernels, 7.6 us in one (with
+// the tile sums added in the PSF's launch, a log L of 64 x 64 pixels 22 -> 13 us, of
+// 200 x 200 25.5 -> 23 us); 16 gradients of 87 x 101 pixels, N = 3, 14.0 -> 9.5 us of render
+// and 80 -> 76.5 us a call.
+constexpr int FUSED_BLOCK = 64 * CUSP_WAVES;
+constexpr int FUSED_MAX_WAVES = 4096;
+template <int NC, bool ITEMS>   // ITEMS: a batch; else one image, w.single
+__global__ __launch_bounds__(FUSED_BLOCK) void render_fused_kernel(WorkArgs w, const PointConst* __restrict__ pcs,
+                                                                   const PointConst64* __restrict__ p64s,
+                                                                   float* __restrict__ L, CuspList cl, bool keep_list) {
   __shared__ CuspScratch lds[CUSP_WAVES];
-  const SysDesc& sd = w.single;
-  const int pix = (int)blockIdx.x * RENDER_SINGLE_BLOCK + (int)threadIdx.x;
-  const bool active = pix < sd.H * sd.W;
-  const PointConst& c = pcs[w.point0];
+  int point = w.point0, tile = blockIdx.x;
+  if (ITEMS) resolve_item(w, point, tile);
+  point = __builtin_amdgcn_readfirstlane(point);
+  const SysDesc& sd = ITEMS ? w.sys_table[w.point_sys ? w.point_sys[point] : 0] : w.single;
+  const int64_t loff = ITEMS ? w.point_loff[point] : 0;
+  const int unit = tile * (int)blockDim.x + (int)threadIdx.x;
+  const bool active = unit < (ITEMS ? unit_count(sd, 1) : sd.H * sd.W);
+  const PointConst& c = pcs[point];
   bool cusp = false;
   float value = 0.0f;
+  int pix = unit;
   if (active) {
+    if (ITEMS) pix = unit_pixel(sd, unit, 1);
     int v;
     const PixelGeom g = pixel_geom(sd, pix, &v);
     const RenderVariant& k = c.rv[v];
@@ -287,16 +295,17 @@ __global__ __launch_bounds__(RENDER_SINGLE_BLOCK) void render_single_kernel(Work
   const unsigned long long mask = __ballot(cusp);
   if (mask != 0ull) {
     const int lane = threadIdx.x & 63;
+    if (ITEMS && keep_list) push_cusp(cl, cusp, point, unit - lane, 1, 0);
     CuspScratch& S = lds[threadIdx.x >> 6];
     const int slot = __popcll(mask & ((1ull << lane) - 1ull));
     if (cusp) S.pix[slot] = pix;
     wave_lds_sync();
-    const float acc = cusp_sum(sd, c, p64s[w.point0], __popcll(mask), lane, S);
+    const float acc = cusp_sum(sd, c, p64s[point], __popcll(mask), lane, S);
     // lane f holds the sum of the f-th flagged pixel
     const float own = __shfl(acc, slot, 64);
     if (cusp) value = cusp_corrected(value, c, own, sd);
   }
-  if (active) L[pix] = value;
+  if (active) L[loff + pix] = value;
 }
 
 // |Kronrod - embedded Gauss| x pixel weight for every pixel of one point (the
@@ -400,65 +409,32 @@ hipError_t launch_compose(float* L, const int64_t* loff, const int* point_sys, c
 
 int render_class(const SysDesc& sd) { return sd.rule == 0 && sd.N <= RENDER_MAX_CLASS ? sd.N : 0; }
 
-hipError_t launch_render(const WorkArgs& w, const PointConst* pcs, const PointConst64* p64s, float* L,
-                         const RenderSpan* spans, int n_spans, const CuspList& cl, hipStream_t stream,
-                         hipEvent_t between) {
-  int n_waves = 0;   // cusp-list capacity: one entry per wave and pixel of a thread
-  for (int i = 0; i < n_spans; ++i) n_waves += spans[i].count * (spans[i].block / 64) * (spans[i].ppt == 2 ? 2 : 1);
-  if (n_waves <= 0) return hipSuccess;
+bool render_fused(const RenderSpan* spans, int n_spans) {
+  int64_t waves = 0;
   for (int i = 0; i < n_spans; ++i) {
-    if (spans[i].count <= 0) continue;
-    WorkArgs ws = w;
-    if (ws.items) ws.items += spans[i].offset;
-    const bool pair = spans[i].ppt == 2 && spans[i].klass > 0;
-    const int bs = spans[i].block;
-    if (bs < 64 || bs > RENDER_BLOCK_MAX || bs % 64 != 0) return hipErrorInvalidValue;
-    hipError_t e = for_item_parts(ws, spans[i].count, [&](const WorkArgs& part, int n) {
-      switch (spans[i].klass) {
-#define LENSED_RENDER_CLASS(NC)                                                                                     \
-  case NC:                                                                                                          \
-    if (pair)                                                                                                       \
-      hipLaunchKernelGGL((render_kernel<NC, 2>), dim3(n), dim3(bs), 0, stream, part, pcs, L, cl);                   \
-    else                                                                                                            \
-      hipLaunchKernelGGL((render_kernel<NC, 1>), dim3(n), dim3(bs), 0, stream, part, pcs, L, cl);                   \
-    break;
-        LENSED_RENDER_CLASS(1)
-        LENSED_RENDER_CLASS(2)
-        LENSED_RENDER_CLASS(3)
-        LENSED_RENDER_CLASS(4)
-        LENSED_RENDER_CLASS(5)
-        LENSED_RENDER_CLASS(6)
-        LENSED_RENDER_CLASS(7)
-        LENSED_RENDER_CLASS(8)
-#undef LENSED_RENDER_CLASS
-        default:
-          hipLaunchKernelGGL((render_kernel<0, 1>), dim3(n), dim3(bs), 0, stream, part, pcs, L, cl);
-          break;
-      }
-      return hipGetLastError();
-    });
-    if (e != hipSuccess) return e;
+    if (spans[i].ppt != 1 || spans[i].block > FUSED_BLOCK) return false;
+    waves += (int64_t)spans[i].count * (spans[i].block / 64);
   }
-  hipError_t e;
-  if (between && (e = hipEventRecord(between, stream)) != hipSuccess) return e;
-  int grid = (n_waves + CUSP_WAVES - 1) / CUSP_WAVES;
-  if (grid > CUSP_BLOCKS) grid = CUSP_BLOCKS;
-  hipLaunchKernelGGL(cusp_kernel, dim3(grid), dim3(64 * CUSP_WAVES), 0, stream, w, pcs, p64s, L, cl);
-  return hipGetLastError();
+  return waves <= FUSED_MAX_WAVES;
 }
 
-hipError_t launch_render(const WorkArgs& w, const PointConst* pcs, const PointConst64* p64s, float* L, int n_blocks,
-                         const CuspList& cl, hipStream_t stream) {
-  const int klass = render_class(w.single);
-  if (!render_single(w.single)) {
-    const RenderSpan span{klass, 1, 0, n_blocks, RENDER_BLOCK};
-    return launch_render(w, pcs, p64s, L, &span, 1, cl, stream);
-  }
-  const int64_t npix = (int64_t)w.single.H * w.single.W;
-  const dim3 grid((unsigned)((npix + RENDER_SINGLE_BLOCK - 1) / RENDER_SINGLE_BLOCK)), block(RENDER_SINGLE_BLOCK);
+// One render kernel of class klass: fused with the corrections, or of ppt pixels per thread.
+hipError_t launch_render_class(int klass, int ppt, bool fused, int n, int bs, const WorkArgs& w, const PointConst* pcs,
+                               const PointConst64* p64s, float* L, const CuspList& cl, bool keep_list,
+                               hipStream_t stream) {
   switch (klass) {
-#define LENSED_RENDER_CLASS(NC)                                                                \
-  case NC: hipLaunchKernelGGL((render_single_kernel<NC>), grid, block, 0, stream, w, pcs, p64s, L); break;
+#define LENSED_RENDER_CLASS(NC)                                                                                       \
+  case NC:                                                                                                            \
+    if (fused && w.items)                                                                                             \
+      hipLaunchKernelGGL((render_fused_kernel<NC, true>), dim3(n), dim3(bs), 0, stream, w, pcs, p64s, L, cl,          \
+                         keep_list);                                                                                  \
+    else if (fused)                                                                                                   \
+      hipLaunchKernelGGL((render_fused_kernel<NC, false>), dim3(n), dim3(bs), 0, stream, w, pcs, p64s, L, cl, false); \
+    else if (ppt == 2)                                                                                                \
+      hipLaunchKernelGGL((render_kernel<NC, 2>), dim3(n), dim3(bs), 0, stream, w, pcs, L, cl);                        \
+    else                                                                                                              \
+      hipLaunchKernelGGL((render_kernel<NC, 1>), dim3(n), dim3(bs), 0, stream, w, pcs, L, cl);                        \
+    break;
     LENSED_RENDER_CLASS(1)
     LENSED_RENDER_CLASS(2)
     LENSED_RENDER_CLASS(3)
@@ -468,9 +444,49 @@ hipError_t launch_render(const WorkArgs& w, const PointConst* pcs, const PointCo
     LENSED_RENDER_CLASS(7)
     LENSED_RENDER_CLASS(8)
 #undef LENSED_RENDER_CLASS
-    default: hipLaunchKernelGGL((render_single_kernel<0>), grid, block, 0, stream, w, pcs, p64s, L); break;
+    default:
+      if (fused && w.items)
+        hipLaunchKernelGGL((render_fused_kernel<0, true>), dim3(n), dim3(bs), 0, stream, w, pcs, p64s, L, cl, keep_list);
+      else if (fused)
+        hipLaunchKernelGGL((render_fused_kernel<0, false>), dim3(n), dim3(bs), 0, stream, w, pcs, p64s, L, cl, false);
+      else
+        hipLaunchKernelGGL((render_kernel<0, 1>), dim3(n), dim3(bs), 0, stream, w, pcs, L, cl);
+      break;
   }
   return hipGetLastError();
+}
+
+hipError_t launch_render(const WorkArgs& w, const PointConst* pcs, const PointConst64* p64s, float* L,
+                         const RenderSpan* spans, int n_spans, const CuspList& cl, bool keep_list, hipStream_t stream,
+                         hipEvent_t between) {
+  int n_waves = 0;   // cusp-list capacity: one entry per wave and pixel of a thread
+  for (int i = 0; i < n_spans; ++i) n_waves += spans[i].count * (spans[i].block / 64) * (spans[i].ppt == 2 ? 2 : 1);
+  if (n_waves <= 0) return hipSuccess;
+  const bool fused = render_fused(spans, n_spans);
+  for (int i = 0; i < n_spans; ++i) {
+    if (spans[i].count <= 0) continue;
+    WorkArgs ws = w;
+    if (ws.items) ws.items += spans[i].offset;
+    const int bs = spans[i].block;
+    if (bs < 64 || bs > RENDER_BLOCK_MAX || bs % 64 != 0) return hipErrorInvalidValue;
+    const hipError_t e = for_item_parts(ws, spans[i].count, [&](const WorkArgs& part, int n) {
+      return launch_render_class(spans[i].klass, spans[i].ppt, fused, n, bs, part, pcs, p64s, L, cl, keep_list, stream);
+    });
+    if (e != hipSuccess) return e;
+  }
+  hipError_t e;
+  if (between && (e = hipEventRecord(between, stream)) != hipSuccess) return e;
+  if (fused) return hipSuccess;
+  int grid = (n_waves + CUSP_WAVES - 1) / CUSP_WAVES;
+  if (grid > CUSP_BLOCKS) grid = CUSP_BLOCKS;
+  hipLaunchKernelGGL(cusp_kernel, dim3(grid), dim3(64 * CUSP_WAVES), 0, stream, w, pcs, p64s, L, cl);
+  return hipGetLastError();
+}
+
+hipError_t launch_render(const WorkArgs& w, const PointConst* pcs, const PointConst64* p64s, float* L, int n_blocks,
+                         const CuspList& cl, hipStream_t stream) {
+  const RenderSpan span{render_class(w.single), 1, 0, n_blocks, RENDER_BLOCK};
+  return launch_render(w, pcs, p64s, L, &span, 1, cl, false, stream);
 }
 
 }  // namespace lensed

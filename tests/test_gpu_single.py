@@ -61,3 +61,19 @@ def test_the_largest_single_image(h, w):
     batch = lensed.loglike_batch(tp, np.zeros(3, np.int32), [gsys]).cpu().numpy()
     for i in range(3):
         assert abs(float(lensed.loglike(tp[i], gsys)) - batch[i]) <= 1e-12 * abs(batch[i])
+
+
+def test_both_sides_of_the_fused_render():
+    """64 points of 64 x 64 pixels are 4096 waves, the most that correct their own pixels
+    as they render; a 65th point takes the list and its kernel. The same log L, and the
+    same gradient to the order of the corrections' sums (both in float64: 1e-6 of the norm)."""
+    spec = small_spec(H=64, W=64)
+    obs = small_obs(spec)
+    pts = mocks.points(spec, 65, seed=11).astype(np.float32)
+    pts[::2, 14] = 3.5   # cuspy sources
+    tp = torch.from_numpy(pts).to(DEV)
+    gsys = gpu_system(spec, obs)
+    ll64, g64 = lensed.loglike_grad(tp[:64].contiguous(), gsys)
+    ll65, g65 = lensed.loglike_grad(tp, gsys)
+    assert torch.equal(ll64, ll65[:64])
+    assert torch.all((g64 - g65[:64]).norm(dim=1) <= 1e-6 * g64.norm(dim=1))
