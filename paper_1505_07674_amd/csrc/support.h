@@ -9,6 +9,7 @@
 #pragma once
 
 #include "internal.h"
+#include "kernels.h"
 
 namespace lensed {
 
