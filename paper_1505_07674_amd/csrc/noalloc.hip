@@ -6,6 +6,7 @@
 // stand-in, not a device address: the address of each device's copy comes from
 // hipGetSymbolAddress, once per device with that device current, and only that
 // pointer is handed to the kernels.
+#include <algorithm>
 #include <cstring>
 #include <mutex>
 
@@ -48,12 +49,14 @@ extern "C" int lensed_loglike_noalloc(const lensed_system* sys, const float* the
   const size_t off_psf = up256(off_p64 + sizeof(PointConst64));
   const size_t off_cc = up256(off_psf + 3 * sizeof(float) * sd.ph * sd.pw);
   const size_t off_ce = up256(off_cc + 2 * sizeof(int));
-  const size_t off_L = up256(off_ce + sizeof(CuspEntry) * (size_t)sd.n_rtiles * (RENDER_BLOCK / 64));
-  // the per-tile sums take the place of the cusp work list, which the PSF stage no
-  // longer needs (every tile has at least 128 pixels, and the list 24 bytes per 64)
+  // the per-tile sums share the space of the cusp work list, which the PSF stage no
+  // longer needs. The list is 24 bytes per 64 pixels and a sum 8 bytes per tile: a
+  // whole tile has at least 128 pixels, but the ragged tiles of an image of one or two
+  // rows or columns have as few as 8, and their sums need more than the list.
   const size_t off_part = off_ce;
+  const size_t off_L = off_ce + std::max(up256(sizeof(CuspEntry) * (size_t)sd.n_rtiles * (RENDER_BLOCK / 64)),
+                                         up256(sizeof(float2) * (size_t)sd.n_ptiles));
   const size_t total = up256(off_L + sizeof(float) * npix);
-  if (sizeof(float2) * sd.n_ptiles > off_L - off_ce) return LENSED_INVALID_ARGUMENT;
   if (total > (size_t)LENSED_NOALLOC_SCRATCH_BYTES) return LENSED_TOO_LARGE;
 
   char* base = (char*)scratch_ptr[dev];

@@ -1,0 +1,39 @@
+"""Images of one or two rows or columns through lensed_loglike_noalloc: their ragged
+PSF tiles hold as few as 8 pixels, so the tile sums can need more of the static
+workspace than the work list whose place they take. Every such image is taken, with the
+log L of lensed_loglike, bit for bit; only what exceeds the workspace is refused."""
+import numpy as np
+import pytest
+import torch
+
+import paper_1505_07674_amd as lensed
+from paper_1505_07674_amd import mocks
+
+from test_zz_no_alloc import LENSED_TOO_LARGE, noalloc
+
+pytestmark = pytest.mark.gpu
+DEV = torch.device("cuda:0")
+
+
+def thin(h, w):
+    rng = np.random.default_rng(h + 3 * w)
+    data = torch.from_numpy(rng.uniform(0, 1, (h, w)).astype(np.float32)).to(DEV)
+    return lensed.System(torch.ones((3, 3), device=DEV), data, torch.ones_like(data), pixscale=0.02, nsub=1)
+
+
+# both sides of the change of tiles at 2^14 pixels and of the single-image tiles at 2^18
+@pytest.mark.parametrize("h,w", [(1, 1), (1, 2048), (1, 16384), (1, 16385), (1, 1 << 18), (1, (1 << 18) + 1), (2, 9000),
+                                 (300, 1), (1000, 2), (16384, 1), (16385, 1), (1 << 18, 1), ((1 << 18) + 1, 1)])
+def test_thin_images_are_taken(h, w):
+    print(f"noalloc, {h} x {w} pixels", flush=True)
+    system = thin(h, w)
+    theta = torch.from_numpy(mocks.c1_spec().truth).to(DEV)
+    want = lensed.loglike(theta, system)
+    rc, got = noalloc(theta, system)
+    assert rc == 0 and torch.isfinite(want).all() and torch.equal(got, want)
+
+
+@pytest.mark.parametrize("h,w", [(1, 1600000), (1600000, 1)])
+def test_only_the_workspace_limits_them(h, w):
+    rc, got = noalloc(torch.from_numpy(mocks.c1_spec().truth).to(DEV), thin(h, w))
+    assert rc == LENSED_TOO_LARGE and torch.isnan(got).all()
