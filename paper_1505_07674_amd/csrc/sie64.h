@@ -44,7 +44,10 @@ __device__ __forceinline__ double rcp64(double a) {
 // The SIE in its own frame: (a, b) with alpha' = f (a, b), at the offset (xp, yp)
 // from its centre; f = k in closed form, theta_E sqrt(q) in the series. x'^2 carries
 // SIE_TINY64, so that at the centre itself the arguments are 0 and so is the
-// deflection; anywhere else it is below float64 resolution.
+// deflection; anywhere else (|x'| > 1e-32) it is below float64 resolution. The smallest
+// product there is 2 q^3 SIE_TINY64^(3/2) under the closed form's reciprocal: a normal
+// number for every float32 q > 0 (down to 1.4e-45), since a subnormal's reciprocal is
+// infinite and the deflection would be 0 x inf.
 //   closed   a = atan(q' x'/psi) as the angle of (psi, q'|x'|), reduced by 0, pi/4 or
 //            pi/2 to an argument within tan(pi/8); b = atanh(q' y'/psi) =
 //            1/2 ln(P/M), P = psi + q'|y'|, M = psi - q'|y'|, with P M = q^2 r^2, so
@@ -55,7 +58,7 @@ __device__ __forceinline__ double rcp64(double a) {
 //   series   a = u F(-(1 - q^2) u^2), b = v F((1 - q^2) v^2), u = x'/psi, v = y'/psi, the
 //            same functions divided by q', through q = 1.
 // Errors: a few 1e-16 in a and b.
-constexpr double SIE_TINY64 = 1e-200;
+constexpr double SIE_TINY64 = 1e-80;
 struct SieAB {
   double a, b, psi2, r2, rs;   // rs = 1/psi
 };
