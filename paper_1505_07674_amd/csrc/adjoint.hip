@@ -264,8 +264,8 @@ __device__ __forceinline__ float sersic_moments(float X, float Y, float e, float
 // choice of the series in s. With AT, (oX, oY) is the source frame instead of
 // the float32 lens equation (the float64 re-traced value near a cuspy source);
 // without LIGHT the lens light is left out.
-// x'^2 carries SIE_TINY so that the lens centre needs no branch, as in the
-// forward render. With G = D (gXx X + gYx Y, gXy X + gYy Y), which is dI/d beta
+// x'^2 carries U.tiny so that the lens centre needs no branch, as in the forward
+// render. With G = D (gXx X + gYx Y, gXy X + gYy Y), which is dI/d beta
 // in the SIE frame up to the per-point factor -2 I_e b e:
 //   0: a Gx + b Gy   1: the q derivative beyond moment 0   2: (v0 - b) Gx + (a - u0) Gy
 //   3: Gx x' - Gy y'   4: Gx y' + Gy x'   5, 6: G   7..11 lens light, 12..16 source:
@@ -280,7 +280,7 @@ __device__ __forceinline__ void subsample_grad(const GradUniform& U, const GradR
   const float xp = fmaf(U.cL, x, row.sLy);
   const float yp = fmaf(-U.sL, x, row.cLy);
   const float yp2 = yp * yp;
-  const float x2t = fmaf(xp, xp, SIE_TINY);
+  const float x2t = fmaf(xp, xp, U.tiny);
   const float r2 = x2t + yp2;
   const float psi2 = RM == 0 ? r2 : fmaf(U.q2, x2t, yp2);
   const float ip = hw_rsq(psi2);

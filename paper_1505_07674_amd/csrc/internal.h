@@ -109,6 +109,7 @@ static_assert(sizeof(PointConst64) == 16 * 8, "PointConst64 layout");
 // each with R^2/R_e^2 = X^2 + Y^2.
 struct GradUniform {
   float cL, sL, q2, qp;
+  float tiny;                 // added to x'^2: q2 tiny, psi^2 at the lens centre, is a normal number (GRAD_PSI2_MIN)
   float A1, A2, B1, B2, C1, C2;
   float Xa, Xb, Ya, Yb;
   float gXx, gYx, gXy, gYy;   // d(R^2/R_e^2)/d beta in the SIE frame: 2 (gXx X + gYx Y, gXy X + gYy Y)
@@ -123,6 +124,11 @@ struct GradUniform {
 };
 // 1 - q^2 below which d/ds of a and b takes the series.
 constexpr double GRAD_SERIES_S = 0.0625;
+// Added to x'^2 in the SIE frame (arcsec^2), so that the lens centre needs no branch.
+constexpr float SIE_TINY = 1e-30f;
+// Least psi^2 of the gradient: ten times the smallest normal float32, since the hardware's rsq takes a
+// subnormal for 0 and x'/psi at the centre would be 0 x inf.
+constexpr double GRAD_PSI2_MIN = 1.2e-37;
 
 // Extra per-point values needed by the adjoint.
 struct GradConst {
@@ -142,7 +148,7 @@ struct GradConst {
   float src_jac[14];
   int srcpos;
   GradUniform u;
-  float pad[16];
+  float pad[15];
 };
 static_assert(sizeof(GradConst) == 112 * 4, "GradConst layout");
 

@@ -533,7 +533,11 @@ __global__ __launch_bounds__(PROLOGUE_THREADS) void prologue_kernel(
       const double tesq = te * s.comp[C_SIE][5], qp2 = qp * qp;
       u.cL = (float)cL;
       u.sL = (float)sL;
-      u.q2 = (float)(q * q);
+      // the render's SIE_TINY; more below q = 3.5e-4 (1.2e-25 at 1e-6), and q^2 itself is held up
+      // where the most is too little (q < 3.5e-12)
+      const double tiny = fmin(fmax((double)SIE_TINY, GRAD_PSI2_MIN / (q * q)), 1e-14);
+      u.tiny = (float)tiny;
+      u.q2 = (float)fmax(q * q, GRAD_PSI2_MIN / tiny);
       u.qp = (float)qp;
       u.A1 = (float)f[5];
       u.A2 = (float)f[6];

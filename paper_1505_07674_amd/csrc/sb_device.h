@@ -81,8 +81,6 @@ __device__ __forceinline__ void source_offset_f64(const PointConst64& e, const P
 // ---------------------------------------------------------------------------
 
 // Terms of the subsample grid that depend on the row (y) only.
-constexpr float SIE_TINY = 1e-30f;
-
 struct RowTerms {
   float y2t;          // sphere: y^2 + SIE_TINY
   float sLy, cLy;     // SIE frame: x' = cL x + sL y, y' = cL y - sL x

@@ -13,7 +13,8 @@ import oracle
 import paper_1505_07674_amd as lensed
 from paper_1505_07674_amd import mocks
 
-from test_gpu_grad import gpu_system, small_obs, small_spec
+from helpers import f32
+from test_gpu_grad import gpu_system, oracle_grads, small_obs, small_spec
 from test_gpu_model import gsys, models, osys
 from test_gpu_model_grad import fd_grad, mock
 
@@ -64,3 +65,28 @@ def test_retraced_centre(q):
     t[1], t[10:12], t[14] = q, 0.0, 4.0
     img = lensed.render(to(t), gpu_system(spec, small_obs(spec)))
     assert torch.isfinite(img).all()
+
+
+@pytest.mark.parametrize("rule", ["sub", "g3k7"])
+def test_gradient_17_parameters(rule):
+    """The float32 gradient, whose psi^2 = q^2 (x'^2 + tiny) at the centre has to be a normal
+    float32 too; 1e-4 of the oracle's norm (test_gpu_grad.py)."""
+    qs = [0.05, 1e-2, 1e-3, 4e-4, 3e-4, 1e-4, 5e-5, 1e-5, 1e-6, 1e-9, 1e-13, 1e-30]
+    spec = small_spec(H=31, W=29, N=1, center=(0.0, 0.0))
+    obs = small_obs(spec)
+    pts = mocks.points(spec, len(qs), seed=5).astype(np.float32)
+    pts[:, 1] = qs
+    gs = lensed.System(to(spec.psf), to(obs.data), to(obs.weight), pixscale=spec.pixscale, nsub=1, rule=rule)
+    o = oracle.System(spec.height, spec.width, f32(spec.pixscale), 1, spec.psf.astype(np.float64),
+                      obs.data.astype(np.float64), obs.weight.astype(np.float64),
+                      rule=None if rule == "sub" else rule)
+    _, g = lensed.loglike_grad(to(pts), gs)
+    g = g.cpu().numpy().astype(np.float64)
+    _, want = oracle_grads(o, pts)
+    for i, q in enumerate(qs):
+        if q >= 1e-6:
+            rel = np.linalg.norm(g[i] - want[i]) / np.linalg.norm(want[i])
+            print(f"rule {rule}, q = {q}: relative gradient error {rel:.1e}", flush=True)
+            assert rel <= 1e-4
+        elif q >= 1e-19:   # below, 1/q^2 is no float32
+            assert np.isfinite(g[i]).all(), q
