@@ -48,21 +48,24 @@ typedef float f32x4 __attribute__((ext_vector_type(4)));
 __device__ __forceinline__ uint16_t f2bf(float f) { return __builtin_bit_cast(uint16_t, (__bf16)f); }
 __device__ __forceinline__ float bf2f(uint16_t h) { return __builtin_bit_cast(float, (uint32_t)h << 16); }
 
-// n / d for d in [1, 1e30]: the steps of a correctly rounded division that need no
-// scaling there (the compiler's general division takes half again as many
-// instructions, and these divisions are most of the vector work here).
+// n / d for d in [1, inf]: the steps of a correctly rounded division that need no
+// scaling for d up to 8e37 (the compiler's general division takes half again as many
+// instructions, and these divisions are most of the vector work here). Past that the
+// quotient, below 1e-35 for every n that can come with it, is off by at most itself:
+// the corrections take d as 8e37, which leaves a reciprocal of 0 at 0. d = inf gives
+// n x 0, as the division does for finite n (0) and for n = -inf (NaN); n = +inf with
+// d = 1 stands as the largest float32, which rounds to inf in bfloat16.
 __device__ __forceinline__ float div_unscaled(float n, float d) {
+  const float dc = fminf(d, 8e37f);
   float r = __builtin_amdgcn_rcpf(d);
-  r = fmaf(fmaf(-d, r, 1.0f), r, r);
+  r = fmaf(fmaf(-dc, r, 1.0f), r, r);
   float q = n * r;
-  q = fmaf(fmaf(-d, q, n), r, q);
-  return fmaf(fmaf(-d, q, n), r, q);
+  q = fmaf(fmaf(-dc, q, n), r, q);
+  return fmaf(fmaf(-dc, q, n), r, q);
 }
-// 1 + exp(-z), kept finite (past z = -69 it only makes a quotient below 1e-28).
-__device__ __forceinline__ float one_plus_exp(float z) { return 1.0f + fminf(__expf(-z), 1e30f); }
-__device__ __forceinline__ float silu(float z) { return div_unscaled(z, one_plus_exp(z)); }
+__device__ __forceinline__ float silu(float z) { return div_unscaled(fminf(z, 3.402823466e38f), 1.0f + __expf(-z)); }
 __device__ __forceinline__ float dsilu(float z) {
-  const float s = div_unscaled(1.0f, one_plus_exp(z));
+  const float s = div_unscaled(1.0f, 1.0f + __expf(-z));
   return s * (1.0f + z * (1.0f - s));
 }
 
