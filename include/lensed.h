@@ -184,9 +184,11 @@ int lensed_loglike_noalloc(const lensed_system* sys, const float* theta, double*
  * keyed by the systems, the mapping and the theta/logl pointers. The first call
  * for a new set of system shapes also autotunes the schedule: it times the PSF +
  * chi^2 stage of the cost model's six best-ranked tile shapes, then the render
- * kernels with one and with two pixels per thread in blocks of 128, 256 and
- * 512 threads, on this launch (synchronising `stream`), and keeps the fastest
- * for every later plan over the same shapes; LENSED_NO_AUTOTUNE=1 in the
+ * and its cusp corrections with one and with two pixels per thread in blocks of
+ * 128, 256 and 512 threads, on this launch (synchronising `stream`), and keeps the
+ * fastest for every later plan over the same shapes (the render schedule apart for
+ * launches of few waves, which can correct their pixels as they render, and for
+ * larger ones); LENSED_NO_AUTOTUNE=1 in the
  * environment keeps the model's tile and one pixel per thread in 256-thread
  * blocks, LENSED_RENDER_PPT=1 or 2 and LENSED_RENDER_BLOCK=128, 256 or 512
  * (read by lensed_create) fix the render schedule. Every schedule gives the
@@ -446,7 +448,8 @@ int lensed_mlp_train_step(lensed_ctx* ctx, float* params, float* m, float* v, in
  * without the captured graph and records a hipEvent between consecutive stages
  * on `stream`. lensed_stage_times waits for the recorded events and returns,
  * summed over the profiled calls since the previous query, the milliseconds of
- *   ms[0] prologue, ms[1] render kernel, ms[2] float64 cusp corrections,
+ *   ms[0] prologue, ms[1] render kernel, ms[2] float64 cusp corrections (in ms[1]
+ *   instead where a launch of few waves makes them in the render kernel),
  *   ms[3] PSF + chi^2, ms[4] finalize,
  * and for lensed_loglike_grad (also profiled) ms[5] A^T rho (the transposed
  * PSF), ms[6] the per-subsample gradient kernel, ms[7] its float64 cusp

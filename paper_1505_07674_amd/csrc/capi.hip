@@ -39,6 +39,12 @@ struct lensed_ctx {
   bool autotune = true;             // time the best-ranked tile shapes on the first batch of a shape set
   int force_ppt = 0;                // 1 or 2: render pixels per thread fixed (not timed)
   int force_block = 0;              // 128, 256 or 512: render threads per block fixed (not timed)
+  // The fixed render schedule in *r, or nullptr when none is fixed.
+  lensed::RenderSchedule* fixed_schedule(lensed::RenderSchedule* r) const {
+    if (!force_ppt && !force_block) return nullptr;
+    *r = lensed::RenderSchedule{force_ppt ? force_ppt : 1, force_block ? force_block : lensed::RENDER_BLOCK};
+    return r;
+  }
   std::vector<std::unique_ptr<BatchPlan>> plans;   // most recently used last
   TileCache tiles;
   bool profiling = false;                          // per-stage hipEvents, no graphs
@@ -469,33 +475,34 @@ int run_batch(lensed_ctx* c, const lensed_system* systems, int n_systems, const 
       }
       c->tiles.set_measured(systems, n_systems, best);
     }
-    if (model) {
-      // the general-model render takes one pixel per thread in 256-thread blocks
-      c->tiles.set_render_measured(systems, n_systems, RenderSchedule{1, RENDER_BLOCK});
-    } else if (c->force_ppt || c->force_block) {
-      c->tiles.set_render_measured(systems, n_systems,
-                                   RenderSchedule{c->force_ppt ? c->force_ppt : 1,
-                                                  c->force_block ? c->force_block : RENDER_BLOCK});
-    } else if (c->autotune && !c->tiles.has_render_measured(systems, n_systems)) {
+    // the render schedule: fixed by LENSED_RENDER_PPT or LENSED_RENDER_BLOCK, else measured
+    RenderSchedule fixed, *fix = c->fixed_schedule(&fixed);
+    std::unique_ptr<BatchPlan> np(new BatchPlan());
+    std::string msg;
+    auto build = [&] {
+      return np->build(systems, n_systems, theta, system_of_point, n_points, logl, c->tiles, msg, nullptr, nullptr, K,
+                       sky, G, model, params_per_point, fix, masked);
+    };
+    hipError_t e = build();
+    if (e == hipSuccess && !model && !fix && c->autotune &&
+        !c->tiles.has_render_measured(systems, n_systems, np->fusable())) {
       // Render schedule: one or two pixels per thread (two share the row terms
       // of the subsample grid) in blocks of 128, 256 or 512 threads, timed the
-      // same way on this launch's render kernels.
+      // same way on this launch's render and cusp corrections (some schedules make
+      // the corrections in the render kernels, the others after them).
+      const bool fusable = np->fusable(), pairs = np->max_ppt() == 2;
+      np.reset(new BatchPlan());   // its scratch, before the trials take theirs
       RenderSchedule best{1, RENDER_BLOCK};
       float best_ms = 1e30f;
-      bool pairs = true;
-      for (int ppt = 1; ppt <= 2 && pairs; ++ppt) {
-        for (const int bs : {128, 256, 512}) {
+      for (int ppt = 1; ppt <= (pairs ? 2 : 1); ++ppt) {
+        for (const int bs : {RENDER_BLOCK_MIN, 256, RENDER_BLOCK_MAX}) {
           const RenderSchedule cand{ppt, bs};
           BatchPlan trial;
-          std::string msg;
-          if (trial.build(systems, n_systems, theta, system_of_point, n_points, logl, c->tiles, msg, nullptr, nullptr,
+          std::string tmsg;
+          if (trial.build(systems, n_systems, theta, system_of_point, n_points, logl, c->tiles, tmsg, nullptr, nullptr,
                           K, sky, G, model, params_per_point, &cand, masked) != hipSuccess) {
             (void)hipGetLastError();
             continue;
-          }
-          if (ppt == 2 && trial.max_ppt() < 2) {   // no class of this launch takes two pixels
-            pairs = false;
-            break;
           }
           float ms = 0.0f;
           LENSED_HIP(c, trial.render_ms((hipStream_t)stream, &ms));
@@ -505,12 +512,9 @@ int run_batch(lensed_ctx* c, const lensed_system* systems, int n_systems, const 
           }
         }
       }
-      c->tiles.set_render_measured(systems, n_systems, best);
+      c->tiles.set_render_measured(systems, n_systems, fusable, best);
+      e = build();
     }
-    std::unique_ptr<BatchPlan> np(new BatchPlan());
-    std::string msg;
-    hipError_t e = np->build(systems, n_systems, theta, system_of_point, n_points, logl, c->tiles, msg, nullptr,
-                             nullptr, K, sky, G, model, params_per_point, nullptr, masked);
     if (e != hipSuccess) return hip_fail(c, e, ("batch plan: " + msg).c_str());
     if (c->use_graphs) {
       e = np->capture(c->cap);
@@ -809,15 +813,14 @@ static int run_grad(lensed_ctx* c, const lensed_system* sys, const float* theta,
       LENSED_HIP(c, hipDeviceSynchronize());
       c->plans.erase(c->plans.begin());
     }
-    // the render schedule: as fixed by LENSED_RENDER_PPT, else as measured for
-    // these shapes by a batched call (one pixel per thread when none was)
-    if (c->force_ppt || c->force_block)
-      c->tiles.set_render_measured(sys, 1, RenderSchedule{c->force_ppt ? c->force_ppt : 1,
-                                                         c->force_block ? c->force_block : RENDER_BLOCK});
+    // the render schedule: as fixed by LENSED_RENDER_PPT or LENSED_RENDER_BLOCK, else as
+    // measured for these shapes by a batched call that is fusable or not, as this one is
+    // (one pixel per thread when none was)
+    RenderSchedule fixed, *fix = c->fixed_schedule(&fixed);
     std::unique_ptr<BatchPlan> np(new BatchPlan());
     std::string msg;
     hipError_t e = np->build(sys, 1, theta, map.data(), n_points, logl, c->tiles, msg, grad, nullptr, K, sky, 1,
-                             spec, params_per_point, nullptr, false, grad_sky);
+                             spec, params_per_point, fix, false, grad_sky);
     if (e != hipSuccess) return hip_fail(c, e, ("gradient plan: " + msg).c_str());
     if (c->use_graphs) {
       e = np->capture(c->cap);

@@ -79,7 +79,7 @@ int render_class(const SysDesc& sd);
 struct RenderSpan {
   int klass, ppt, offset, count, block;
 };
-constexpr int RENDER_BLOCK_MAX = 512;
+constexpr int RENDER_BLOCK_MIN = 128, RENDER_BLOCK_MAX = 512;   // threads per block of the schedules
 // A render schedule: pixels per thread and threads per block.
 struct RenderSchedule {
   int ppt, block;

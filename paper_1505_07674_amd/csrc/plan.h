@@ -39,20 +39,26 @@ class TileCache {
   void set_measured(const lensed_system* s, int n, TileShape t) { measured_[key(s, n)] = t; }
   // Render schedule (pixels per thread of the midpoint classes, threads per
   // block): the measured choice for this set of image sizes and rules, else one
-  // pixel per thread in RENDER_BLOCK-thread blocks.
-  RenderSchedule render_schedule(const lensed_system* s, int n) const {
-    auto it = render_measured_.find(render_key(s, n));
+  // pixel per thread in RENDER_BLOCK-thread blocks. Launches that can correct their
+  // pixels as they render (fusable: few waves) and larger ones are measured apart: the
+  // one wants many small waves in one kernel, the other pairs or large blocks.
+  RenderSchedule render_schedule(const lensed_system* s, int n, bool fusable) const {
+    auto it = render_measured_.find(render_key(s, n, fusable));
     return it == render_measured_.end() ? RenderSchedule{1, RENDER_BLOCK} : it->second;
   }
-  bool has_render_measured(const lensed_system* s, int n) const { return render_measured_.count(render_key(s, n)) != 0; }
-  void set_render_measured(const lensed_system* s, int n, RenderSchedule r) { render_measured_[render_key(s, n)] = r; }
+  bool has_render_measured(const lensed_system* s, int n, bool fusable) const {
+    return render_measured_.count(render_key(s, n, fusable)) != 0;
+  }
+  void set_render_measured(const lensed_system* s, int n, bool fusable, RenderSchedule r) {
+    render_measured_[render_key(s, n, fusable)] = r;
+  }
   static double model_cost(int H, int W, int ph, int pw, TileShape t, int max_ph);
   // The cost model's best tile for one system (no cache, no allocation).
   static TileShape model_best(const lensed_system& s);
 
  private:
   static std::string key(const lensed_system* s, int n);
-  static std::string render_key(const lensed_system* s, int n);
+  static std::string render_key(const lensed_system* s, int n, bool fusable);
   std::map<std::tuple<int, int, int, int>, TileShape> cache_;
   std::map<std::string, TileShape> measured_;
   std::map<std::string, RenderSchedule> render_measured_;
@@ -92,9 +98,12 @@ class BatchPlan {
                    const RenderSchedule* force_render = nullptr, bool masked = false,
                    float* grad_sky = nullptr);
   // Runs the plan stage by stage (a warm-up, then three timed runs) and returns
-  // the fastest PSF + chi^2 stage, or the fastest render kernels, in milliseconds.
-  hipError_t psf_ms(hipStream_t s, float* ms) const { return stage_ms(s, 3, ms); }
-  hipError_t render_ms(hipStream_t s, float* ms) const { return stage_ms(s, 1, ms); }
+  // the fastest PSF + chi^2 stage, or the fastest render with its cusp corrections
+  // (in the render kernels or after them, as the schedule has it), in milliseconds.
+  hipError_t psf_ms(hipStream_t s, float* ms) const { return stage_ms(s, 3, 4, ms); }
+  hipError_t render_ms(hipStream_t s, float* ms) const { return stage_ms(s, 1, 3, ms); }
+  // Whether some schedule renders this plan with the corrections in its kernels.
+  bool fusable() const { return fusable_; }
   // The most pixels per thread a render class of this plan could take (1 or 2).
   int max_ppt() const { return max_ppt_; }
   // The schedule in use: PSF tile, pixels per thread of the midpoint classes and
@@ -106,7 +115,8 @@ class BatchPlan {
   int64_t rendered_subsamples() const { return rendered_subsamples_; }
   hipError_t capture(hipStream_t cap);
   // events, when given, are LENSED_NSTAGES + 1 events recorded around the stages
-  // (prologue, render kernel, cusp corrections and composition, PSF + chi^2,
+  // (prologue, render kernel with the cusp corrections where it makes them itself
+  // (render_fused), else those corrections, with the composition, PSF + chi^2,
   // finalize; with a gradient A^T rho, gradient kernel, its cusp corrections and sums)
   hipError_t enqueue(hipStream_t s, hipEvent_t* events = nullptr) const;
   hipError_t run(hipStream_t s) const;
@@ -163,10 +173,11 @@ class BatchPlan {
   int rbs_ = RENDER_BLOCK;        // threads (render units) per render block
   SupportSizes support_;          // of a gradient plan
   int max_ppt_ = 1;
+  bool fusable_ = false;
   bool masked_ = false;
   int64_t rendered_pixels_ = 0;   // pixels the render stage computes per launch
   int64_t rendered_subsamples_ = 0;
-  hipError_t stage_ms(hipStream_t s, int stage, float* ms) const;
+  hipError_t stage_ms(hipStream_t s, int first, int last, float* ms) const;
 };
 
 }  // namespace lensed

@@ -85,14 +85,14 @@ std::string TileCache::key(const lensed_system* s, int n) {
   return k;
 }
 
-std::string TileCache::render_key(const lensed_system* s, int n) {
+std::string TileCache::render_key(const lensed_system* s, int n, bool fusable) {
   std::vector<std::string> parts;
   for (int i = 0; i < n; ++i)
     parts.push_back(std::to_string(s[i].height) + "x" + std::to_string(s[i].width) + "n" + std::to_string(s[i].nsub) +
                     "r" + std::to_string(s[i].rule));
   std::sort(parts.begin(), parts.end());
   parts.erase(std::unique(parts.begin(), parts.end()), parts.end());
-  std::string k;
+  std::string k = fusable ? "f:" : "";
   for (const auto& p : parts) k += p + ";";
   return k;
 }
@@ -199,13 +199,9 @@ hipError_t BatchPlan::build(const lensed_system* systems, int n_systems, const f
   }
 
   // Pixels per render thread: two for a midpoint class whose images all have
-  // an even width (a pair never straddles two rows), if the schedule says so;
+  // an even width (a pair never straddles two rows), if the schedule, below, says so;
   // general-model plans keep one (their kernel walks one pixel per thread). The
   // gradient kernels have item lists of their own.
-  const RenderSchedule rs = force_render ? *force_render : tiles.render_schedule(systems, n_systems);
-  ppt_ = rs.ppt == 2 ? 2 : 1;
-  rbs_ = rs.block >= 64 && rs.block <= RENDER_BLOCK_MAX && rs.block % 64 == 0 ? rs.block : RENDER_BLOCK;
-  if (model) ppt_ = 1, rbs_ = RENDER_BLOCK;   // the general-model render walks 256-pixel tiles
   std::vector<int> class_div(RENDER_MAX_CLASS + 1, 2);   // pixels per thread each class allows
   class_div[0] = 1;
   for (int s = 0; s < n_systems; ++s)
@@ -213,7 +209,6 @@ hipError_t BatchPlan::build(const lensed_system* systems, int n_systems, const f
   max_ppt_ = 1;
   if (!model)
     for (int s = 0; s < n_systems; ++s) max_ppt_ = std::max(max_ppt_, class_div[render_class(desc[s])]);
-  auto class_ppt = [&](int klass) { return std::min(ppt_, class_div[klass]); };
 
   // Masked plans: per system, the render units the chi^2 can see and the PSF
   // tiles that hold a pixel with w > 0 (from the weights, read back once here).
@@ -221,7 +216,9 @@ hipError_t BatchPlan::build(const lensed_system* systems, int n_systems, const f
   // borders, so the pixels needed are the w > 0 support dilated by that box.
   masked_ = masked && !grad && !model;
   std::vector<std::vector<int>> units(n_systems);
-  std::vector<std::vector<char>> ptile_on(n_systems);
+  std::vector<std::vector<char>> needed(n_systems), ptile_on(n_systems);
+  std::vector<int64_t> rendered(n_systems);   // pixels of an image that are rendered
+  for (int s = 0; s < n_systems; ++s) rendered[s] = (int64_t)desc[s].H * desc[s].W;
   if (masked_) {
     for (int s = 0; s < n_systems; ++s) {
       const SysDesc& d = desc[s];
@@ -234,7 +231,8 @@ hipError_t BatchPlan::build(const lensed_system* systems, int n_systems, const f
       }
       const int p = d.ph / 2, q = d.pw / 2;
       // separable box dilation: distance to the nearest marked pixel along rows, then along columns
-      std::vector<char> rowd(npx, 0), need(npx, 0);
+      std::vector<char> rowd(npx, 0), &need = needed[s];
+      need.assign(npx, 0);
       std::vector<int> nxt(std::max(d.H, d.W) + 1);
       for (int r = 0; r < d.H; ++r) {
         const float* wr = &w[(size_t)r * d.W];
@@ -255,15 +253,31 @@ hipError_t BatchPlan::build(const lensed_system* systems, int n_systems, const f
           need[(size_t)r * d.W + c] = (r - last <= p) || (nxt[r] - r <= p);
         }
       }
-      const int pp = class_ppt(render_class(d));
-      for (size_t pix = 0; pix < npx; pix += pp)
-        if (need[pix] || (pp == 2 && need[pix + 1])) units[s].push_back((int)pix);
+      rendered[s] = std::count(need.begin(), need.end(), 1);
       ptile_on[s].assign(d.n_ptiles, 0);
       for (int r = 0; r < d.H; ++r)
         for (int c = 0; c < d.W; ++c)
           if (w[(size_t)r * d.W + c] > 0.0f) ptile_on[s][(r / d.TH) * d.tiles_x + c / d.TW] = 1;
-      desc[s].n_active = (int)units[s].size();
     }
+  }
+
+  // The render schedule, measured apart for launches that some schedule renders with
+  // the cusp corrections in the kernel.
+  int64_t smallest_blocks = 0;
+  for (int p = 0; p < n_points; ++p) smallest_blocks += (rendered[map[p]] + RENDER_BLOCK_MIN - 1) / RENDER_BLOCK_MIN;
+  const RenderSpan smallest{0, 1, 0, (int)std::min<int64_t>(smallest_blocks, INT32_MAX), RENDER_BLOCK_MIN};
+  fusable_ = !model && render_fused(&smallest, 1);
+  const RenderSchedule rs = force_render ? *force_render : tiles.render_schedule(systems, n_systems, fusable_);
+  ppt_ = rs.ppt == 2 ? 2 : 1;
+  rbs_ = rs.block >= 64 && rs.block <= RENDER_BLOCK_MAX && rs.block % 64 == 0 ? rs.block : RENDER_BLOCK;
+  if (model) ppt_ = 1, rbs_ = RENDER_BLOCK;   // the general-model render walks 256-pixel tiles
+  auto class_ppt = [&](int klass) { return std::min(ppt_, class_div[klass]); };
+  for (int s = 0; masked_ && s < n_systems; ++s) {
+    const std::vector<char>& need = needed[s];
+    const int pp = class_ppt(render_class(desc[s]));
+    for (size_t pix = 0; pix < need.size(); pix += pp)
+      if (need[pix] || (pp == 2 && need[pix + 1])) units[s].push_back((int)pix);
+    desc[s].n_active = (int)units[s].size();
   }
   rendered_pixels_ = rendered_subsamples_ = 0;
 
@@ -593,7 +607,7 @@ hipError_t BatchPlan::capture(hipStream_t cap) {
   return hipGraphInstantiate(&exec_, graph_, nullptr, nullptr, 0);
 }
 
-hipError_t BatchPlan::stage_ms(hipStream_t s, int stage, float* ms) const {
+hipError_t BatchPlan::stage_ms(hipStream_t s, int first, int last, float* ms) const {
   hipEvent_t ev[LENSED_NSTAGES + 1] = {};
   hipError_t e = hipSuccess;
   for (auto& x : ev)
@@ -606,7 +620,7 @@ hipError_t BatchPlan::stage_ms(hipStream_t s, int stage, float* ms) const {
     e = enqueue(s, ev);
     if (e == hipSuccess) e = hipEventSynchronize(ev[LENSED_NSTAGES]);
     float t = 0.0f;
-    if (e == hipSuccess) e = hipEventElapsedTime(&t, ev[stage], ev[stage + 1]);
+    if (e == hipSuccess) e = hipEventElapsedTime(&t, ev[first], ev[last]);
     if (e == hipSuccess && t < *ms) *ms = t;
   }
   for (auto& x : ev)
