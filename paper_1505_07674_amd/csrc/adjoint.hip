@@ -524,12 +524,6 @@ constexpr int GCUSP_BLOCKS = 1024;
 // pixels flagged, took 73 us with the same re-tracing.)
 constexpr int GCUSP_CHUNK = 16;   // subsamples per pass
 
-__device__ __forceinline__ void gcusp_lds_sync() {
-  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
-  __builtin_amdgcn_wave_barrier();
-  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup");
-}
-
 __device__ __forceinline__ PixelGeom gcusp_geom(const SysDesc& sd, int pix) {
   const int r = row_of(sd, pix);
   const int col = pix - r * sd.W;
@@ -567,7 +561,7 @@ __global__ __launch_bounds__(64 * GCUSP_WAVES, 4) void grad_cusp_kernel(WorkArgs
     const GradConst& gc = gcs[point];
     const GradUniform& U = gc.u;
     if (mine) fp[__popcll(e.mask & ((1ull << lane) - 1ull))] = unit_pixel(sd, e.unit0 + lane, e.ppt) + e.half;
-    gcusp_lds_sync();
+    wave_lds_sync();
     const int N = sd.N, NN = N * N;
     const GkRule* Rg = sd.rule > 0 ? &kGkRules[sd.rule - 1] : nullptr;
     float acc[NPAR];
@@ -595,7 +589,7 @@ __global__ __launch_bounds__(64 * GCUSP_WAVES, 4) void grad_cusp_kernel(WorkArgs
         if (within) qu[qn + __popcll(bal & ((1ull << lane) - 1ull))] = (unsigned short)(f | (j << 6));
         qn += __popcll(bal);
       }
-      gcusp_lds_sync();
+      wave_lds_sync();
       for (int q0 = 0; q0 < qn; q0 += 64) {
         if (q0 + lane < qn) {
           const int item = qu[q0 + lane];
@@ -628,7 +622,7 @@ __global__ __launch_bounds__(64 * GCUSP_WAVES, 4) void grad_cusp_kernel(WorkArgs
           for (int k = 0; k < NPAR; ++k) acc[k] = fmaf(diff[k], wg, acc[k]);
         }
       }
-      gcusp_lds_sync();
+      wave_lds_sync();
     }
     // every lane of an entry belongs to the same point; a lane per moment adds its sum
     float mine_sum = 0.0f;
@@ -639,7 +633,7 @@ __global__ __launch_bounds__(64 * GCUSP_WAVES, 4) void grad_cusp_kernel(WorkArgs
       mine_sum = lane == k ? sum : mine_sum;
     }
     if (lane < NPAR && mine_sum != 0.0f) atomicAdd(&corr[(size_t)point * NPAR + lane], (double)mine_sum);
-    gcusp_lds_sync();   // the queue and the pixel list are written anew
+    wave_lds_sync();   // the queue and the pixel list are written anew
   }
 }
 

@@ -60,13 +60,10 @@ def atanh_over_v(s):
 
 
 def emit(name, coeffs, err, mean, domain):
-    c32 = np.asarray(coeffs, dtype=np.float32)
     print(f"// {name}: max relative error {err:.3e} (mean {mean:+.1e}) on {domain}, float32 coefficients")
-    print(f"#define {name}_DEGREE {len(c32) - 1}")
-    body = ", ".join(f"{float(v)!r}f" for v in c32)
-    print(f"static constexpr float {name}[{len(c32)}] = {{{body}}};")
+    print(f"#define {name}_DEGREE {len(coeffs) - 1}")
     body = ", ".join(f"{float(v)!r}" for v in coeffs)
-    print(f"static constexpr double {name}_D[{len(c32)}] = {{{body}}};")
+    print(f"static constexpr double {name}_D[{len(coeffs)}] = {{{body}}};")
 
 
 if __name__ == "__main__":

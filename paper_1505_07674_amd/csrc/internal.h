@@ -7,7 +7,6 @@
 namespace lensed {
 
 constexpr int NPAR = 17;
-constexpr float LN2F = 0.693147180559945309f;
 constexpr double LOG2E = 1.44269504088896340736;
 // Source-plane radius around a cuspy source centre inside which subsamples are
 // re-traced in float64 (the float32 ray position carries ~1e-7 arcsec of rounding).
@@ -259,6 +258,14 @@ struct CuspEntry {
 struct CuspList {
   CuspEntry* entries;   // capacity: one entry per render wave of the launch
   int* count;
-};   // pixels per render tile / threads per render block
+};
+
+// LDS written by some lanes of a wave and read by others: order the accesses
+// and wait for the writes.
+__device__ __forceinline__ void wave_lds_sync() {
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
+  __builtin_amdgcn_wave_barrier();
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup");
+}
 
 }  // namespace lensed

@@ -235,7 +235,7 @@ __global__ __launch_bounds__(RENDER_BLOCK, PLANES ? 1 : 3) void model_render_ker
 // with G = sum over the lensed Sersics of grad S_j(beta). Every partial is a
 // per-point linear combination of a few sums over the subsamples (moments), so the
 // kernel accumulates those. A pass (blockIdx.y) covers two SIEs, the first of
-// them also the shear and the sky, or four Sersics, so that a thread keeps at most 28
+// them also the shear and the sky, or two Sersics, so that a thread keeps at most 14
 // sums; the ray (every SIE) and G are evaluated once per pass.
 //
 // Several lens planes (model_grad_planes_kernel): forward-mode dual numbers, one
@@ -255,12 +255,6 @@ __device__ inline Dl<M> dconst(double v) {
   r.v = v;
 #pragma unroll
   for (int i = 0; i < M; ++i) r.d[i] = 0.0;
-  return r;
-}
-template <int M>
-__device__ inline Dl<M> dvar(double v, int k) {
-  Dl<M> r = dconst<M>(v);
-  r.d[k] = 1.0;
   return r;
 }
 // f(a) with f'(a) = fp
@@ -624,7 +618,6 @@ __device__ __forceinline__ void sie_moments(const SieConst& c, const SieAB& o, d
 }
 
 constexpr int GRAD_SIES = 2, GRAD_SERSICS = 2;   // components per pass
-constexpr int GRAD_WAYS = 1;                     // subsamples interleaved
 constexpr int GRAD_SUMS_LENS = 5 * GRAD_SIES + 3, GRAD_SUMS_LIGHT = 7 * GRAD_SERSICS;
 // Passes over the SIEs (the first also covers the shear and the sky), and in all.
 __host__ __device__ inline int grad_lens_passes(const ModelSpec& s) {
@@ -675,109 +668,80 @@ __global__ __launch_bounds__(RENDER_BLOCK, LIGHT ? 4 : 3) void model_grad_kernel
       const int jj = LIGHT ? first + j : j;
       any_lensed = any_lensed || (jj < m.n_sersic && m.plane[jj] != 0);
     }
-    // S subsamples of a row, their chains interleaved
-    auto samples = [&](int ky, int kx, auto sc) {
-      constexpr int S = decltype(sc)::value;
-      double x[S], y[S], wq[S], bx[S], by[S];
-#pragma unroll
-      for (int i = 0; i < S; ++i) {
-        x[i] = cx + (ux + rule.off[kx + i]) * d;
-        y[i] = cy + (uy + rule.off[ky]) * d;
-        wq[i] = rule.w[kx + i] * rule.w[ky];
-        bx[i] = x[i] - (m.g1 * x[i] + m.g2 * y[i]);
-        by[i] = y[i] - (m.g2 * x[i] - m.g1 * y[i]);
-      }
+    auto subsample = [&](int ky, int kx) {
+      const double x[1] = {cx + (ux + rule.off[kx]) * d}, y[1] = {cy + (uy + rule.off[ky]) * d};
+      const double wq = rule.w[kx] * rule.w[ky];
+      double bx[1] = {x[0] - (m.g1 * x[0] + m.g2 * y[0])}, by[1] = {y[0] - (m.g2 * x[0] - m.g1 * y[0])};
       if constexpr (LIGHT) {
         if (any_lensed)
-          for (int k = 0; k < m.n_sie; ++k) sub_sie<S>(m.sie[k], x, y, bx, by);
+          for (int k = 0; k < m.n_sie; ++k) sub_sie<1>(m.sie[k], x, y, bx, by);
 #pragma unroll
         for (int j = 0; j < GRAD_SERSICS; ++j) {
           if (first + j >= m.n_sersic) break;
-          const SersicConst& lc = m.ser[first + j];
           const bool lensed = m.plane[first + j] != 0;
-#pragma unroll
-          for (int i = 0; i < S; ++i) {
-            const SersicM s = sersic_moments(lc, lensed ? bx[i] : x[i], lensed ? by[i] : y[i]);
-            double* __restrict__ a = acc + 7 * j;
-            const double D = wq[i] * s.D, DX = D * s.X, DY = D * s.Y;
-            a[0] += DX;
-            a[1] += DY;
-            a[2] = fma(wq[i], s.E, a[2]);
-            a[3] = fma(DX, s.X, a[3]);
-            a[4] = fma(DY, s.Y, a[4]);
-            a[5] = fma(DX, s.Y, a[5]);
-            a[6] = fma(wq[i], s.dn, a[6]);
-          }
+          const SersicM s = sersic_moments(m.ser[first + j], lensed ? bx[0] : x[0], lensed ? by[0] : y[0]);
+          double* __restrict__ a = acc + 7 * j;
+          const double D = wq * s.D, DX = D * s.X, DY = D * s.Y;
+          a[0] += DX;
+          a[1] += DY;
+          a[2] = fma(wq, s.E, a[2]);
+          a[3] = fma(DX, s.X, a[3]);
+          a[4] = fma(DY, s.Y, a[4]);
+          a[5] = fma(DX, s.Y, a[5]);
+          a[6] = fma(wq, s.dn, a[6]);
         }
       } else {
         // the ray: the pass's own SIEs keep their deflections for the moments
-        SieAB own[GRAD_SIES][S];
-        double xp[GRAD_SIES][S], yp[GRAD_SIES][S];
+        SieAB own[GRAD_SIES];
+        double xp[GRAD_SIES], yp[GRAD_SIES];
         if (any_lensed) {
           for (int k = 0; k < m.n_sie; ++k)
-            if (k < first || k >= first + GRAD_SIES) sub_sie<S>(m.sie[k], x, y, bx, by);
+            if (k < first || k >= first + GRAD_SIES) sub_sie<1>(m.sie[k], x, y, bx, by);
 #pragma unroll
           for (int k = 0; k < GRAD_SIES; ++k) {
             if (first + k >= m.n_sie) break;
             const SieConst& lc = m.sie[first + k];
             const bool closed = lc.closed;
             const double f = closed ? lc.k : lc.tesq;
-#pragma unroll
-            for (int i = 0; i < S; ++i) {
-              const double dx = x[i] - lc.x, dy = y[i] - lc.y;
-              xp[k][i] = fma(lc.c, dx, lc.s * dy);
-              yp[k][i] = fma(lc.c, dy, -(lc.s * dx));
-              own[k][i] = closed ? sie_ab<true>(lc, xp[k][i], yp[k][i]) : sie_ab<false>(lc, xp[k][i], yp[k][i]);
-              const double a1 = f * own[k][i].a, a2 = f * own[k][i].b;
-              bx[i] -= fma(lc.c, a1, -(lc.s * a2));
-              by[i] -= fma(lc.s, a1, lc.c * a2);
-            }
+            const double dx = x[0] - lc.x, dy = y[0] - lc.y;
+            xp[k] = fma(lc.c, dx, lc.s * dy);
+            yp[k] = fma(lc.c, dy, -(lc.s * dx));
+            own[k] = closed ? sie_ab<true>(lc, xp[k], yp[k]) : sie_ab<false>(lc, xp[k], yp[k]);
+            const double a1 = f * own[k].a, a2 = f * own[k].b;
+            bx[0] -= fma(lc.c, a1, -(lc.s * a2));
+            by[0] -= fma(lc.s, a1, lc.c * a2);
           }
         }
-        double Gx[S], Gy[S];
-#pragma unroll
-        for (int i = 0; i < S; ++i) Gx[i] = Gy[i] = 0.0;
+        double Gx = 0.0, Gy = 0.0;
         if (any_lensed) {
           for (int j = 0; j < m.n_sersic; ++j)
             if (m.plane[j] != 0) {
-#pragma unroll
-              for (int i = 0; i < S; ++i) {
-                const SersicM s = sersic_moments(m.ser[j], bx[i], by[i]);
-                double gx, gy;
-                sersic_gradient(m.ser[j], s, gx, gy);
-                Gx[i] += gx;
-                Gy[i] += gy;
-              }
+              double gx, gy;
+              sersic_gradient(m.ser[j], sersic_moments(m.ser[j], bx[0], by[0]), gx, gy);
+              Gx += gx;
+              Gy += gy;
             }
 #pragma unroll
           for (int k = 0; k < GRAD_SIES; ++k) {
             if (first + k >= m.n_sie) break;
             const SieConst& lc = m.sie[first + k];
             const bool closed = lc.closed;
-#pragma unroll
-            for (int i = 0; i < S; ++i)
-              if (closed)
-                sie_moments<true>(lc, own[k][i], xp[k][i], yp[k][i], Gx[i], Gy[i], wq[i], acc + 5 * k);
-              else
-                sie_moments<false>(lc, own[k][i], xp[k][i], yp[k][i], Gx[i], Gy[i], wq[i], acc + 5 * k);
+            if (closed)
+              sie_moments<true>(lc, own[k], xp[k], yp[k], Gx, Gy, wq, acc + 5 * k);
+            else
+              sie_moments<false>(lc, own[k], xp[k], yp[k], Gx, Gy, wq, acc + 5 * k);
           }
         }
         if (extra) {
-#pragma unroll
-          for (int i = 0; i < S; ++i) {
-            // beta = x - alpha_SIE - Gamma x, Gamma = gamma [[c2, s2], [s2, -c2]]
-            acc[5 * GRAD_SIES] += wq[i] * fma(Gx[i], x[i], -(Gy[i] * y[i]));
-            acc[5 * GRAD_SIES + 1] += wq[i] * fma(Gx[i], y[i], Gy[i] * x[i]);
-            acc[5 * GRAD_SIES + 2] += wq[i];
-          }
+          // beta = x - alpha_SIE - Gamma x, Gamma = gamma [[c2, s2], [s2, -c2]]
+          acc[5 * GRAD_SIES] += wq * fma(Gx, x[0], -(Gy * y[0]));
+          acc[5 * GRAD_SIES + 1] += wq * fma(Gx, y[0], Gy * x[0]);
+          acc[5 * GRAD_SIES + 2] += wq;
         }
       }
     };
-    for (int ky = 0; ky < N; ++ky) {
-      int kx = 0;
-      for (; kx + GRAD_WAYS <= N; kx += GRAD_WAYS) samples(ky, kx, std::integral_constant<int, GRAD_WAYS>{});
-      for (; kx < N; ++kx) samples(ky, kx, std::integral_constant<int, 1>{});
-    }
+    for (int ky = 0; ky < N; ++ky)
+      for (int kx = 0; kx < N; ++kx) subsample(ky, kx);
     const double scale = (double)gp * sd.wgt;
 #pragma unroll
     for (int i = 0; i < SUMS; ++i) acc[i] *= scale;

@@ -168,14 +168,6 @@ struct Dither {
   __device__ float variant(int v) const { return frac + ((v + 0.5) / RENDER_VARIANTS - 0.5) >= 0.5 ? hi : lo; }
 };
 
-// Makes the LDS writes of a wave's lanes visible to its other lanes (the lanes
-// of a point share a wave; no other wave reads them).
-__device__ __forceinline__ void wave_sync() {
-  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
-  __builtin_amdgcn_wave_barrier();
-  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup");
-}
-
 // PSF blocks: one per system, or with the adjoint one per system and border
 // class, of PROLOGUE_THREADS threads. The PSF is normalised to unit sum in
 // float64 and stored three ways (row-major; column-major flipped, the
@@ -391,7 +383,7 @@ __global__ __launch_bounds__(PROLOGUE_THREADS) void prologue_kernel(
   }
   const double v[7] = {t[10], t[11], t[0], t[1], t[2], t[3], t[4]};
   if (valid && srcpos && (j == 14 || (ADJ && j < 14))) lens_map_lane(v, j, s.maps);
-  wave_sync();
+  wave_lds_sync();
   if (ADJ) {
     if (j < 7) {
       if (valid && srcpos)
@@ -400,7 +392,7 @@ __global__ __launch_bounds__(PROLOGUE_THREADS) void prologue_kernel(
         s.jac[j] = s.jac[7 + j] = 0.0f;
     }
     if (grad_corr && j < NPAR) grad_corr[(size_t)p * NPAR + j] = 0.0;
-    wave_sync();
+    wave_lds_sync();
   }
 
   if (j == 0) {   // the point's head, its float64 folded constants (to LDS) and the adjoint's constants
@@ -586,7 +578,7 @@ __global__ __launch_bounds__(PROLOGUE_THREADS) void prologue_kernel(
   }
   // the dithered float32 roundings of the folded constants, one set per render
   // variant: lane j of the point rounds constant j
-  wave_sync();
+  wave_lds_sync();
   const Dither d(s.folded[j]);
   float* rv = reinterpret_cast<float*>(pcs[p].rv) + j;
 #pragma unroll

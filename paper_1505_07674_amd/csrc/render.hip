@@ -147,14 +147,6 @@ struct CuspScratch {
   int pix[64];                             // the flagged pixels
 };
 
-// LDS written by some lanes of a wave and read by others: order the accesses
-// and wait for the writes.
-__device__ __forceinline__ void wave_lds_sync() {
-  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
-  __builtin_amdgcn_wave_barrier();
-  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup");
-}
-
 __device__ __forceinline__ void subsample_xy(const GkRule* R, int N, int kx, int ky, const PixelGeom& g, float& x,
                                              float& y) {
   y = R ? fmaf(g.uy + R->x[ky], g.d, g.cy) : fmaf(g.uy + sub_offset_rt(ky, N), g.d, g.cy);

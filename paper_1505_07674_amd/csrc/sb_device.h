@@ -31,20 +31,6 @@ __device__ __forceinline__ float hw_log2(float x) { return __builtin_amdgcn_logf
 __device__ __forceinline__ float hw_rsq(float x) { return __builtin_amdgcn_rsqf(x); }
 __device__ __forceinline__ float hw_rcp(float x) { return __builtin_amdgcn_rcpf(x); }
 
-template <int DEG>
-__device__ __forceinline__ float horner(const float (&c)[DEG + 1], float s) {
-  float p = c[DEG];
-#pragma unroll
-  for (int k = DEG - 1; k >= 0; --k) p = fmaf(p, s, c[k]);
-  return p;
-}
-
-__device__ __forceinline__ float atan_small(float u) {
-  return u * horner<ATAN_SMALL_POLY_DEGREE>(ATAN_SMALL_POLY, u * u);
-}
-__device__ __forceinline__ float atan_unit(float u) { return u * horner<ATAN_UNIT_POLY_DEGREE>(ATAN_UNIT_POLY, u * u); }
-__device__ __forceinline__ float atanh_poly(float v) { return v * horner<ATANH_POLY_DEGREE>(ATANH_POLY, v * v); }
-
 // Midpoint offset of subsample k of N, in pixel units: (k + 1/2)/N - 1/2.
 template <int N>
 __device__ __forceinline__ constexpr float sub_offset(int k) {

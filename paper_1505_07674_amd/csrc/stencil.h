@@ -198,7 +198,7 @@ __device__ __forceinline__ void mfma_column(const float* a, const float (*const 
 template <int KP, int Q, int C>
 __device__ __forceinline__ void stencil(const float* __restrict__ S0, const float* __restrict__ T, int ph, int pw,
                                         int cs, bool finite, f32x4_t (&acc)[C][Q]) {
-  static_assert(C == 1 || C == 2, "the column window is unrolled by C");
+  static_assert(C == 2, "the column window is unrolled by two");
   constexpr int ts = tap_stride(KP), NA = (KP + 15) / 16, NB = (KP + 4 * (Q - 1) + 3) / 4;
 #pragma unroll
   for (int c = 0; c < C; ++c)
@@ -237,20 +237,13 @@ __device__ __forceinline__ void stencil(const float* __restrict__ S0, const floa
     for (int g = 0; g < NA; ++g) a[g] = Tl[l * ts + 16 * g];
     mfma_column<Q, C>(a, w, acc, std::make_integer_sequence<int, KP>{});
   };
-  if constexpr (C == 1) {
-    for (int l = 0; l < pw; ++l) {
-      load(win[0], l);
-      column(l, {&win[0]});
-    }
-  } else {
-    load(win[0], 0);
-    for (int l = 0; l < pw; l += 2) {   // pw is odd: the last column is the first of its pair
-      load(win[1], l + 1);
-      column(l, {&win[0], &win[1]});
-      if (l + 1 >= pw) break;
-      load(win[0], l + 2);
-      column(l + 1, {&win[1], &win[0]});
-    }
+  load(win[0], 0);
+  for (int l = 0; l < pw; l += 2) {   // pw is odd: the last column is the first of its pair
+    load(win[1], l + 1);
+    column(l, {&win[0], &win[1]});
+    if (l + 1 >= pw) break;
+    load(win[0], l + 2);
+    column(l + 1, {&win[1], &win[0]});
   }
 }
 
