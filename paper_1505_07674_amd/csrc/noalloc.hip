@@ -52,7 +52,7 @@ extern "C" int lensed_loglike_noalloc(const lensed_system* sys, const float* the
   // the per-tile sums share the space of the cusp work list, which the PSF stage no
   // longer needs. The list is 24 bytes per 64 pixels and a sum 8 bytes per tile: a
   // whole tile has at least 128 pixels, but the ragged tiles of an image of one or two
-  // rows or columns have as few as 8, and their sums need more than the list.
+  // rows or columns have as few as 16, and their sums need more than the list.
   const size_t off_part = off_ce;
   const size_t off_L = off_ce + std::max(up256(sizeof(CuspEntry) * (size_t)sd.n_rtiles * (RENDER_BLOCK / 64)),
                                          up256(sizeof(float2) * (size_t)sd.n_ptiles));

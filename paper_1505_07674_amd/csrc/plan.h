@@ -18,9 +18,14 @@ namespace lensed {
 struct TileShape {
   int TW, TH;
 };
-// The tiles of psf_single_kernel (one image at a time, up to four waves of pixels per SIMD).
+// The tile of psf_single_kernel (one image at a time, up to four waves of pixels per
+// SIMD). A tile of 16 x 8, with four times the blocks, gained at most 0.4 us of the kernel's
+// 5.4 (7 x 7 taps, up to 16 x 16 pixels) and lost elsewhere; calls in a row with 16 x 8 against
+// 32 x 16: 7 x 7 taps 16.6 and 16.7 us at 32 x 32 pixels, 17.3 and 16.9 at 64 x 64, 22.2 and 17.7
+// at 200 x 200; 21 x 21 taps 20.8 and 19.8 at 32 x 32, 27.7 and 22.0 at 200 x 200.
 constexpr int64_t SINGLE_MAX_PIXELS = 1 << 18;
-inline bool is_single_tile(TileShape t) { return (t.TW == 32 && t.TH == 16) || (t.TW == 16 && t.TH == 8); }
+constexpr TileShape SINGLE_TILE{32, 16};
+inline bool is_single_tile(TileShape t) { return t.TW == SINGLE_TILE.TW && t.TH == SINGLE_TILE.TH; }
 
 // Chooses the TW x TH output tile of the PSF/chi^2 kernel for a launch. The
 // model counts lane slots of the stencil (ragged tiles and partly idle waves

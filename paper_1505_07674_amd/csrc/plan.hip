@@ -65,12 +65,10 @@ double TileCache::model_cost(int H, int W, int ph, int pw, TileShape t, int max_
   return ntiles * (lanes * (per_lane + 200.0) + staging + 20.0 * t.TW * t.TH + 4000.0);
 }
 
-// One image: the small tiles of psf_single_kernel, as long as the image leaves the
-// chip mostly idle with them; a larger image takes the tile of the batches.
+// One image: the tile of psf_single_kernel, as long as the image leaves the chip mostly
+// idle with it; a larger image takes the tile of the batches.
 TileShape TileCache::latency_best(const lensed_system& s) {
-  const int64_t npix = (int64_t)s.height * s.width;
-  if (npix > SINGLE_MAX_PIXELS) return model_best(s);
-  return npix > 128 * 128 ? TileShape{32, 16} : TileShape{16, 8};
+  return (int64_t)s.height * s.width > SINGLE_MAX_PIXELS ? model_best(s) : SINGLE_TILE;
 }
 
 std::string TileCache::key(const lensed_system* s, int n) {

@@ -1,5 +1,5 @@
 """Images of one or two rows or columns through lensed_loglike_noalloc: their ragged
-PSF tiles hold as few as 8 pixels, so the tile sums can need more of the static
+PSF tiles hold as few as 16 pixels, so the tile sums can need more of the static
 workspace than the work list whose place they take. Every such image is taken, with the
 log L of lensed_loglike, bit for bit; only what exceeds the workspace is refused."""
 import numpy as np
@@ -21,7 +21,7 @@ def thin(h, w):
     return lensed.System(torch.ones((3, 3), device=DEV), data, torch.ones_like(data), pixscale=0.02, nsub=1)
 
 
-# both sides of the change of tiles at 2^14 pixels and of the single-image tiles at 2^18
+# among them both sides of the largest image that takes the single-image tile, 2^18 pixels
 @pytest.mark.parametrize("h,w", [(1, 1), (1, 2048), (1, 16384), (1, 16385), (1, 1 << 18), (1, (1 << 18) + 1), (2, 9000),
                                  (300, 1), (1000, 2), (16384, 1), (16385, 1), (1 << 18, 1), ((1 << 18) + 1, 1)])
 def test_thin_images_are_taken(h, w):
