@@ -226,9 +226,10 @@ __device__ __forceinline__ float grad_poly(const float* p, float z) {
 // those of the render; but the cusp correction takes back what grad_kernel added, so
 // the two share every expression from here to the moments, without contractions that
 // a compiler might make in one of them only. (At an odd N that is no power of two the
-// middle offset comes out as about 1e-8 of a pixel, not 0, and a light centre exactly
-// there is a singular point of the profile: its own light's partials are then off by
-// what that subsample weighs.)
+// middle offset comes out as about 1e-8 of a pixel, where the render's is 0. Where a
+// pixel's centre lies on the lens's, that subsample is then deflected and its steep light
+// dimmed, unlike in the render: errors of the gradient of 1e-5 to 1e-3 of its norm, and of
+// its own size for lens lights of n = 6 and more. (2k + 1 - N)/(2N) would be exact.)
 __device__ __forceinline__ float grad_offset(int k, float iN) { return fmaf((float)k + 0.5f, iN, -0.5f); }
 
 // What depends on the row of subsamples only.
@@ -429,10 +430,11 @@ __device__ __forceinline__ float lane_value(float v, int lane) {
 
 // One thread per pixel, one block per (point, render tile): sums
 // g_pix * d^2/N^2 * dI/dtheta over the pixel's subsamples, then over the block.
-// What bounds it: the issue rate, about 100 vector instructions a subsample (12 of
-// them transcendental) in the modes with a logarithm; 174 before the source frame,
-// the deflection polynomials and every per-point factor of the partials were folded
-// into constants, and the q derivative and Y^2 taken from other moments. 1024 points
+// What bounds it: the issue rate, 117 vector instructions a subsample by the counters
+// (11.5 of them transcendental; what a pixel and the block sums take is among them); 187
+// before the source frame, the deflection polynomials and every per-point factor of the
+// partials were folded into constants, and the q derivative and Y^2 taken from other
+// moments. 1024 points
 // of 200 x 200 pixels (41 % of them in the support), N = 4: 1107 -> 745 us, 30 us of it
 // from the block sums by 16 lanes a moment instead of a wave. Six waves per SIMD hide
 // the transcendental chains; five and seven measured the same.

@@ -21,7 +21,7 @@
 //                     applies Adam to it.
 // One Adam step at 4096 rows: 1959 us with one kernel per layer and reduction, 49 us
 // so (rows 27, weight gradients 13, sums 6, weight conversion 5 us, of which a
-// launch is about 4 each); predictions for 16384 rows 154 -> 29 us. What is left
+// launch is about 4 each); predictions for 16384 rows 154 -> 30 us. What is left
 // is latency: 12.6 million SiLUs are 6 us of vector work, the products 4 us.
 //
 // Flat parameter layout (float32): W1 [256][17], b1 [256], W2 [256][256], b2,

@@ -18,8 +18,8 @@
 // root and one reciprocal (both refined to float64), and 13 multiply-adds each
 // for the atan and the atanh, with constants folded per point in the prologue
 // and two subsamples interleaved: about 340 slots. 256 points of the 41-parameter model
-// (200 x 200 pixels, N = 4) on one card: render 3.65 -> 1.62 ms; gradients of 64
-// points 2.62 -> 0.66 ms (closed-form moments in two kinds of passes instead of dual
+// (200 x 200 pixels, N = 4) on one card: render 3.65 -> 1.65 ms; gradients of 64
+// points 2.62 -> 0.65 ms (closed-form moments in two kinds of passes instead of dual
 // numbers in one pass per component).
 #include <hip/hip_runtime.h>
 

@@ -249,7 +249,7 @@ __global__ __launch_bounds__(64 * CUSP_WAVES, 4) void cusp_kernel(WorkArgs w, co
 // the gradient's correction. The registers of the corrections do not matter where
 // the launch has at most four waves per SIMD (FUSED_MAX_WAVES), the second launch
 // does: one image of 200 x 200 pixels, N = 4, 12.5 us in two kernels, 7.6 us in one (with
-// the tile sums added in the PSF's launch, a log L of 64 x 64 pixels 22 -> 13 us, of
+// the tile sums added in the PSF's launch, a log L of 64 x 64 pixels 22 -> 13 to 15 us, of
 // 200 x 200 25.5 -> 23 us); 16 gradients of 87 x 101 pixels, N = 3, 14.0 -> 9.5 us of render
 // and 80 -> 76.5 us a call.
 constexpr int FUSED_BLOCK = 64 * CUSP_WAVES;
