@@ -602,6 +602,11 @@ __global__ __launch_bounds__(64 * GCUSP_WAVES, 4) void grad_cusp_kernel(WorkArgs
           const float iN = 1.0f / (float)N;
           const float y = fmaf(gq.uy + (Rg ? Rg->x[ky] : grad_offset(ky, iN)), gq.d, gq.cy);
           const float x = fmaf(gq.ux + (Rg ? Rg->x[kx] : grad_offset(kx, iN)), gq.d, gq.cx);
+          // the middle subsample of an odd N in a pixel centred on the lens (y and x may miss it
+          // by 1e-8 of a pixel): no deflection there, while 1e-8 of a pixel off it is
+          // theta_E and would multiply the steep source's gradient
+          const bool centre = 2 * ky + 1 == N && 2 * kx + 1 == N && fmaf(gq.uy, gq.d, gq.cy) == 0.0f &&
+                              fmaf(gq.ux, gq.d, gq.cx) == 0.0f;
           const double oy = Rg ? Rg->xd[ky] : ((double)ky + 0.5) / N - 0.5;
           const double ox = Rg ? Rg->xd[kx] : ((double)kx + 0.5) / N - 0.5;
           const float sw = Rg ? Rg->w[kx] * Rg->w[ky] : 1.0f;
@@ -616,7 +621,7 @@ __global__ __launch_bounds__(64 * GCUSP_WAVES, 4) void grad_cusp_kernel(WorkArgs
             const GradRow row(U, y);
             subsample_grad<M::RM, M::SER, true, true, false>(U, row, x, sw, diff, X, Y);
 #pragma unroll
-            for (int k = 0; k < NPAR; ++k) diff[k] = -diff[k];
+            for (int k = 0; k < NPAR; ++k) diff[k] = centre && k < 5 ? 0.0f : -diff[k];   // 0..4: the deflection's
             subsample_grad<M::RM, M::SER, true, false, false>(U, row, x, sw, diff);
           });
           const float wg = -(float)sd.wgt * G[goff + qpix];

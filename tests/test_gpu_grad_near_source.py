@@ -1,0 +1,43 @@
+"""A cuspy source right behind the lens centre, with a subsample exactly on that centre: the
+re-traced subsample's partials take the deflection that it has there, none, also at the odd
+N whose abscissae in the float32 part of the gradient miss the centre by a rounding. Against
+the oracle, 1e-4 of the norm (test_gpu_grad.py), partial by partial for the lens's, which a
+source's steep gradient times a deflection of theta_E would swamp."""
+import numpy as np
+import pytest
+import torch
+
+import oracle
+import paper_1505_07674_amd as lensed
+from paper_1505_07674_amd import mocks
+
+from helpers import f32
+from test_gpu_grad import oracle_grads, small_spec
+
+pytestmark = pytest.mark.gpu
+RADII = [0.0, 1e-7, 1e-5, 1e-3, 0.01, 0.02]   # arcsec, inside the re-traced radius
+
+
+def to(a):
+    return torch.from_numpy(np.ascontiguousarray(a, np.float32)).to("cuda:0")
+
+
+@pytest.mark.parametrize("n", [1.5, 4.0])
+@pytest.mark.parametrize("N,rule", [(3, "sub"), (4, "sub"), (5, "sub"), (9, "sub"), (1, "g3k7")])
+def test_source_behind_the_lens_centre(N, rule, n):
+    spec = small_spec(H=31, W=29, N=N, center=(0.0, 0.0))
+    rng = np.random.default_rng(5)
+    data, weight = rng.uniform(0, 2, (31, 29)).astype(np.float32), rng.uniform(0.5, 2, (31, 29)).astype(np.float32)
+    gs = lensed.System(to(spec.psf), to(data), to(weight), pixscale=spec.pixscale, nsub=N, rule=rule)
+    osys = oracle.System(31, 29, f32(spec.pixscale), N, spec.psf.astype(np.float64), data.astype(np.float64),
+                         weight.astype(np.float64), rule=None if rule == "sub" else rule)
+    pts = mocks.points(spec, len(RADII), seed=11).astype(np.float32)
+    pts[:, 5], pts[:, 7], pts[:, 14] = 0.01, 0.5, n   # a faint, flat lens light
+    pts[:, 10], pts[:, 11] = np.multiply(RADII, 0.8), np.multiply(RADII, 0.6)
+    _, g = lensed.loglike_grad(to(pts), gs)
+    g = g.cpu().numpy().astype(np.float64)
+    _, want = oracle_grads(osys, pts)
+    rel = np.linalg.norm(g - want, axis=1) / np.linalg.norm(want, axis=1)
+    lens = np.linalg.norm((g - want)[:, :5], axis=1) / np.linalg.norm(want[:, :5], axis=1)
+    print(f"N = {N}, {rule}, n = {n}: norm {rel.max():.1e}, lens partials {lens.max():.1e}", flush=True)
+    assert np.all(rel <= 1e-4) and np.all(lens <= 1e-3)
