@@ -114,6 +114,7 @@ struct GradUniform {
   float gXx, gYx, gXy, gYy;   // d(R^2/R_e^2)/d beta in the SIE frame: 2 (gXx X + gYx Y, gXy X + gYy Y)
   float h11, h12, h21, h22;
   float he, hB, se, sB;       // 1/(2n), b_n log2(e)
+  float floor;                // least R^2/R_e^2 of the source's float32 slope: the re-traced radius
   float s11, s12, s21, s22;   // source frame of an offset from the source centre
   float kb, kc;               // modes 2, 3: b = sign(y') (kb log2((psi + q'|y'|)/r) + kc)
   float s, hs2, iq2;          // 1 - q^2; 1/s (0 where the series in s is taken); 1/q^2
@@ -128,6 +129,7 @@ constexpr float SIE_TINY = 1e-30f;
 // Least psi^2 of the gradient: ten times the smallest normal float32, since the hardware's rsq takes a
 // subnormal for 0 and x'/psi at the centre would be 0 x inf.
 constexpr double GRAD_PSI2_MIN = 1.2e-37;
+constexpr float GRAD_R2_MIN = 1e-37f;   // and of R^2/R_e^2 under its reciprocal
 
 // Extra per-point values needed by the adjoint.
 struct GradConst {
@@ -147,7 +149,7 @@ struct GradConst {
   float src_jac[14];
   int srcpos;
   GradUniform u;
-  float pad[15];
+  float pad[14];
 };
 static_assert(sizeof(GradConst) == 112 * 4, "GradConst layout");
 
