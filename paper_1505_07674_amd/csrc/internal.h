@@ -95,7 +95,11 @@ struct PointConst64 {
   double sx0, sy0;                // source centre
   int closed;                     // sie_ab's form
   int pad0;
-  double pad[4];
+  // offsets from the source centre below this are 0: with an image-plane source position the
+  // centre is the image of a point under the same lens, and a subsample on that point
+  // differs from it by the rounding of the two computations (0 otherwise)
+  double snap;
+  double pad[3];
 };
 static_assert(sizeof(PointConst64) == 16 * 8, "PointConst64 layout");
 

@@ -501,7 +501,8 @@ __global__ __launch_bounds__(PROLOGUE_THREADS) void prologue_kernel(
       e.m22 = m22;
       e.sx0 = xs;
       e.sy0 = ys;
-      for (int i = 0; i < 4; ++i) e.pad[i] = 0.0;
+      e.snap = srcpos ? 1e-14 * (1.0 + fabs(te) + fabs(v[0]) + fabs(v[1])) : 0.0;
+      for (int i = 0; i < 3; ++i) e.pad[i] = 0.0;
       if (!valid) e.m11 = e.m12 = e.m22 = __builtin_nan("");
       p64s[p] = e;
     }

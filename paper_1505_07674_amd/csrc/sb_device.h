@@ -54,8 +54,9 @@ __device__ __forceinline__ void source_offset_f64(const PointConst64& e, const P
   const double xp = e.cL * x + e.sL * y, yp = e.cL * y - e.sL * x;
   const SieAB o = e.closed ? sie_ab<true>(e.q2, e.qp, e.s2, xp, yp) : sie_ab<false>(e.q2, e.qp, e.s2, xp, yp);
   const double ax = e.f * (e.cL * o.a - e.sL * o.b), ay = e.f * (e.sL * o.a + e.cL * o.b);
-  dx = (float)(e.m11 * x + e.m12 * y - ax - e.sx0);
-  dy = (float)(e.m12 * x + e.m22 * y - ay - e.sy0);
+  const double ex = e.m11 * x + e.m12 * y - ax - e.sx0, ey = e.m12 * x + e.m22 * y - ay - e.sy0;
+  dx = fabs(ex) < e.snap ? 0.0f : (float)ex;
+  dy = fabs(ey) < e.snap ? 0.0f : (float)ey;
 }
 
 // ---------------------------------------------------------------------------
