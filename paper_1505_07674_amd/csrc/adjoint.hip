@@ -240,10 +240,11 @@ struct GradRow {
 };
 
 // One Sersic at frame coordinates (X, Y): E = I/I_e, Et = E t and D = E t/R^2
-// (dI/dR^2 = -I_e b e D; 0 at the centre, where t = 0), and its five moments. R^2 under D's
-// quotient is at least `floor`.
-template <bool WT>
-__device__ __forceinline__ float sersic_moments(float X, float Y, float e, float B, float floor, float sw, float* acc) {
+// (dI/dR^2 = -I_e b e D; 0 at the centre, where t = 0), and its five moments. R^2 below
+// U.near2 is U.under in D's quotient with NEAR, and GRAD_R2_MIN at least without.
+template <bool WT, bool NEAR>
+__device__ __forceinline__ float sersic_moments(const GradUniform& U, float X, float Y, float e, float B, float sw,
+                                                float* acc) {
   #pragma clang fp contract(off)
   const float R2 = fmaf(X, X, Y * Y);
   const float L2 = hw_log2(R2);
@@ -251,7 +252,7 @@ __device__ __forceinline__ float sersic_moments(float X, float Y, float e, float
   float E = hw_exp2(fmaf(-B, t, B));
   if (WT) E *= sw;
   const float Et = E * t;
-  const float D = Et * hw_rcp(fmaxf(R2, floor));
+  const float D = Et * hw_rcp(NEAR ? (R2 < U.near2 ? U.under : R2) : fmaxf(R2, GRAD_R2_MIN));
   const float DX = D * X;
   acc[0] += E;
   acc[1] += Et;
@@ -309,8 +310,8 @@ __device__ __forceinline__ void subsample_grad(const GradUniform& U, const GradR
   const float Y = AT ? oY : fmaf(U.Ya, a, fmaf(U.Yb, b, fmaf(U.A2, x, row.rY)));
   // inside the re-traced radius the correction takes back what is added here, and D = E t / R^2
   // of a subsample 1e-7 arcsec from a cuspy source, where X and Y are rounding errors, would
-  // leave its own rounding (1e-7 of 1e5 times the others) behind: the floor keeps it small
-  const float D = sersic_moments<WT>(X, Y, U.se, U.sB, AT ? GRAD_R2_MIN : U.floor, sw, acc + 12);
+  // leave its own rounding (1e-7 of 1e5 times the others) behind: near2 and under keep it small
+  const float D = sersic_moments<WT, !AT>(U, X, Y, U.se, U.sB, sw, acc + 12);
   const float DX = D * X, DY = D * Y;
   const float Gx = fmaf(U.gXx, DX, U.gYx * DY), Gy = fmaf(U.gXy, DX, U.gYy * DY);
   acc[0] = fmaf(b, Gy, fmaf(a, Gx, acc[0]));
@@ -328,7 +329,7 @@ __device__ __forceinline__ void subsample_grad(const GradUniform& U, const GradR
   acc[5] += Gx;
   acc[6] += Gy;
   if (LIGHT)
-    (void)sersic_moments<WT>(fmaf(U.h11, x, row.h12y), fmaf(U.h21, x, row.h22y), U.he, U.hB, GRAD_R2_MIN, sw, acc + 7);
+    (void)sersic_moments<WT, false>(U, fmaf(U.h11, x, row.h12y), fmaf(U.h21, x, row.h22y), U.he, U.hB, sw, acc + 7);
 }
 
 // Calls f with the point's mode as a type: the choices are per point, taken once

@@ -558,7 +558,9 @@ __global__ __launch_bounds__(PROLOGUE_THREADS) void prologue_kernel(
       u.hB = (float)(bh * LOG2E);
       u.se = (float)s.comp[C_S][4];
       u.sB = (float)(bs * LOG2E);
-      u.floor = c.cusp_r2 > 0.0f ? c.cusp_r2 : GRAD_R2_MIN;
+      const double near = GRAD_ROUNDING * (fabs(te) + fabs(xs) + fabs(ys)) / t[13];
+      u.near2 = c.cusp_r2 > 0.0f ? c.cusp_r2 : fmaxf((float)(near * near), GRAD_R2_MIN);
+      u.under = c.cusp_r2 > 0.0f ? c.cusp_r2 : __builtin_inff();
       u.s11 = (float)s11;
       u.s12 = (float)s12;
       u.s21 = (float)s21;
