@@ -240,8 +240,8 @@ struct GradRow {
 };
 
 // One Sersic at frame coordinates (X, Y): E = I/I_e, Et = E t and D = E t/R^2
-// (dI/dR^2 = -I_e b e D; 0 at the centre, where t = 0), and its five moments. R^2 below
-// U.near2 is U.under in D's quotient with NEAR, and GRAD_R2_MIN at least without.
+// (dI/dR^2 = -I_e b e D; 0 at the centre, where t = 0), and its five moments. With NEAR
+// D is 0 where R^2 < U.near2.
 template <bool WT, bool NEAR>
 __device__ __forceinline__ float sersic_moments(const GradUniform& U, float X, float Y, float e, float B, float sw,
                                                 float* acc) {
@@ -252,7 +252,7 @@ __device__ __forceinline__ float sersic_moments(const GradUniform& U, float X, f
   float E = hw_exp2(fmaf(-B, t, B));
   if (WT) E *= sw;
   const float Et = E * t;
-  const float D = Et * hw_rcp(NEAR ? (R2 < U.near2 ? U.under : R2) : fmaxf(R2, GRAD_R2_MIN));
+  const float D = NEAR ? (R2 < U.near2 ? 0.0f : Et * hw_rcp(R2)) : Et * hw_rcp(fmaxf(R2, GRAD_R2_MIN));
   const float DX = D * X;
   acc[0] += E;
   acc[1] += Et;
@@ -308,9 +308,6 @@ __device__ __forceinline__ void subsample_grad(const GradUniform& U, const GradR
   }
   const float X = AT ? oX : fmaf(U.Xa, a, fmaf(U.Xb, b, fmaf(U.A1, x, row.rX)));
   const float Y = AT ? oY : fmaf(U.Ya, a, fmaf(U.Yb, b, fmaf(U.A2, x, row.rY)));
-  // inside the re-traced radius the correction takes back what is added here, and D = E t / R^2
-  // of a subsample 1e-7 arcsec from a cuspy source, where X and Y are rounding errors, would
-  // leave its own rounding (1e-7 of 1e5 times the others) behind: near2 and under keep it small
   const float D = sersic_moments<WT, !AT>(U, X, Y, U.se, U.sB, sw, acc + 12);
   const float DX = D * X, DY = D * Y;
   const float Gx = fmaf(U.gXx, DX, U.gYx * DY), Gy = fmaf(U.gXy, DX, U.gYy * DY);

@@ -118,8 +118,7 @@ struct GradUniform {
   float gXx, gYx, gXy, gYy;   // d(R^2/R_e^2)/d beta in the SIE frame: 2 (gXx X + gYx Y, gXy X + gYy Y)
   float h11, h12, h21, h22;
   float he, hB, se, sB;       // 1/(2n), b_n log2(e)
-  float near2, under;         // where the source's R^2/R_e^2 is below near2, its slope is over `under` instead: the
-                              // re-traced radius in both; or GRAD_ROUNDING and inf, no slope
+  float near2;                // R^2/R_e^2 of the source below which float32 takes no slope (GRAD_ROUNDING)
   float s11, s12, s21, s22;   // source frame of an offset from the source centre
   float kb, kc;               // modes 2, 3: b = sign(y') (kb log2((psi + q'|y'|)/r) + kc)
   float s, hs2, iq2;          // 1 - q^2; 1/s (0 where the series in s is taken); 1/q^2
@@ -135,9 +134,10 @@ constexpr float SIE_TINY = 1e-30f;
 // subnormal for 0 and x'/psi at the centre would be 0 x inf.
 constexpr double GRAD_PSI2_MIN = 1.2e-37;
 constexpr float GRAD_R2_MIN = 1e-37f;   // and of R^2/R_e^2 under its reciprocal
-// Offset from a source of n <= 1, which is not re-traced, as a part of theta_E + |x_S| + |y_S|, that may
-// all be rounding: float32 does not have its direction. A subsample on the centre has no slope, as in
-// float64; another is this close once in 1e7 points.
+// Offset from the source, as a part of theta_E + |x_S| + |y_S|, that may all be rounding: float32 does
+// not have its direction. For n <= 1 a subsample on the centre then has no slope, as in float64 (another
+// is this close once in 1e7 points). For n > 1 the re-tracing gives the slope; float32's, 1e5 times
+// another subsample's, would leave its rounding behind when the correction takes it back.
 constexpr double GRAD_ROUNDING = 1e-6;
 
 // Extra per-point values needed by the adjoint.
@@ -158,7 +158,7 @@ struct GradConst {
   float src_jac[14];
   int srcpos;
   GradUniform u;
-  float pad[13];
+  float pad[14];
 };
 static_assert(sizeof(GradConst) == 112 * 4, "GradConst layout");
 
