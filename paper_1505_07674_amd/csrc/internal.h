@@ -138,7 +138,7 @@ constexpr float GRAD_R2_MIN = 1e-37f;   // and of R^2/R_e^2 under its reciprocal
 // not have its direction. For n <= 1 a subsample on the centre then has no slope, as in float64 (another
 // is this close once in 1e7 points). For n > 1 the re-tracing gives the slope; float32's, 1e5 times
 // another subsample's, would leave its rounding behind when the correction takes it back.
-constexpr double GRAD_ROUNDING = 1e-6;
+constexpr float GRAD_ROUNDING = 1e-6f;
 
 // Extra per-point values needed by the adjoint.
 struct GradConst {

@@ -558,8 +558,8 @@ __global__ __launch_bounds__(PROLOGUE_THREADS) void prologue_kernel(
       u.hB = (float)(bh * LOG2E);
       u.se = (float)s.comp[C_S][4];
       u.sB = (float)(bs * LOG2E);
-      const double near = GRAD_ROUNDING * (fabs(te) + fabs(xs) + fabs(ys)) / t[13];
-      u.near2 = fmaxf((float)(near * near), GRAD_R2_MIN);
+      const float near = GRAD_ROUNDING * (float)(fabs(te) + fabs(xs) + fabs(ys)) / t[13];
+      u.near2 = fmaxf(near * near, GRAD_R2_MIN);
       if (c.cusp_r2 > 0.0f) u.near2 = fminf(u.near2, 0.25f * c.cusp_r2);   // well inside the re-traced radius
       u.s11 = (float)s11;
       u.s12 = (float)s12;
